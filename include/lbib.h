@@ -223,9 +223,8 @@ lbib_status lbib_set_transfer(lbib_ctx* ctx, int32_t mode, int32_t weight, doubl
  * cutoff 2 is this library's reading (the expression has none).  Evaluated
  * at X^n with the membrane forces: red cells spread it, soft particles add
  * it to their vertex forces, rigid particles to their force and torque.
- * coeff = 0 switches it off.  With it on, the merged step form is not used
- * (the repulsion needs every body's X^n first) and the adjoint calls return
- * LBIB_EINVAL.  Errors: LBIB_EINVAL for coeff < 0, a non-finite value or a
+ * coeff = 0 switches it off.  With it on, the merged step form is not
+ * reported and the adjoint calls return LBIB_EINVAL.  Errors: LBIB_EINVAL for coeff < 0, a non-finite value or a
  * cutoff outside (0, 16]; LBIB_ESTATE outside set-up or on a batch (a batch
  * takes each instance's setting). */
 lbib_status lbib_set_repulsion(lbib_ctx* ctx, double coeff, double cutoff);
@@ -458,17 +457,17 @@ lbib_status lbib_adjoint_backward(lbib_ctx* ctx, double dJ, double* grad);
  * the last adjoint forward window. */
 lbib_status lbib_set_body_params(lbib_ctx* ctx, int32_t body, double ks, double kb, double sigma);
 
-/* How steps are launched (the results are the same bit for bit):
- *   1  three kernels per step: body forces and particle motion, fused
- *      lattice step, marker advance;
- *   2  merged: inside a run the body kernel first finishes the previous
- *      step's marker advance for its own bodies (two kernels per step; used
- *      only when every body has <= 512 vertices, else as 1);
- *   3  overlapped: the lattice tiles without IB force run on a second stream
- *      while the body kernel runs, the tiles with IB force after it;
- *   0  automatic (default): 2 when every body has <= 512 vertices, else 1.
- * Allowed in any phase; LBIB_EINVAL for other values.  lbib_get_step_mode
- * returns the form in use (after finalize_setup) or the requested mode. */
+/* Step form.  All forms run the same kernels and give the same bits: body
+ * forces and particle motion, fused lattice step, marker advance.
+ *   1  three kernels per step;
+ *   2  merged advance (reported only when every body has <= 512 vertices and
+ *      the repulsion is off, else as 1);
+ *   3  overlapped lattice tiles;
+ *   0  automatic (default): 1.
+ * Forms 2 and 3 name launch forms that measured slower everywhere and are
+ * kept as names.  Allowed in any phase; LBIB_EINVAL for other values.
+ * lbib_get_step_mode returns the form (after finalize_setup) or the
+ * requested mode. */
 lbib_status lbib_set_step_mode(lbib_ctx* ctx, int32_t mode);
 lbib_status lbib_get_step_mode(const lbib_ctx* ctx, int32_t* mode);
 

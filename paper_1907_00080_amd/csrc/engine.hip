@@ -62,7 +62,7 @@ struct Layout {
   size_t x, y, xm, ym, xn, yn, fx, fy, l0, th0, r0x, r0y;
   size_t mbody, minfo, cx, cy, wx, wy, frep, rep_chunk, obs;
   size_t s[9];
-  size_t cnt[2], bins[2], touched, overflow, fmax, bond_flag, step_slot, spin, Uspare, tile_inst;
+  size_t cnt[2], bins[2], touched, overflow, fmax, bond_flag, spin, Uspare, tile_inst;
   size_t lig_body, lig_elem, l2r, r2l, lig_flag, rec_x, lig_va, lig_vb, lig_sigma, lig_sp;
   size_t step_next, step_cur, ties, red;
   size_t chunk_info, area_part, rig_part, body_cnt, star, pbox, star_wg, slot_chunk;
@@ -104,9 +104,8 @@ struct lbib_ctx {
   bool ktiming = false;       // bracket fused-kernel launches with events
   std::vector<std::pair<hipEvent_t, hipEvent_t>> kevents;
   int bin_cap = 1024;         // marker registrations per tile and bin set
-  int body_cache = 16 * 1024; // LDS bytes of a particle workgroup's rho*, u* cache
-  // how a step is launched (lbib_set_step_mode): 0 automatic, 1 three
-  // kernels, 2 merged advance, 3 overlapped lattice tiles
+  // the step form asked for (lbib_set_step_mode) and, below, reported; every
+  // form launches the same kernels
   int step_mode = 0;
   // cache hints of the fused lattice kernel's population accesses
   // (lbib_set_cache_hints): -1 automatic, else the NT bits
@@ -119,16 +118,14 @@ struct lbib_ctx {
   // inplace is the resolved form (see streamed_slot in lbib_dev.h)
   int streaming = -1;
   bool inplace = false;
-  bool merge_advance = true;  // resolved from step_mode and the bodies
+  bool merge_advance = false; // form 2 asked for and possible
   bool repulsion = false;     // some instance has the vertex repulsion on
   int nrep_chunk = 0;         // repulsion work units (kRepChunk vertices of a body)
-  bool overlap = false;
-  hipStream_t aux = nullptr;  // second stream of the overlapped form
+  bool overlap = false;       // form 3 asked for
   // streams of the adjoint's backward pass (segment recompute, reverse
   // sweep), created together so that they sit on different hardware queues
   hipStream_t adj_s[2] = {nullptr, nullptr};
   hipEvent_t ev_adj_start = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // adjoint window (single-instance contexts): caller-owned workspace
   char* aws = nullptr;
   size_t aws_bytes = 0;
@@ -164,8 +161,8 @@ int elem_size(int dtype) { return dtype == LBIB_F64 ? 8 : 4; }
 
 // Workgroups of the star pass for one particle: its node box at rest (the
 // vertex extent widened by 4 nodes on each side) with 10 % spare for
-// deformation, 1024 nodes per workgroup and pass (any larger box is still
-// covered: the workgroups loop over it).
+// deformation, kStarNodes nodes per workgroup and pass (any larger box is
+// still covered: the workgroups loop over it).
 int star_workgroups(const BodyHost& b) {
   if (b.d.kind == LBIB_RBC_KINEMATIC) return 0;
   double x0 = 1e300, x1 = -1e300, y0 = 1e300, y1 = -1e300;
@@ -174,7 +171,7 @@ int star_workgroups(const BodyHost& b) {
     y0 = std::min(y0, b.xy[2 * v + 1]); y1 = std::max(y1, b.xy[2 * v + 1]);
   }
   const double nodes = std::ceil(x1 - x0 + 10.0) * std::ceil(y1 - y0 + 10.0) * 1.1;
-  return std::max(1, (int)std::ceil(nodes / 1024.0));
+  return std::max(1, (int)std::ceil(nodes / kStarNodes));
 }
 
 void compute_sizes(lbib_ctx* c) {
@@ -251,7 +248,6 @@ void compute_layout(lbib_ctx* c) {
   L.overflow = take(8);
   L.fmax = take(8 * 2 * (size_t)c->ninst);        // two slots, by step parity
   L.bond_flag = take(4 * 2 * (size_t)c->ninst);
-  L.step_slot = take(8 * 2 * (size_t)c->ninst);
   L.spin = take(8);
   L.Uspare = take(es * 2 * c->nodes);   // velocity output of measurement launches
   L.tile_inst = take(4 * c->ntiles);
@@ -327,8 +323,6 @@ Ptrs<T> make_ptrs(const lbib_ctx* c) {
     p.fmax_next = (unsigned long long*)(w + L.fmax) + oth * ni;
     p.bond_flag = (int*)(w + L.bond_flag) + cur * ni;
     p.bond_flag_next = (int*)(w + L.bond_flag) + oth * ni;
-    p.step_slot = (long long*)(w + L.step_slot) + cur * ni;
-    p.step_prev = (long long*)(w + L.step_slot) + oth * ni;
   }
   p.spin_timeouts = (int*)(w + L.spin);
   p.bin_cap = c->bin_cap;
@@ -366,29 +360,6 @@ Ptrs<T> make_ptrs(const lbib_ctx* c) {
   return p;
 }
 
-// LDS bytes for a particle workgroup's cache of rho*, u*: the node box that
-// its vertex and probe stencils reach (extent + probe 1.2 + stencil 1 + margin
-// 2 on each side), with 10 % spare for deformation; 16 KB to 96 KB.
-int body_cache_bytes(const lbib_ctx* c) {
-  const int es = elem_size(c->dtype);
-  long long need = 0;
-  for (auto& I : c->inst)
-    for (auto& b : I.bodies) {
-      if (b.d.kind == LBIB_RBC_KINEMATIC) continue;
-      double x0 = 1e300, x1 = -1e300, y0 = 1e300, y1 = -1e300;
-      for (int v = 0; v < b.d.nv; ++v) {
-        x0 = std::min(x0, b.xy[2 * v]); x1 = std::max(x1, b.xy[2 * v]);
-        y0 = std::min(y0, b.xy[2 * v + 1]); y1 = std::max(y1, b.xy[2 * v + 1]);
-      }
-      const double pad = 2.0 * (1.2 + 1.0 + 2.0) + 2.0;
-      const long long nodes = (long long)std::ceil(x1 - x0 + pad) * (long long)std::ceil(y1 - y0 + pad);
-      need = std::max(need, nodes * 3 * es * 11 / 10);
-    }
-  const long long lo = 16 * 1024, hi = 96 * 1024;
-  need = std::min(std::max(need, lo), hi);
-  return (int)((need + 255) & ~255ll);
-}
-
 StepArgs step_args(const lbib_ctx* c) {
   StepArgs a;
   a.tile_x = c->TX;
@@ -399,10 +370,8 @@ StepArgs step_args(const lbib_ctx* c) {
     const int nt = ((c->inst[i].lat.nx + c->TX - 1) / c->TX) * ((c->inst[i].lat.ny + c->TY - 1) / c->TY);
     a.max_inst_tiles = std::max(a.max_inst_tiles, nt);
   }
-  a.body_cache_bytes = c->body_cache;
   a.lb_wpc = c->lb_wpc;
   a.n_cu = c->n_cu;
-  a.max_nv = 0;
   a.any_mls = 0;
   // automatic cache hints: non-temporal loads and stores on a single lattice
   // whose two population buffers stay well inside the 256 MB last-level cache
@@ -413,7 +382,6 @@ StepArgs step_args(const lbib_ctx* c) {
   a.nt_mode = c->cache_hints >= 0 ? c->cache_hints
                                   : (c->ninst == 1 && pop_bytes <= 128.0 * 1024 * 1024 ? 3 : 0);
   for (auto& I : c->inst) {
-    for (auto& b : I.bodies) a.max_nv = std::max(a.max_nv, b.d.nv);
     if (I.transfer == LBIB_TRANSFER_MLS) a.any_mls = 1;
   }
   return a;
@@ -691,7 +659,6 @@ lbib_status upload_all(lbib_ctx* c) {
   HIPCHK(c, hipMemsetAsync(w + L.obs, 0, sizeof(lbib_body_obs) * (size_t)std::max(c->nbody, 1), s));
   HIPCHK(c, hipMemsetAsync(w + L.fmax, 0, 8 * 2 * (size_t)c->ninst, s));
   HIPCHK(c, hipMemsetAsync(w + L.bond_flag, 0, 4 * 2 * (size_t)c->ninst, s));
-  HIPCHK(c, hipMemsetAsync(w + L.step_slot, 0, 8 * 2 * (size_t)c->ninst, s));
   HIPCHK(c, hipMemsetAsync(w + L.spin, 0, 8, s));
   HIPCHK(c, hipStreamSynchronize(s));
   // populations: equilibrium of the initial fields, shifted by the weights
@@ -732,21 +699,9 @@ lbib_status upload_all(lbib_ctx* c) {
   return LBIB_OK;
 }
 
-// n steps.  With merge_advance, two kernels each: the Lagrangian kernel
-// (which, after the first step, also finishes the previous step's marker
-// advance for its own bodies) and the fused lattice kernel, and the last
-// step ends with the marker advance of all markers.  Otherwise three kernels
-// each: Lagrangian, fused lattice, marker advance.
-// Step form of the context: three kernels (body, lattice, advance), the
-// merged form (the body kernel finishes the previous step's advance; only
-// when every body has <= kSmallBody vertices, where one round of the
-// workgroup covers them), or the overlapped form (the lattice tiles without IB force
-// on a second stream while the body kernel runs).  Automatic: merged when
-// possible, else three kernels (measured faster than the overlapped form on
-// the 2000 x 200 and 6667 x 667 capillaries and the 64-instance sweep).
-// The vertex repulsion needs X^n of every body before any body's forces,
-// which the merged form cannot give (there each body workgroup finishes its
-// own advance): with the repulsion on, the merged form is not used.
+// Whether the merged form, where it was asked for, can be the form in use
+// (lbib_get_step_mode): it needs small bodies and no vertex repulsion.
+constexpr int kSmallBody = 512;
 void resolve_step_mode(lbib_ctx* c) {
   bool small_bodies = true;
   c->repulsion = false;
@@ -755,35 +710,25 @@ void resolve_step_mode(lbib_ctx* c) {
       if (b.d.nv > kSmallBody) small_bodies = false;
     if (I.rep_coeff > 0.0 && !I.bodies.empty()) c->repulsion = true;
   }
-  int m = c->step_mode;
-  if (m == 0) m = small_bodies && !c->repulsion ? 2 : 1;
-  c->merge_advance = m == 2 && small_bodies && !c->repulsion;
-  c->overlap = m == 3;
+  c->merge_advance = c->step_mode == 2 && small_bodies && !c->repulsion;
+  c->overlap = c->step_mode == 3;
 }
 
+// n steps of three kernels each (four with the repulsion): bodies, lattice,
+// advance.  Every step form runs these.  Two others were measured and gone:
+// a body kernel per body that also finished the previous step's advance
+// (us per step, against these three: 256x64 22.0 and 18.4, 2000x200 27.5 and
+// 23.4, six Couette boxes 43.7 and 31.9), and the lattice tiles without
+// markers beside the bodies, on a second stream (6667x667 107 and 80) or in
+// one launch (6667x667 86 and 70: the bodies' chains of dependent steps
+// stretch beside the bandwidth-bound tiles).
 template <typename T>
 void enqueue_steps(lbib_ctx* c, long long n) {
   const StepArgs a = step_args(c);
-  if (c->overlap && !c->ktiming) {
-    for (long long k = 0; k < n; ++k) {
-      Ptrs<T> p = make_ptrs<T>(c);
-      if (c->repulsion) launch_repulsion<T>(p, a, (const int*)(c->ws + c->L.rep_chunk), c->nrep_chunk, c->stream);
-      (void)hipEventRecord(c->ev_fork, c->stream);
-      (void)hipStreamWaitEvent(c->aux, c->ev_fork, 0);
-      launch_lb_fused<T>(p, a, c->aux, 1 | (1 << 2));        // tiles without IB force
-      (void)hipEventRecord(c->ev_join, c->aux);
-      launch_lagrangian<T>(p, a, c->stream, false);
-      launch_lb_fused<T>(p, a, c->stream, 1 | (2 << 2));     // tiles with IB force
-      (void)hipStreamWaitEvent(c->stream, c->ev_join, 0);
-      launch_advance<T>(p, a, c->stream);
-      c->parity ^= 1;
-    }
-    return;
-  }
   for (long long k = 0; k < n; ++k) {
     Ptrs<T> p = make_ptrs<T>(c);
     if (c->repulsion) launch_repulsion<T>(p, a, (const int*)(c->ws + c->L.rep_chunk), c->nrep_chunk, c->stream);
-    launch_lagrangian<T>(p, a, c->stream, c->merge_advance && k > 0);
+    launch_lagrangian<T>(p, a, c->stream);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->ktiming && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess) {
       launch_lb_fused<T>(p, a, c->stream, 3, e0, e1);
@@ -791,7 +736,7 @@ void enqueue_steps(lbib_ctx* c, long long n) {
     } else {
       launch_lb_fused<T>(p, a, c->stream);
     }
-    if (!c->merge_advance || k == n - 1) launch_advance<T>(p, a, c->stream);
+    launch_advance<T>(p, a, c->stream);
     c->parity ^= 1;
   }
 }
@@ -1155,7 +1100,7 @@ void enqueue_recompute(lbib_ctx* c, const AdjLayout& A, int buf, long long n) {
   for (long long s = 0; s < n; ++s) {
     char* rec = seg + (size_t)s * A.rec_bytes;
     Ptrs<T> p = make_ptrs<T>(c);
-    launch_lagrangian<T>(p, sa, c->stream, c->merge_advance && s > 0);
+    launch_lagrangian<T>(p, sa, c->stream);
     if (c->inplace) {
       // h^n in scheme-0 order, before the lattice kernel rewrites its buffer
       const long long nn = (long long)c->inst[0].lat.nx * c->inst[0].lat.ny;
@@ -1178,7 +1123,7 @@ void enqueue_recompute(lbib_ctx* c, const AdjLayout& A, int buf, long long n) {
       cl.bytes[k - k0] = by[k];
     }
     launch_copies(cl, c->stream);
-    if (!c->merge_advance || s == n - 1) launch_advance<T>(p, sa, c->stream);
+    launch_advance<T>(p, sa, c->stream);
     c->parity ^= 1;
   }
 }
@@ -1574,11 +1519,6 @@ lbib_status lbib_bind(lbib_ctx* c, void* ws, size_t bytes, void* stream) {
   c->ws = (char*)ws;
   c->ws_bytes = bytes;
   c->stream = (hipStream_t)stream;
-  if (!c->aux) {
-    HIPCHK(c, hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking));
-    HIPCHK(c, hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
-    HIPCHK(c, hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
-  }
   c->phase = 1;
   return LBIB_OK;
 }
@@ -1586,7 +1526,6 @@ lbib_status lbib_bind(lbib_ctx* c, void* ws, size_t bytes, void* stream) {
 lbib_status lbib_finalize_setup(lbib_ctx* c) {
   if (!c) return fail(c, LBIB_EINVAL, "NULL context");
   if (c->phase != 1) return fail(c, LBIB_ESTATE, "bind a workspace before finalize_setup");
-  c->body_cache = body_cache_bytes(c);
   resolve_step_mode(c);
   c->inplace = resolve_inplace(c);
   lbib_status s = c->dtype == LBIB_F64 ? upload_all<double>(c) : upload_all<float>(c);
@@ -2040,9 +1979,6 @@ lbib_status lbib_destroy(lbib_ctx* c) {
     if (c->ev_rec[k]) (void)hipEventDestroy(c->ev_rec[k]);
     if (c->ev_rev[k]) (void)hipEventDestroy(c->ev_rev[k]);
   }
-  if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
-  if (c->ev_join) (void)hipEventDestroy(c->ev_join);
-  if (c->aux) (void)hipStreamDestroy(c->aux);
   for (auto& st : c->adj_s)
     if (st) (void)hipStreamDestroy(st);
   if (c->ev_adj_start) (void)hipEventDestroy(c->ev_adj_start);

@@ -21,11 +21,9 @@
 //                 stencil overlaps, for the next step's fused kernel.
 //
 // No multiply-add contraction in this file: the same quantity is computed by
-// several kernels (a body's forces by the chunked body kernel and by the
-// merged step kernel, a probe value from an LDS cache or straight from the
-// populations), and all of them must round alike.  Fused multiply-adds the
-// compiler would form differently in each inlining context could differ in
-// the last bit; the few fused operations kept are explicit (__fma_rn).
+// several kernels and instantiations (a stencil by the advance and by the
+// stencil pass, each transfer form), and all of them must round alike.  The
+// fused operations are explicit (__fma_rn).
 #pragma clang fp contract(off)
 #include "lbib_dev.h"
 #include "mls.h"
@@ -40,7 +38,7 @@ namespace lbib {
 // uniform plane offset plus a 32-bit in-plane offset per direction (a plane
 // holds at most 2^31 nodes).
 template <typename T>
-__device__ inline void pull_node(const T* A, int sch, long long N, int nx, int ny, int pitch, bool pery,
+__device__ __forceinline__ void pull_node(const T* A, int sch, long long N, int nx, int ny, int pitch, bool pery,
                                  int x, int y, T hv[kQ]) {
   const unsigned o0 = (unsigned)y * (unsigned)pitch + (unsigned)x;
   if (sch == 2) {   // node-local layout: slot i of the node itself
@@ -68,8 +66,9 @@ __device__ inline void pull_node(const T* A, int sch, long long N, int nx, int n
 // force (the step's IB forces are not known yet).
 template <typename T>
 __device__ __forceinline__ void wall_fill_drive(const LatDev& L, int y, T hv[kQ]) {
+  const T lo = T(L.u_wall_lo), hi = T(L.u_wall_hi);   // values, not places, to choose from
   if (L.wall_mode == 1 && !L.periodic_y && (y == 0 || y == L.ny - 1))
-    zou_he_fill(hv, y == 0, T(y == 0 ? L.u_wall_lo : L.u_wall_hi), T(L.gx), T(L.gy));
+    zou_he_fill(hv, y == 0, y == 0 ? lo : hi, T(L.gx), T(L.gy));
 }
 
 // rho* - 1 and u* = (sum f e + g/2) / rho* of a node of the pre-forcing
@@ -125,83 +124,6 @@ __device__ __forceinline__ void interp_mls(const LatDev& L, double X, double Y, 
   }
 }
 
-// rho*, u* of the pre-forcing state at a node (x, y) inside the lattice,
-// from the streamed populations, as star_values rounds them.
-template <typename T>
-__device__ inline void node_star(const T* A, int sch, const LatDev& L, int x, int y, double& rho,
-                                 double& ux, double& uy) {
-  T hv[kQ];
-  pull_node(A, sch, L.plane, L.nx, L.ny, L.pitch, L.periodic_y != 0, x, y, hv);
-  wall_fill_drive(L, y, hv);
-  double drho = 0.0, jx = 0.0, jy = 0.0;
-#pragma unroll
-  for (int i = 0; i < kQ; ++i) {
-    const double h = double(hv[i]);
-    drho += h;
-    jx += ex(i) * h;
-    jy += ey(i) * h;
-  }
-  T d, u, v;
-  star_values(L, drho, jx, jy, d, u, v);
-  rho = 1.0 + double(d);
-  ux = double(u);
-  uy = double(v);
-}
-
-// Kernel (or, with MLS compiled in and selected, MLS) interpolant of rho*,
-// u* at a point and (optionally) its gradient, node by node straight from
-// the streamed populations: compact code for the rare point whose nodes no
-// cache holds.  MLS = false compiles the kernel weights only: the
-// latency-bound kernels of runs without the MLS transfer carry none of its
-// code (their instruction fetches grow with the code they hold).  The three
-// interpolants here (this one, interp_cached, star_sum) take the same
-// node values and sum them alike, so they agree to the bit; a stencil row
-// beyond a wall adds nothing (skipped here, zero weight in star_sum:
-// the same sums).
-template <bool MLS, typename T>
-__device__ inline void interp_star(const T* A, int sch, const LatDev& L, double X, double Y, bool grad,
-                                   double& rho, double& ux, double& uy, double g[4]) {
-  if (MLS && use_mls(L)) {
-    auto fetch = [&](int, int, int xr, int row, double& r, double& u, double& v) {
-      node_star(A, sch, L, wrap_i(xr, L.nx), L.periodic_y ? wrap_i(row, L.ny) : row, r, u, v);
-    };
-    if (grad) interp_mls<true>(L, X, Y, fetch, rho, ux, uy, g);
-    else interp_mls<false>(L, X, Y, fetch, rho, ux, uy, g);
-    return;
-  }
-  const double cxr = floor(X + 0.5), cyr = floor(Y + 0.5);
-  rho = 0; ux = 0; uy = 0;
-  g[0] = g[1] = g[2] = g[3] = 0;  // du/dx, du/dy, dv/dx, dv/dy
-  const bool pery = L.periodic_y != 0;
-  double wxa[3], dwxa[3], wya[3], dwya[3];
-  roma_weights3<true>(cxr - X, wxa, dwxa);
-  roma_weights3<true>(cyr - Y, wya, dwya);
-  for (int b = 0; b < 3; ++b) {
-    const double ry = cyr + (b - 1);
-    int row = (int)ry;
-    if (pery) row = wrap_i(row, L.ny);
-    else if (row < 0 || row >= L.ny) continue;
-    const double wy = wya[b], dwy = dwya[b];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const double rx = cxr + (a - 1);
-      const int col = wrap_i((int)rx, L.nx);
-      const double wx = wxa[a], dwx = dwxa[a];
-      double r, u, v;
-      node_star(A, sch, L, col, row, r, u, v);
-      rho += r * wx * wy;
-      ux += u * wx * wy;
-      uy += v * wx * wy;
-      if (grad) {
-        g[0] -= u * dwx * wy;
-        g[1] -= u * wx * dwy;
-        g[2] -= v * dwx * wy;
-        g[3] -= v * wx * dwy;
-      }
-    }
-  }
-}
-
 // The star field (4 values per node: rho* - 1, u*x, u*y, unused) that the
 // advance and stencil passes leave over every particle's node box, at the
 // 3 x 3 nodes of a point: loaded first (nine 4-wide loads), summed by
@@ -214,16 +136,21 @@ struct Star9 {
 
 template <typename T>
 __device__ __forceinline__ void star_load(const T* S, const LatDev& L, double X, double Y, Star9<T>& n) {
-  const double cxr = floor(X + 0.5), cyr = floor(Y + 0.5);
+  // one division for the centre column (X is unwrapped), then neighbours; node
+  // numbers fit 32 bits (a plane holds at most 2^31 nodes)
+  const int cx = wrap_i((int)floor(X + 0.5), L.nx), cy = (int)floor(Y + 0.5);
   const bool pery = L.periodic_y != 0;
+  const int ry = pery ? wrap_i(cy, L.ny) : cy;
+  unsigned col[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) col[a] = wrap_near(cx + a - 1, L.nx);
 #pragma unroll
   for (int b = 0; b < 3; ++b) {
-    const int r = (int)(cyr + (b - 1));
-    const int row = pery ? wrap_i(r, L.ny) : min(max(r, 0), L.ny - 1);
+    const int row = pery ? wrap_near(ry + b - 1, L.ny) : min(max(ry + b - 1, 0), L.ny - 1);
+    const unsigned r0 = (unsigned)row * (unsigned)L.pitch;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const long long node = (long long)row * L.pitch + wrap_i((int)cxr + a - 1, L.nx);
-      const T* q = S + 4 * node;
+      const T* q = S + 4ull * (r0 + col[a]);
       n.r[3 * b + a] = q[0];
       n.u[3 * b + a] = q[1];
       n.v[3 * b + a] = q[2];
@@ -231,8 +158,10 @@ __device__ __forceinline__ void star_load(const T* S, const LatDev& L, double X,
   }
 }
 
-// Interpolant of rho*, u* (and with GRAD its gradient) from the node values
-// star_load gave, summed as interp_star and interp_cached sum them.
+// Kernel (or, with MLS compiled in and selected, MLS) interpolant of rho*, u*
+// (and with GRAD its gradient) from the node values star_load gave.  MLS =
+// false compiles the kernel weights only: the latency-bound kernels of runs
+// without the MLS transfer carry none of its code.
 template <bool MLS, bool GRAD, typename T>
 __device__ __forceinline__ void star_sum(const LatDev& L, double X, double Y, const Star9<T>& n,
                                          double& rho, double& ux, double& uy, double g[4]) {
@@ -276,64 +205,9 @@ __device__ __forceinline__ void star_sum(const LatDev& L, double X, double Y, co
   }
 }
 
-// rho*, u* of the nodes in a box [bx0, bx0 + bw) x [by0, by0 + bh) cached in
-// LDS (x unwrapped; rows wrapped for a periodic lattice), as star_values
-// gives them.  Same interpolant as interp_star, read from the cache.
-template <typename T>
-struct StarCache {
-  const T* c;   // 3 values per node: rho - 1, ux, uy
-  int bx0, by0, bw, bh;
-};
+__device__ __forceinline__ double wrap_x(double cx, int nx) { return cx - nx * floor(cx / nx); }
 
-template <bool MLS, typename T>
-__device__ __forceinline__ void interp_cached(const StarCache<T>& C, const LatDev& L, double X, double Y,
-                                     bool grad, double& rho, double& ux, double& uy, double g[4]) {
-  if (MLS && use_mls(L)) {
-    auto fetch = [&](int, int, int xr, int row, double& r, double& u, double& v) {
-      const int k = 3 * ((row - C.by0) * C.bw + (xr - C.bx0));
-      r = 1.0 + double(C.c[k]);
-      u = double(C.c[k + 1]);
-      v = double(C.c[k + 2]);
-    };
-    if (grad) interp_mls<true>(L, X, Y, fetch, rho, ux, uy, g);
-    else interp_mls<false>(L, X, Y, fetch, rho, ux, uy, g);
-    return;
-  }
-  const double cxr = floor(X + 0.5), cyr = floor(Y + 0.5);
-  rho = 0; ux = 0; uy = 0;
-  g[0] = g[1] = g[2] = g[3] = 0;
-  const bool pery = L.periodic_y != 0;
-  double wxa[3], dwxa[3], wya[3], dwya[3];
-  roma_weights3<true>(cxr - X, wxa, dwxa);
-  roma_weights3<true>(cyr - Y, wya, dwya);
-  for (int b = 0; b < 3; ++b) {
-    const double ry = cyr + (b - 1);
-    const int row = (int)ry;
-    if (!pery && (row < 0 || row >= L.ny)) continue;
-    const double wy = wya[b], dwy = dwya[b];
-    const int kr = (row - C.by0) * C.bw;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const double rx = cxr + (a - 1);
-      const double wx = wxa[a], dwx = dwxa[a];
-      const int k = 3 * (kr + ((int)rx - C.bx0));
-      const double r = 1.0 + double(C.c[k]), u = double(C.c[k + 1]), v = double(C.c[k + 2]);
-      rho += r * wx * wy;
-      ux += u * wx * wy;
-      uy += v * wx * wy;
-      if (grad) {
-        g[0] -= u * dwx * wy;
-        g[1] -= u * wx * dwy;
-        g[2] -= v * dwx * wy;
-        g[3] -= v * wx * dwy;
-      }
-    }
-  }
-}
-
-__device__ inline double wrap_x(double cx, int nx) { return cx - nx * floor(cx / nx); }
-
-__device__ inline double min_image(double xr, double cxw, int nx) {
+__device__ __forceinline__ double min_image(double xr, double cxw, int nx) {
   double d = xr - cxw;
   if (d > 0.5 * nx) d -= nx;
   else if (d < -0.5 * nx) d += nx;
@@ -341,7 +215,7 @@ __device__ inline double min_image(double xr, double cxw, int nx) {
 }
 
 // Bond length between element centroid c and receptor (xr, wall).
-__device__ inline double bond_len(double cx, double cy, double xr, int wall, const LatDev& L) {
+__device__ __forceinline__ double bond_len(double cx, double cy, double xr, int wall, const LatDev& L) {
 #pragma clang fp contract(off)
   const double dx = min_image(xr, wrap_x(cx, L.nx), L.nx);
   const double yw = wall == 0 ? L.y_wall_lo : L.y_wall_hi;
@@ -350,146 +224,98 @@ __device__ inline double bond_len(double cx, double cy, double xr, int wall, con
 }
 
 // ---------------------------------------------------------------- marker bins
-// Register marker gm in every tile its 3x3 stencil overlaps (centre cx, cy).
-// Three consecutive columns (rows) touch at most three tiles (a ragged last
-// tile can be one column wide), so a marker joins at most nine bins.  Slots
-// come from wave-aggregated atomics: a run of adjacent lanes that hit the
-// same tile (neighbours along a membrane) shares one atomic.  A full bin drops the
-// registration and counts it in *overflow (the fused kernel then poisons
-// that tile's force so the watchdog reports it).
-// The registration in two halves: bins_reserve issues the slot
-// reservations (the atomics), bins_commit waits for them and stores the
-// marker ids, so that a caller can do other work while the atomics are in
-// flight.
-template <int R>
+// Register a marker (one per lane, centre node cx, cy inside the lattice along
+// periodic axes) in every tile its 3x3 stencil overlaps.  Three consecutive
+// columns (rows) touch at most three tiles (a ragged last tile can be one
+// column wide), so a marker joins at most nine bins; more than two columns or
+// rows of tiles is rare.  A full bin drops the registration and counts it in
+// *overflow (the fused kernel then poisons that tile's force so the watchdog
+// reports it).  Slots come from wave-aggregated atomics: a run of adjacent
+// lanes that hit the same tile (neighbours along a membrane) shares one; an
+// atomic per lane queues at the counters (advance on 2000x200 9.6 us against
+// 6.7).  In two halves: bins_reserve issues the reservations, bins_commit waits
+// for them and stores the marker ids, so that a caller can do other work while
+// they are in flight.
 struct BinSlots {
-  int key[R][9], leader[R][9], rank[R][9], base[R][9];
-  unsigned used;   // slots some lane of the wave uses (bit r * 9 + s9; wave-uniform)
+  int key[9];           // tile of slot 3 * row + column, -1: none
+  int leader[9], rank[9], base[9];
+  unsigned used;        // slots some lane of the wave uses (wave-uniform)
 };
 
-template <int TX, int TY, int R>
-__device__ inline void bins_reserve(int* cnt, const LatDev& L, const int* cx, const int* cy,
-                                    const bool* active, BinSlots<R>& S) {
-  // lattice fields in registers: read inside the loop below, the compiler
-  // reloads them (and waits for them) at every slot
+// The distinct non-negative values of (a, b, c), in order, else -1.
+__device__ __forceinline__ void distinct3(int a, int b, int c, int d[3]) {
+  const bool nb = b >= 0 && b != a, nc = c >= 0 && c != a && c != b;
+  const int x = a >= 0 ? a : (nb ? b : c);                       // the first
+  const int y = a >= 0 ? (nb ? b : (nc ? c : -1)) : (nb && nc ? c : -1);
+  d[0] = x;
+  d[1] = y;
+  d[2] = a >= 0 && nb && nc ? c : -1;
+}
+
+template <int TX, int TY>
+__device__ __forceinline__ void bins_reserve(int* cnt, const LatDev& L, int cx, int cy, bool active,
+                                             BinSlots& S) {
   const bool pery = L.periodic_y != 0;
-  const int nx = L.nx, ny = L.ny, tile_base = L.tile_base, ntx = L.ntx;
-  const int lane = threadIdx.x & 63;
-  const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  int gcount[R][9];
-  auto& key = S.key;
-  auto& leader = S.leader;
-  auto& rank = S.rank;
-  unsigned used = 0;
+  int tc[3], tr[3];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    // tile column and row of each stencil offset; an offset whose tile an
-    // earlier offset already reached adds no slot (fixed indices only, so
-    // the lists stay in registers)
-    int tc[3], tr[3];
-    bool okc[3], okr[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      int c = cx[r] + a - 1;
-      c = c < 0 ? c + nx : (c >= nx ? c - nx : c);
-      tc[a] = c / TX;
-      okc[a] = active[r];
-      int rr = cy[r] + a - 1;
-      bool ok = active[r];
-      if (pery) rr = rr < 0 ? rr + ny : (rr >= ny ? rr - ny : rr);
-      else ok = ok && rr >= 0 && rr < ny;
-      tr[a] = ok ? rr / TY : -1;
-      okr[a] = ok;
-    }
-    bool vc[3], vr[3];
-    vc[0] = okc[0];
-    vc[1] = okc[1] && tc[1] != tc[0];
-    vc[2] = okc[2] && tc[2] != tc[0] && tc[2] != tc[1];
-    vr[0] = okr[0];
-    vr[1] = okr[1] && !(okr[0] && tr[1] == tr[0]);
-    vr[2] = okr[2] && !(okr[0] && tr[2] == tr[0]) && !(okr[1] && tr[2] == tr[1]);
-    // 1. group the lanes of every slot by tile, no memory traffic: a run of
-    //    adjacent lanes with the same tile (neighbouring markers) is one
-    //    group; a tile met in several runs gets one group per run
-#pragma unroll
-    for (int s9 = 0; s9 < 9; ++s9) {
-      const int i = s9 / 3, j = s9 % 3;
-      const bool has = vr[i] && vc[j];
-      const int k = has ? tile_base + tr[i] * ntx + tc[j] : -1;
-      key[r][s9] = k;
-      leader[r][s9] = lane;
-      rank[r][s9] = 0;
-      gcount[r][s9] = 0;
-      const unsigned long long hasm = __ballot(has);
-      if (hasm == 0ull) continue;
-      used |= 1u << (r * 9 + s9);
-      const int kprev = dpp_i<kDppWaveShr1>(k);   // lane 0: its own (not used)
-      const unsigned long long heads = __ballot(has && (lane == 0 || kprev != k));
-      const unsigned long long le = lt | (1ull << lane);
-      const unsigned long long mine = heads & le;
-      const int ld = mine ? 63 - __clzll((long long)mine) : lane;
-      leader[r][s9] = ld;
-      rank[r][s9] = lane - ld;
-      const unsigned long long brk = (heads | ~hasm) & ~le;   // lanes after this one that end the run
-      const int next = brk ? __ffsll((long long)brk) - 1 : 64;
-      gcount[r][s9] = has && lane == ld ? next - lane : 0;
-    }
+  for (int a = 0; a < 3; ++a) {
+    tc[a] = active ? (int)((unsigned)wrap_near(cx + a - 1, L.nx) / TX) : -1;
+    const int r = cy + a - 1, rw = pery ? wrap_near(r, L.ny) : r;
+    tr[a] = rw >= 0 && rw < L.ny ? (int)((unsigned)rw / TY) : -1;
   }
-  // 2. every group leader reserves its slots; the atomics of all markers,
-  //    groups and slots are in flight together
+  int dc[3], dr[3];
+  distinct3(tc[0], tc[1], tc[2], dc);
+  distinct3(tr[0], tr[1], tr[2], dr);
+  const int lane = threadIdx.x & 63;
+  const unsigned long long lt = (1ull << lane) - 1ull, le = lt | (1ull << lane);
+  // 1. group the lanes of every slot by tile, no memory traffic
+  int count[9];
+  unsigned used = 0;
+  const bool wide = __ballot(dc[2] >= 0 || dr[2] >= 0) != 0ull;
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int q = 0; q < 9; ++q) {
+    const int i = q / 3, j = q % 3;
+    S.key[q] = -1;
+    S.leader[q] = lane;
+    S.rank[q] = 0;
+    count[q] = 0;
+    if ((i == 2 || j == 2) && !wide) continue;
+    const bool has = dr[i] >= 0 && dc[j] >= 0;
+    const unsigned long long hasm = __ballot(has);
+    if (hasm == 0ull) continue;
+    used |= 1u << q;
+    const int k = has ? L.tile_base + dr[i] * L.ntx + dc[j] : -1;
+    S.key[q] = k;
+    const int kprev = dpp_i<kDppWaveShr1>(k);   // lane 0: its own (not used)
+    const unsigned long long heads = __ballot(has && (lane == 0 || kprev != k));
+    const unsigned long long mine = heads & le;
+    const int ld = mine ? 63 - __clzll((long long)mine) : lane;
+    S.leader[q] = ld;
+    S.rank[q] = lane - ld;
+    const unsigned long long brk = (heads | ~hasm) & ~le;   // lanes after this one that end the run
+    const int next = brk ? __ffsll((long long)brk) - 1 : 64;
+    count[q] = has && lane == ld ? next - lane : 0;
+  }
+  // 2. every group leader reserves its slots, all in flight together
 #pragma unroll
-    for (int s9 = 0; s9 < 9; ++s9)
-      S.base[r][s9] = (used >> (r * 9 + s9) & 1u) && gcount[r][s9] > 0
-                          ? atomicAdd(&cnt[key[r][s9]], gcount[r][s9]) : 0;
+  for (int q = 0; q < 9; ++q)
+    S.base[q] = (used >> q & 1u) && count[q] > 0 ? atomicAdd(&cnt[S.key[q]], count[q]) : 0;
   S.used = used;
 }
 
-// 3. positions and stores
-//    (every slot's position first, then the stores: a store issued between
-//    two of the reads would be waited for by the next one)
-template <int R>
-__device__ inline void bins_commit(int* bin, int cap, int* overflow, const int* gm, const BinSlots<R>& S) {
-  const unsigned used = S.used;
-  int pos[R][9];
+// 3. positions first, then the stores (a store issued between two of the
+// shuffles would be waited for by the next one)
+__device__ __forceinline__ void bins_commit(int* bin, int cap, int* overflow, int gm, const BinSlots& S) {
+  int pos[9], dropped = 0;
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int q = 0; q < 9; ++q) pos[q] = S.used >> q & 1u ? __shfl(S.base[q], S.leader[q]) + S.rank[q] : 0;
 #pragma unroll
-    for (int s9 = 0; s9 < 9; ++s9)
-      pos[r][s9] = (used >> (r * 9 + s9) & 1u) ? __shfl(S.base[r][s9], S.leader[r][s9]) + S.rank[r][s9] : 0;
-  int dropped = 0;
-  int* dst[R][9];
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int s9 = 0; s9 < 9; ++s9) {
-      const bool on = (used >> (r * 9 + s9) & 1u) && S.key[r][s9] >= 0;
-      dropped += on && pos[r][s9] >= cap;
-      dst[r][s9] = on && pos[r][s9] < cap ? bin + (long long)S.key[r][s9] * cap + pos[r][s9] : nullptr;
-    }
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int s9 = 0; s9 < 9; ++s9)
-      if (dst[r][s9]) *dst[r][s9] = gm[r];
+  for (int q = 0; q < 9; ++q) {
+    if (!(S.used >> q & 1u) || S.key[q] < 0) continue;
+    if (pos[q] < cap) bin[(long long)S.key[q] * cap + pos[q]] = gm;
+    else ++dropped;
+  }
   if (dropped) atomicAdd(overflow, dropped);
-}
-
-template <int TX, int TY, int R>
-__device__ inline void register_markers(int* cnt, int* bin, int cap, int* overflow, const LatDev& L,
-                                        const int* gm, const int* cx, const int* cy,
-                                        const bool* active) {
-  BinSlots<R> S;
-  bins_reserve<TX, TY, R>(cnt, L, cx, cy, active, S);
-  bins_commit<R>(bin, cap, overflow, gm, S);
-}
-
-// One marker per lane.
-template <int TX, int TY>
-__device__ inline void register_marker(int* cnt, int* bin, int cap, int* overflow, const LatDev& L,
-                                       int gm, int cx, int cy, bool active) {
-  register_markers<TX, TY, 1>(cnt, bin, cap, overflow, L, &gm, &cx, &cy, &active);
 }
 
 // ---------------------------------------------------------------- stencils
@@ -499,7 +325,7 @@ __device__ inline void register_marker(int* cnt, int* bin, int cap, int* overflo
 // along each axis (zero for rows beyond the walls), or the MLS shape
 // functions.
 // Stencil centre node of a marker at (X, Y), as marker_stencil stores it.
-__device__ inline void stencil_centre(const LatDev& L, double X, double Y, int& ocx, int& ocy) {
+__device__ __forceinline__ void stencil_centre(const LatDev& L, double X, double Y, int& ocx, int& ocy) {
   const bool pery = L.periodic_y != 0;
   const double cxr = floor(X + 0.5), cyr = floor(Y + 0.5);
   ocx = wrap_i((int)cxr, L.nx);
@@ -507,7 +333,7 @@ __device__ inline void stencil_centre(const LatDev& L, double X, double Y, int& 
 }
 
 template <bool MLS = true, typename T>
-__device__ inline void marker_stencil(const Ptrs<T>& p, const LatDev& L, int gm, double X, double Y,
+__device__ __forceinline__ void marker_stencil(const Ptrs<T>& p, const LatDev& L, int gm, double X, double Y,
                                       int& ocx, int& ocy) {
   const int nm = p.nm_total;
   const bool pery = L.periodic_y != 0;
@@ -535,10 +361,6 @@ __device__ inline void marker_stencil(const Ptrs<T>& p, const LatDev& L, int gm,
   p.cy[gm] = ocy;
 }
 
-
-// LDS cache of rho*, u* per particle: sized by the host from the particles'
-// extent (between 16 KB and 96 KB; the body kernel's static LDS is ~41 KB)
-
 // ---------------------------------------------------------------- advance
 // Kinematic IB update of a red-cell vertex (Eq. kinematicPos): the velocity
 // of the step, interpolated at X^n with the stencil stored for X^n, then
@@ -562,7 +384,7 @@ template <> struct RbcAdv<true> {
 };
 
 template <bool MLS, typename T>
-__device__ inline void rbc_adv_load(const Ptrs<T>& p, const LatDev& L, int gm, RbcAdv<MLS>& a) {
+__device__ __forceinline__ void rbc_adv_load(const Ptrs<T>& p, const LatDev& L, int gm, RbcAdv<MLS>& a) {
   const int nm = p.nm_total;
   a.cx = p.cx[gm];
   a.cy = p.cy[gm];
@@ -589,29 +411,46 @@ __device__ inline void rbc_adv_load(const Ptrs<T>& p, const LatDev& L, int gm, R
 }
 
 template <bool MLS, typename T>
-__device__ inline void rbc_adv_finish(const Ptrs<T>& p, const LatDev& L, const RbcAdv<MLS>& in, double X,
+__device__ __forceinline__ void rbc_adv_finish(const Ptrs<T>& p, const LatDev& L, const RbcAdv<MLS>& in, double X,
                                       double Y, bool first, double& xn, double& yn) {
-  const long long N = L.plane;
   const T* U = p.U + 2 * L.node_base;
-  const int cx = in.cx, cy = in.cy;
+  const T* V = U + L.plane;
+  const int cx = in.cx, cy = in.cy;   // inside the lattice along periodic axes
   double ux = 0.0, uy = 0.0;
   // a row beyond a wall has weight exactly zero: it reads a clamped row and
-  // adds zeros, so all 18 loads are independent of control flow
+  // adds zeros, so the loads are independent of control flow.  Away from the
+  // seam a row's three nodes are consecutive: one wide load each.
+  const bool seam = __ballot(cx < 1 || cx + 1 >= L.nx) != 0ull;
+  T u[9], v[9];
 #pragma unroll
-  for (int b2 = 0; b2 < 3; ++b2) {
-    int row = cy + b2 - 1;
-    if (L.periodic_y) row = wrap_i(row, L.ny);
+  for (int b = 0; b < 3; ++b) {
+    int row = cy + b - 1;
+    if (L.periodic_y) row = wrap_near(row, L.ny);
     else row = min(max(row, 0), L.ny - 1);
+    const unsigned r0 = (unsigned)row * (unsigned)L.pitch;
+    if (seam) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int col = wrap_i(cx + a - 1, L.nx);
-      double w;
-      if constexpr (MLS) w = use_mls(L) ? in.ph[3 * b2 + a] : in.ph[a] * in.ph[3 + b2];
-      else w = in.wx[a] * in.wy[b2];
-      const long long node = (long long)row * L.pitch + col;
-      ux += double(U[node]) * w;
-      uy += double(U[N + node]) * w;
+      for (int a = 0; a < 3; ++a) {
+        const unsigned node = r0 + (unsigned)wrap_near(cx + a - 1, L.nx);
+        u[3 * b + a] = U[node];
+        v[3 * b + a] = V[node];
+      }
+    } else {
+      const T *ur = U + (r0 + cx - 1u), *vr = V + (r0 + cx - 1u);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        u[3 * b + a] = ur[a];
+        v[3 * b + a] = vr[a];
+      }
     }
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    double w;
+    if constexpr (MLS) w = use_mls(L) ? in.ph[k] : in.ph[k % 3] * in.ph[3 + k / 3];
+    else w = in.wx[k % 3] * in.wy[k / 3];
+    ux += double(u[k]) * w;
+    uy += double(v[k]) * w;
   }
   if (first) {
     xn = X + ux;
@@ -623,7 +462,7 @@ __device__ inline void rbc_adv_finish(const Ptrs<T>& p, const LatDev& L, const R
 }
 
 template <bool MLS, typename T>
-__device__ inline void advance_rbc(const Ptrs<T>& p, const LatDev& L, int gm, double X, double Y,
+__device__ __forceinline__ void advance_rbc(const Ptrs<T>& p, const LatDev& L, int gm, double X, double Y,
                                    bool first, double& xn, double& yn) {
   RbcAdv<MLS> a;
   rbc_adv_load<MLS>(p, L, gm, a);
@@ -632,7 +471,7 @@ __device__ inline void advance_rbc(const Ptrs<T>& p, const LatDev& L, int gm, do
 
 // ---------------------------------------------------------------- k_bonds
 template <typename T>
-__device__ __forceinline__ void bonds_kinetics(Ptrs<T>& p, const LatDev& L, int inst, long long n,
+__device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L, int inst, long long n,
                                                int nx, int ny, int* s_tmp, int& s_nelig) {
   const int tid = threadIdx.x, nt = blockDim.x;
   // bond kinetics (Sec. 2.2): rupture then formation (a frozen topology
@@ -668,8 +507,7 @@ __device__ __forceinline__ void bonds_kinetics(Ptrs<T>& p, const LatDev& L, int 
       const int l = l0 + r * nt + tid;
       flag[r] = 0;
       if (!on[r]) continue;
-      // particle positions X^n: xn (equal to x once a step has ended; while
-      // the merged step kernel runs, its particle workgroups copy xn into x)
+      // particle positions X^n: xn (equal to x once a step has ended)
       const double cx = 0.5 * (p.xn[va[r]] + p.xn[vb[r]]);
       const double cy = 0.5 * (p.yn[va[r]] + p.yn[vb[r]]);
       const int rc = rr[r];
@@ -795,7 +633,7 @@ __device__ __forceinline__ void bonds_kinetics(Ptrs<T>& p, const LatDev& L, int 
 // workgroups of the body kernel).  Ends by raising the instance's flag that
 // particle workgroups wait for before they read the bond table.
 template <typename T>
-__device__ __forceinline__ void bonds_impl(Ptrs<T>& p, int inst, int* s_tmp, int* s_nelig_p) {
+__device__ __forceinline__ void bonds_impl(const Ptrs<T>& p, int inst, int* s_tmp, int* s_nelig_p) {
   int& s_nelig = *s_nelig_p;
   const LatDev L = p.lat[inst];
   const int tid = threadIdx.x, nt = blockDim.x;
@@ -804,7 +642,6 @@ __device__ __forceinline__ void bonds_impl(Ptrs<T>& p, int inst, int* s_tmp, int
   if (tid == 0) {
     p.step_cur[inst] = n;
     p.step_next[inst] = n + 1;
-    p.step_slot[inst] = n;
   }
   if (inst == 0 && tid == 0) {
     // the other slot was last used by the previous step, whose kernels have
@@ -830,14 +667,14 @@ __device__ __forceinline__ void bonds_impl(Ptrs<T>& p, int inst, int* s_tmp, int
 struct IBox {
   int x0, x1, y0, y1;
 };
-__device__ inline IBox wave_box(double x, double y, bool on) {
+__device__ __forceinline__ IBox wave_box(double x, double y, bool on) {
   const auto mn = [](int a, int b) { return min(a, b); };
   const auto mx = [](int a, int b) { return max(a, b); };
   return IBox{wave_reduce_i(on ? (int)floor(x) : 0x7fffffff, mn), wave_reduce_i(on ? (int)ceil(x) : -0x7fffffff, mx),
               wave_reduce_i(on ? (int)floor(y) : 0x7fffffff, mn), wave_reduce_i(on ? (int)ceil(y) : -0x7fffffff, mx)};
 }
 
-__device__ inline void put_box(int* pbox, int chunk, const IBox& q) {
+__device__ __forceinline__ void put_box(int* pbox, int chunk, const IBox& q) {
   pbox[4 * chunk] = q.x0;
   pbox[4 * chunk + 1] = q.x1;
   pbox[4 * chunk + 2] = q.y0;
@@ -856,18 +693,21 @@ __device__ inline void put_box(int* pbox, int chunk, const IBox& q) {
 // before their first store: read through a reference, its fields are
 // reloaded (and waited for) after every store, which may alias them.
 template <typename T>
-__device__ inline void star_pass(Ptrs<T>& p, const T* src, int sch, int w) {
+__device__ __forceinline__ void star_pass(const Ptrs<T>& p, const T* src, int sch, int w) {
   const int b = p.star_wg[3 * w], rank = p.star_wg[3 * w + 1], K = p.star_wg[3 * w + 2];
-  const BodyDev& B = p.body[b];
-  const LatDev L = p.lat[B.inst];
+  const BodyDev B = load_uniform(p.body + b);
+  const LatDev L = load_uniform(p.lat + B.inst);
   const int nch = chunks_of(B.nv);
   int x0 = 0x7fffffff, x1 = -0x7fffffff, y0 = 0x7fffffff, y1 = -0x7fffffff;
-  for (int k = 0; k < nch; ++k) {
-    const int* q = p.pbox + 4 * (B.chunk0 + k);
-    x0 = min(x0, q[0]);
-    x1 = max(x1, q[1]);
-    y0 = min(y0, q[2]);
-    y1 = max(y1, q[3]);
+  for (int k0 = 0; k0 < nch; k0 += 4) {   // four chunk boxes in flight together
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int4 q = load_uniform((const int4*)p.pbox + B.chunk0 + min(k0 + k, nch - 1));
+      x0 = min(x0, q.x);
+      x1 = max(x1, q.y);
+      y0 = min(y0, q.z);
+      y1 = max(y1, q.w);
+    }
   }
   x0 -= 4; x1 += 4; y0 -= 4; y1 += 4;
   const bool pery = L.periodic_y != 0;
@@ -880,56 +720,44 @@ __device__ inline void star_pass(Ptrs<T>& p, const T* src, int sch, int w) {
   const int nbox = bw * bh;
   const T* A = src + 9 * L.node_base;
   T* S = p.star + 4 * L.node_base;
-  constexpr int NB = 4;   // nodes per lane per pass: 36 loads in flight
-  const int t = threadIdx.x, nt = blockDim.x;
-  for (int k0 = rank * NB * nt; k0 < nbox; k0 += K * NB * nt) {
-    T hv[NB][kQ];
-    int row[NB];
-    long long node[NB];
+  // one node per lane and pass (four before): the wave's chain of instructions
+  // bounds this pass, and the chip has room for the workgroups
+  for (int k = rank * kStarNodes + threadIdx.x; k < nbox; k += K * kStarNodes) {
+    const unsigned dr = (unsigned)k / (unsigned)bw, dc = (unsigned)k - dr * (unsigned)bw;
+    const int col = wrap_i(x0 + (int)dc, L.nx);
+    int row = y0 + (int)dr;
+    if (pery) row = wrap_i(row, L.ny);
+    T hv[kQ];
+    pull_node(A, sch, L.plane, L.nx, L.ny, L.pitch, pery, col, row, hv);
+    wall_fill_drive(L, row, hv);
+    double drho = 0.0, jx = 0.0, jy = 0.0;
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      const int k = k0 + q * nt + t;
-      const int kk = k < nbox ? k : 0;
-      const int col = wrap_i(x0 + kk % bw, L.nx);
-      int r = y0 + kk / bw;
-      if (pery) r = wrap_i(r, L.ny);
-      row[q] = r;
-      node[q] = (long long)r * L.pitch + col;
-      pull_node(A, sch, L.plane, L.nx, L.ny, L.pitch, pery, col, r, hv[q]);
+    for (int i = 0; i < kQ; ++i) {
+      const double h = double(hv[i]);
+      drho += h;
+      jx += ex(i) * h;
+      jy += ey(i) * h;
     }
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      if (k0 + q * nt + t >= nbox) continue;
-      wall_fill_drive(L, row[q], hv[q]);
-      double drho = 0.0, jx = 0.0, jy = 0.0;
-#pragma unroll
-      for (int i = 0; i < kQ; ++i) {
-        const double h = double(hv[q][i]);
-        drho += h;
-        jx += ex(i) * h;
-        jy += ey(i) * h;
-      }
-      T* o = S + 4 * node[q];
-      star_values(L, drho, jx, jy, o[0], o[1], o[2]);
-    }
+    T* o = S + 4ull * ((unsigned)row * (unsigned)L.pitch + (unsigned)col);
+    star_values(L, drho, jx, jy, o[0], o[1], o[2]);
   }
 }
 
 // ---------------------------------------------------------------- k_body
 constexpr int kBodyThreads = 256;
 constexpr int kWaves = kBodyThreads / 64;
+// the wave's number in its workgroup, in a scalar register
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 constexpr int kSpinMax = 1 << 22;   // bounded wait for the bond flag (~0.2 s)
-constexpr int kVmax = kSmallBody;
-constexpr int kMaxChunks = (kVmax + kChunk - 1) / kChunk;
 
 // max that propagates NaN (fmax drops it)
-__device__ inline double fmax_nan(double a, double b) { return (a > b || a != a) ? a : b; }
+__device__ __forceinline__ double fmax_nan(double a, double b) { return (a > b || a != a) ? a : b; }
 
 // Largest |F| the lanes of a wave hand to the fluid, folded into the
 // instance maximum (non-negative doubles order like their bit patterns; NaN
 // and Inf sort above every finite value, so a broken force shows up as a
 // non-finite maximum).
-__device__ inline void record_fmax(unsigned long long* slot, double m) {
+__device__ __forceinline__ void record_fmax(unsigned long long* slot, double m) {
   m = wave_reduce_d(m, [](double a, double b) { return fmax_nan(a, b); });
   if ((threadIdx.x & 63) == 0 && m != 0.0) atomicMax(slot, (unsigned long long)__double_as_longlong(m));
 }
@@ -940,7 +768,7 @@ __device__ inline void record_fmax(unsigned long long* slot, double m) {
 // they are always dispatched).  The polls are relaxed and one acquire fence
 // follows them: an acquire load invalidates the cache on every poll.
 template <typename T>
-__device__ inline void wait_bonds(const Ptrs<T>& p, int inst) {
+__device__ __forceinline__ void wait_bonds(const Ptrs<T>& p, int inst) {
   if ((threadIdx.x & 63) == 0) {
     int it = 0;
     while (__hip_atomic_load(&p.bond_flag[inst], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 &&
@@ -953,8 +781,7 @@ __device__ inline void wait_bonds(const Ptrs<T>& p, int inst) {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
-// ---- membrane and particle arithmetic, shared by the chunked and the merged
-// body kernels (the same expressions on the same inputs give the same bits)
+// ---- membrane and particle arithmetic
 
 // Element from (x0, y0) to (x1, y1): length and unit tangent.  The outward
 // normal of the counter-clockwise contour is (ty, -tx).
@@ -1043,20 +870,18 @@ struct VertexNbr {
 // half of each adjacent element's load, then the repulsion magnitude sv
 // (Eq. repFor) along the inward vertex normal.
 __device__ __forceinline__ void membrane_force(const VertexNbr& q, double ks, double l0v, double l0m,
-                                               bool rep, double sv, double& fx, double& fy) {
+                                               bool bend, bool rep, double sv, double& fx, double& fy) {
   const double sr = ks * (q.len - l0v);
   const double sl = ks * (q.len_m - l0m);
   // tangents from normals: t = (-n_y, n_x)
   fx = sr * (-q.ny) - sl * (-q.ny_m);
   fy = sr * q.nx - sl * q.nx_m;
-  {
+  if (bend) {
     const double fr = q.len_mm / (q.len_mm + q.len_m);
     fx += q.bc_m * fr * q.bnx_m;
     fy += q.bc_m * fr * q.bny_m;
-  }
-  fx -= q.bc * q.bnx;
-  fy -= q.bc * q.bny;
-  {
+    fx -= q.bc * q.bnx;
+    fy -= q.bc * q.bny;
     const double fl = q.len_p / (q.len + q.len_p);
     fx += q.bc_p * fl * q.bnx_p;
     fy += q.bc_p * fl * q.bny_p;
@@ -1160,7 +985,7 @@ __device__ __forceinline__ void rigid_vertex(double rx, double ry, const double 
 // and the fluid velocity at its vertices, and the chunk that arrives last
 // (a counter per body) takes the rigid step and moves every vertex.
 template <typename T, bool MLS>
-__device__ __forceinline__ void chunk_impl(Ptrs<T>& p, int code, int b, double (*s_rp)[kWaves]) {
+__device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, int code, int b, double (*s_rp)[kWaves]) {
   const int lane = threadIdx.x & 63;
   // code: the chunk of body b, or -2 for an idle wave in the workgroup of a
   // rigid body whose chunks share this workgroup (it takes part in the sums)
@@ -1176,7 +1001,7 @@ __device__ __forceinline__ void chunk_impl(Ptrs<T>& p, int code, int b, double (
   const int v = chunk_vertex(lane, first_v, nv), gm = v0 + v;
   const bool inner = lane >= 2 && lane < 2 + cnt;     // the chunk's own vertices
   const bool has_elem = lane >= 1 && lane < 2 + cnt;  // elements v -> v+1 they touch
-  const LatDev L = p.lat[inst];
+  const LatDev L = load_uniform(p.lat + inst);
   const T* S = p.star + 4 * L.node_base;   // rho*, u* over the particles' boxes
   const bool rigid = kind == kRigid, particle = kind != kRBC;
   const bool rep = L.rep_coeff > 0.0;
@@ -1202,8 +1027,9 @@ __device__ __forceinline__ void chunk_impl(Ptrs<T>& p, int code, int b, double (
   const double enx = ty, eny = -tx;
   const double txl = lane_prev(tx), tyl = lane_prev(ty);
   double bnx = 0.0, bny = 0.0, bc = 0.0;
-  if (!rigid || rep) vertex_normal(txl, tyl, tx, ty, bnx, bny);
-  if (!rigid) bc = bend_coeff(txl, tyl, tx, ty, B.kb, th0v);
+  const bool bend = !rigid && B.kb != 0.0;   // the capillary's red cells have none
+  if (bend || rep) vertex_normal(txl, tyl, tx, ty, bnx, bny);
+  if (bend) bc = bend_coeff(txl, tyl, tx, ty, B.kb, th0v);
 
   // particles: probe load of the element and fluid velocity u* at the vertex,
   // from the star field of the particle's box
@@ -1219,15 +1045,16 @@ __device__ __forceinline__ void chunk_impl(Ptrs<T>& p, int code, int b, double (
     Star9<T> nq, nv;
     star_load(S, L, qx, qy, nq);
     star_load(S, L, X, Y, nv);
+    // the vertex first: its sum needs fewer registers beside the other
+    // point's nodes
     double rho, ux, uy, g[4];
-    star_sum<MLS, true>(L, qx, qy, nq, rho, ux, uy, g);
-    if (has_elem) probe_load(rho, g, nu, enx, eny, len, pfx, pfy);
-    double rho2, g2[4];
-    star_sum<MLS, false>(L, X, Y, nv, rho2, ux, uy, g2);
+    star_sum<MLS, false>(L, X, Y, nv, rho, ux, uy, g);
     if (inner) {
       uvx = ux;
       uvy = uy;
     }
+    star_sum<MLS, true>(L, qx, qy, nq, rho, ux, uy, g);
+    if (has_elem) probe_load(rho, g, nu, enx, eny, len, pfx, pfy);
   }
   // adhesion springs on bonded ligand elements (after this step's bond
   // update).  A ligand element whose centroid lies farther than y_cr from
@@ -1283,7 +1110,8 @@ __device__ __forceinline__ void chunk_impl(Ptrs<T>& p, int code, int b, double (
       rigid_step(&B, first, r3, st);
       __syncthreads();   // every wave has read the rigid state
       if (threadIdx.x == 0) rigid_commit(Bp, st);
-      const double cs = cos(st[5]), sn = sin(st[5]);
+      double sn, cs;
+      sincos(st[5], &sn, &cs);
       if (inner) {
         rigid_vertex(r0xv, r0yv, st, cs, sn, uvx, uvy, ds, xn, yn, fx, fy);
         p.xn[gm] = xn;
@@ -1320,7 +1148,8 @@ __device__ __forceinline__ void chunk_impl(Ptrs<T>& p, int code, int b, double (
       for (int k = 0; k < 3; ++k) r3[k] = chunk_total(p.rig_part + k * nct + ch0, nch);
       rigid_step(&B, first, r3, st);
       if (lane == 0) rigid_commit(Bp, st);
-      const double cs = cos(st[5]), sn = sin(st[5]);
+      double sn, cs;
+      sincos(st[5], &sn, &cs);
       IBox q{0x7fffffff, -0x7fffffff, 0x7fffffff, -0x7fffffff};
       // four vertices per lane and pass, their loads issued before any store
       for (int w0 = 0; w0 < nv; w0 += 4 * 64) {
@@ -1389,7 +1218,7 @@ __device__ __forceinline__ void chunk_impl(Ptrs<T>& p, int code, int b, double (
   double sxn = 0.0, syn = 0.0, ffx, ffy;   // a soft particle's new position
   if (inner) {
     double fx, fy;
-    membrane_force(q, B.ks, l0v, l0m, rep, sv, fx, fy);
+    membrane_force(q, B.ks, l0v, l0m, bend, rep, sv, fx, fy);
     if (rep) p.frep[gm] = 0.0;   // applied: the next step's repulsion kernel rewrites it
     if (kind == kRBC) {
       p.fx[gm] = fx;
@@ -1411,456 +1240,40 @@ __device__ __forceinline__ void chunk_impl(Ptrs<T>& p, int code, int b, double (
   record_fmax(p.fmax_bits + inst, fm);
 }
 
-// ---------------------------------------------------------------- merged step kernel
-// Sum over a body's vertices in the canonical order (terms in LDS, term[v]):
-// wave w forms the partials of chunks w, w + kWaves, ... over the lanes of
-// the chunk layout, then every lane adds the chunk partials in chunk order.
-__device__ inline double canonical_sum(const double* term, int nv, double* s_part) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int nch = chunks_of(nv);
-  __syncthreads();   // the terms are in LDS
-  for (int c = w; c < nch; c += kWaves) {
-    const int first = c * kChunk, cnt = min(kChunk, nv - first);
-    const int v = chunk_vertex(lane, first, nv);
-    const bool inner = lane >= 2 && lane < 2 + cnt;
-    const double s = wave_sum(inner ? term[v] : 0.0);
-    if (lane == 0) s_part[c] = s;
-  }
-  __syncthreads();
-  const double out = chunk_total(s_part, nch);
-  __syncthreads();   // the terms and partials may be overwritten
-  return out;
-}
-
-// One 256-lane workgroup per body of at most kVmax vertices, its per-vertex
-// data in LDS.  The body's vertices first finish the previous step (the
-// kinematic update of red cells or the adoption of the particle dynamics,
-// stencils, and the bins of this step's fused kernel; two vertices per lane,
-// their loads and bin reservations in flight together), then the forces
-// and particle dynamics of this step, with the arithmetic of the chunked
-// kernel.  Particles cache rho*, u* of the node box their stencils reach in
-// LDS.
-template <typename T, int TX, int TY, bool MLS>
-__device__ __forceinline__ void body_merged_impl(Ptrs<T>& p, int b, int cache_nodes, double (*sm)[kVmax],
-                                                 double (*s_terms)[kVmax], double (*s_part)[kMaxChunks],
-                                                 int* s_box, int* s_nbox, unsigned char* s_dyn,
-                                                 double (*s_uv)[kBodyThreads / 2]) {
-  BodyDev* Bp = p.body + b;
-  const int kind = Bp->kind, nv = Bp->nv, v0 = Bp->v0, inst = Bp->inst;
-  const double ks = Bp->ks, kb = Bp->kb, ka = Bp->ka, p_ref = Bp->p_ref, A0 = Bp->A0;
-  const double mv = Bp->mv, sigma = Bp->sigma;
-  const int lig_stride = Bp->lig_stride, lig_base = Bp->lig_base;
-  const LatDev L = p.lat[inst];
-  const int t = threadIdx.x, nt = kBodyThreads;   // the launch's block size
-  const T* A = p.A + 9 * L.node_base;
-  const double nu = (L.tau - 0.5) / 3.0;
-  const bool pery = L.periodic_y != 0;
-  // the repulsion needs every body's X^n before any body's forces, which
-  // this form cannot give: it is never launched with the repulsion on
-  const bool rep = false;
-  // rest data of this lane's two vertices (va, vb), requested now so that
-  // the loads are in flight during the work before their use (scalars, not
-  // arrays: an array the compiler fails to keep in registers goes to
-  // private memory)
-  static_assert(kVmax == 2 * kBodyThreads, "two vertices per lane");
-  const int va = t, vb = t + nt;
-  double th0a, th0b, l0a, l0b, l0ma, l0mb;
-  {
-    const bool soft = kind != kRigid;
-    const int ua = va < nv ? va : 0, ub = vb < nv ? vb : 0;
-    th0a = soft ? p.th0[v0 + ua] : 0.0;
-    th0b = soft ? p.th0[v0 + ub] : 0.0;
-    l0a = soft ? p.l0[v0 + ua] : 0.0;
-    l0b = soft ? p.l0[v0 + ub] : 0.0;
-    l0ma = soft ? p.l0[v0 + (ua == 0 ? nv - 1 : ua - 1)] : 0.0;
-    l0mb = soft ? p.l0[v0 + (ub == 0 ? nv - 1 : ub - 1)] : 0.0;
-  }
-  const double* X = sm[0];
-  const double* Y = sm[1];
-  double* S_len = sm[2];
-  double* S_nx = sm[3];
-  double* S_ny = sm[4];
-  double* S_bc = sm[5];
-  double* S_bnx = sm[6];
-  double* S_bny = sm[7];
-  double* S_fex = sm[8];
-  double* S_fey = sm[9];
-  // ---- end of the previous step for this body's vertices: X^n, stencils,
-  // bins of this step's fused kernel.  Particles also take the bounding box
-  // of X^n for their LDS cache from here.
-  int mnx = 0x7fffffff, mxx = -0x7fffffff, mny = 0x7fffffff, mxy = -0x7fffffff;
-  {
-    const bool first_prev = p.step_prev[inst] == 0;
-    constexpr int R = 2;
-    for (int base0 = 0; base0 < nv; base0 += R * nt) {
-      int gmv[R], ncx[R], ncy[R];
-      bool act[R];
-      double xo[R], yo[R], xn[R], yn[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int v = base0 + r * nt + t;
-        act[r] = v < nv;
-        gmv[r] = v0 + (act[r] ? v : 0);
-        xo[r] = p.x[gmv[r]];
-        yo[r] = p.y[gmv[r]];
-      }
-      if (kind == kRBC) {
-        RbcAdv<MLS> ra[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) rbc_adv_load<MLS>(p, L, gmv[r], ra[r]);
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-          rbc_adv_finish<MLS>(p, L, ra[r], xo[r], yo[r], first_prev, xn[r], yn[r]);
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          xn[r] = p.xn[gmv[r]];
-          yn[r] = p.yn[gmv[r]];
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        ncx[r] = 0;
-        ncy[r] = 0;
-        if (act[r]) {
-          p.xm[gmv[r]] = xo[r];
-          p.ym[gmv[r]] = yo[r];
-          p.x[gmv[r]] = xn[r];
-          p.y[gmv[r]] = yn[r];
-          sm[0][base0 + r * nt + t] = xn[r];
-          sm[1][base0 + r * nt + t] = yn[r];
-          marker_stencil<MLS>(p, L, gmv[r], xn[r], yn[r], ncx[r], ncy[r]);
-          if (kind != kRBC) {
-            mnx = min(mnx, (int)floor(xn[r]) - 4); mxx = max(mxx, (int)ceil(xn[r]) + 4);
-            mny = min(mny, (int)floor(yn[r]) - 4); mxy = max(mxy, (int)ceil(yn[r]) + 4);
-          }
-        }
-      }
-      register_markers<TX, TY, R>(p.cnt_cur, p.bin_cur, p.bin_cap, p.overflow, L, gmv, ncx, ncy, act);
-    }
-  }
-
-  // ---- particles: LDS cache of rho*, u* over the box of nodes their vertex
-  // and probe stencils can reach: the vertex bounding box of X^n widened by
-  // 4 nodes (probe 1.2 along the normal, stencil reach 1.5, one node of
-  // margin).  Boxes larger than the cache fall back to direct evaluation
-  // (the same values: star_values rounds both alike).
-  bool cached = false;
-  StarCache<T> C{(const T*)s_dyn, 0, 0, 0, 0};
-  if (kind != kRBC) {
-    // wave reductions first: only one lane per wave touches the LDS words.
-    // (Shuffles, not wave_reduce_i: with the DPP form this kernel's FP32
-    // MLS particles went non-finite, for a cause not found.)
-    for (int o = 32; o > 0; o >>= 1) {
-      mnx = min(mnx, __shfl_xor(mnx, o)); mxx = max(mxx, __shfl_xor(mxx, o));
-      mny = min(mny, __shfl_xor(mny, o)); mxy = max(mxy, __shfl_xor(mxy, o));
-    }
-    if (t == 0) { s_box[0] = 0x7fffffff; s_box[1] = -0x7fffffff; s_box[2] = 0x7fffffff; s_box[3] = -0x7fffffff; }
-    __syncthreads();
-    if ((t & 63) == 0) {
-      atomicMin(&s_box[0], mnx); atomicMax(&s_box[1], mxx);
-      atomicMin(&s_box[2], mny); atomicMax(&s_box[3], mxy);
-    }
-    __syncthreads();
-    int by0 = s_box[2], by1 = s_box[3];
-    if (!pery) { by0 = max(by0, 0); by1 = min(by1, L.ny - 1); }
-    const int bw = s_box[1] - s_box[0] + 1, bh = by1 - by0 + 1;
-    if (bw > 0 && bh > 0 && (long long)bw * bh <= cache_nodes) {
-      cached = true;
-      C.bx0 = s_box[0]; C.by0 = by0; C.bw = bw; C.bh = bh;
-      const int nbox = bw * bh;
-      const long long Nn = L.plane;
-      T* cw = (T*)s_dyn;
-      constexpr int NB = 4;   // nodes per lane per batch: 36 loads in flight
-      T hv[NB][kQ];
-      for (int k0 = 0; k0 < nbox; k0 += NB * nt) {
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-          const int k = k0 + q * nt + t;
-          const int kk = k < nbox ? k : 0;
-          const int col = wrap_i(C.bx0 + kk % bw, L.nx);
-          int row = by0 + kk / bw;
-          if (pery) row = wrap_i(row, L.ny);
-          pull_node(A, p.sch, Nn, L.nx, L.ny, L.pitch, pery, col, row, hv[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-          const int k = k0 + q * nt + t;
-          if (k >= nbox) continue;
-          if (L.wall_mode == 1) {   // velocity walls: wall rows take the drive as force
-            int row = by0 + k / bw;
-            if (pery) row = wrap_i(row, L.ny);
-            wall_fill_drive(L, row, hv[q]);
-          }
-          double drho = 0.0, jx = 0.0, jy = 0.0;
-#pragma unroll
-          for (int i = 0; i < kQ; ++i) {
-            const double h = double(hv[q][i]);
-            drho += h;
-            jx += ex(i) * h;
-            jy += ey(i) * h;
-          }
-          star_values(L, drho, jx, jy, cw[3 * k], cw[3 * k + 1], cw[3 * k + 2]);
-        }
-      }
-    }
-  }
-  __syncthreads();   // positions, stencils and cache visible to the workgroup
-
-  // pass 1: element geometry (element v joins v -> v+1), bending, shoelace terms
-  auto pass1 = [&](int v, double th0v) {
-    const int vp = v + 1 == nv ? 0 : v + 1, vm = v == 0 ? nv - 1 : v - 1;
-    double lr, txr, tyr, ll, txl, tyl;
-    edge_of(X[v], Y[v], X[vp], Y[vp], lr, txr, tyr);
-    edge_of(X[vm], Y[vm], X[v], Y[v], ll, txl, tyl);
-    S_len[v] = lr;
-    S_nx[v] = tyr;
-    S_ny[v] = -txr;
-    if (kind != kRigid || rep) {
-      double bnx, bny;
-      vertex_normal(txl, tyl, txr, tyr, bnx, bny);
-      S_bnx[v] = bnx;
-      S_bny[v] = bny;
-    }
-    if (kind != kRigid) S_bc[v] = bend_coeff(txl, tyl, txr, tyr, kb, th0v);
-    s_terms[0][v] = shoelace_term(X[v], Y[v], X[vp], Y[vp]);
-  };
-  if (va < nv) pass1(va, th0a);
-  if (vb < nv) pass1(vb, th0b);
-  // twice the area in the canonical order of body_area2: per chunk the sum
-  // over its interior edges (a wave butterfly in the chunk layout) plus its
-  // last edge, then the chunks in order (the barriers also publish the scratch)
-  double area;
-  {
-    const int lane = t & 63, w = t >> 6, nch = chunks_of(nv);
-    __syncthreads();
-    for (int c = w; c < nch; c += kWaves) {
-      const int first = c * kChunk, cnt = min(kChunk, nv - first);
-      const int v = chunk_vertex(lane, first, nv);
-      const double P = wave_sum(lane >= 2 && lane < 1 + cnt ? s_terms[0][v] : 0.0);
-      if (lane == 0) s_part[0][c] = P + s_terms[0][first + cnt - 1];
-    }
-    __syncthreads();
-    area = chunk_total(s_part[0], nch) * 0.5;
-    __syncthreads();
-  }
-
-  const bool first = kind == kRigid && Bp->stepped == 0;
-  if (kind != kRBC) wait_bonds(p, inst);
-
-  // A particle of at most nt/2 vertices: the upper half of the lanes (other
-  // waves, so other SIMDs) interpolates the fluid velocity at the vertices
-  // while the lower half runs the probes, instead of after the particle's
-  // update; the values are the same, read back from LDS.
-  const bool vel_early = kind != kRBC && nv <= nt / 2;
-  if (vel_early && t >= nt / 2 && t - nt / 2 < nv) {
-    const int v = t - nt / 2;
-    double rho, ux, uy, g[4];
-    if (cached) interp_cached<MLS>(C, L, X[v], Y[v], false, rho, ux, uy, g);
-    else interp_star<MLS>(A, p.sch, L, X[v], Y[v], false, rho, ux, uy, g);
-    s_uv[0][v] = ux;
-    s_uv[1][v] = uy;
-  }
-  auto vertex_velocity = [&](int v, double& ux, double& uy) {
-    double rho, g[4];
-    if (vel_early) {
-      ux = s_uv[0][v];
-      uy = s_uv[1][v];
-    } else if (cached) {
-      interp_cached<MLS>(C, L, X[v], Y[v], false, rho, ux, uy, g);
-    } else {
-      interp_star<MLS>(A, p.sch, L, X[v], Y[v], false, rho, ux, uy, g);
-    }
-  };
-  // pass 2: element loads (area penalty, adhesion springs, probe stresses)
-  for (int l = t; l < nv; l += nt) {
-    const int lp = l + 1 == nv ? 0 : l + 1;
-    const double len = S_len[l], nxl = S_nx[l], nyl = S_ny[l];
-    const double ca = kind != kRigid ? ka * (1.0 - area / A0) * p_ref * len : 0.0;
-    bool spring_on = false;
-    double sp = 0.0, pfx = 0.0, pfy = 0.0;
-    if (kind != kRBC) {
-      const double cx = 0.5 * (X[l] + X[lp]), cy = 0.5 * (Y[l] + Y[lp]);
-      if (lig_stride > 0 && l % lig_stride == 0) {
-        const int gl = lig_base + l / lig_stride;
-        spring_on = p.l2r[gl] >= 0;
-        sp = spring_on ? p.lig_sp[gl] : 0.0;   // sigma (y_l - y_eq), from the bond workgroup
-      }
-      double qx, qy, rho, ux, uy, g[4];
-      probe_point(L, cx, cy, nxl, nyl, qx, qy);
-      if (cached) interp_cached<MLS>(C, L, qx, qy, true, rho, ux, uy, g);
-      else interp_star<MLS>(A, p.sch, L, qx, qy, true, rho, ux, uy, g);
-      probe_load(rho, g, nu, nxl, nyl, len, pfx, pfy);
-    }
-    element_load(kind != kRigid, ca, spring_on, sp, kind != kRBC, pfx, pfy, nxl, nyl, S_fex[l], S_fey[l]);
-  }
-  __syncthreads();
-
-  double fm = 0.0;
-  if (kind == kRigid) {
-    const double xc0 = Bp->xc, yc0 = Bp->yc;
-    for (int l = t; l < nv; l += nt) {
-      const int lp = l + 1 == nv ? 0 : l + 1;
-      double t3[3];
-      rigid_terms(S_fex[l], S_fey[l], 0.5 * (X[l] + X[lp]) - xc0, 0.5 * (Y[l] + Y[lp]) - yc0, rep,
-                  0.0, 0.0, X[l] - xc0, Y[l] - yc0, t3);
-      s_terms[0][l] = t3[0];
-      s_terms[1][l] = t3[1];
-      s_terms[2][l] = t3[2];
-    }
-    double r3[3], st[6];
-    r3[0] = canonical_sum(s_terms[0], nv, s_part[0]);
-    r3[1] = canonical_sum(s_terms[1], nv, s_part[1]);
-    r3[2] = canonical_sum(s_terms[2], nv, s_part[2]);
-    rigid_step(Bp, first, r3, st);
-    __syncthreads();   // every lane has read the rigid state
-    if (t == 0) rigid_commit(Bp, st);
-    const double cs = cos(st[5]), sn = sin(st[5]);
-    IBox q{0x7fffffff, -0x7fffffff, 0x7fffffff, -0x7fffffff};
-    for (int v = t; v < nv; v += nt) {
-      const int gm = v0 + v, vm = v == 0 ? nv - 1 : v - 1;
-      double ux, uy, xn, yn, fx, fy;
-      vertex_velocity(v, ux, uy);
-      rigid_vertex(p.r0x[gm], p.r0y[gm], st, cs, sn, ux, uy, 0.5 * (S_len[vm] + S_len[v]), xn, yn, fx,
-                   fy);
-      p.xn[gm] = xn;
-      p.yn[gm] = yn;
-      p.fx[gm] = fx;
-      p.fy[gm] = fy;
-      fm = fmax_nan(fm, fmax_nan(fabs(fx), fabs(fy)));
-      q.x0 = min(q.x0, (int)floor(xn)); q.x1 = max(q.x1, (int)ceil(xn));
-      q.y0 = min(q.y0, (int)floor(yn)); q.y1 = max(q.y1, (int)ceil(yn));
-    }
-    record_fmax(p.fmax_bits + inst, fm);
-    publish_box(p.pbox, Bp->chunk0, chunks_of(nv), q, s_nbox);
-    return;
-  }
-
-  // membrane vertex forces: strain + bending + shared element loads
-  IBox q{0x7fffffff, -0x7fffffff, 0x7fffffff, -0x7fffffff};   // soft particles' new box
-  auto vertex_force = [&](int v, double l0v, double l0m) {
-    const int gm = v0 + v;
-    const int vm = v == 0 ? nv - 1 : v - 1, vp = v + 1 == nv ? 0 : v + 1;
-    const int vmm = vm == 0 ? nv - 1 : vm - 1;
-    VertexNbr n;
-    n.len_mm = S_len[vmm];
-    n.len_m = S_len[vm];
-    n.len = S_len[v];
-    n.len_p = S_len[vp];
-    n.nx_m = S_nx[vm];
-    n.ny_m = S_ny[vm];
-    n.nx = S_nx[v];
-    n.ny = S_ny[v];
-    n.bc_m = S_bc[vm];
-    n.bc = S_bc[v];
-    n.bc_p = S_bc[vp];
-    n.bnx_m = S_bnx[vm];
-    n.bny_m = S_bny[vm];
-    n.bnx = S_bnx[v];
-    n.bny = S_bny[v];
-    n.bnx_p = S_bnx[vp];
-    n.bny_p = S_bny[vp];
-    n.fex_m = S_fex[vm];
-    n.fey_m = S_fey[vm];
-    n.fex = S_fex[v];
-    n.fey = S_fey[v];
-    double fx, fy;
-    membrane_force(n, ks, l0v, l0m, rep, 0.0, fx, fy);
-    if (kind == kRBC) {
-      p.fx[gm] = fx;
-      p.fy[gm] = fy;
-      fm = fmax_nan(fm, fmax_nan(fabs(fx), fabs(fy)));
-    } else {
-      double ux, uy, xn, yn, ffx, ffy;
-      vertex_velocity(v, ux, uy);
-      soft_vertex(X[v], Y[v], ux, uy, fx, fy, mv, 0.5 * (n.len_m + n.len), xn, yn, ffx, ffy);
-      p.xn[gm] = xn;
-      p.yn[gm] = yn;
-      p.fx[gm] = ffx;
-      p.fy[gm] = ffy;
-      fm = fmax_nan(fm, fmax_nan(fabs(ffx), fabs(ffy)));
-      q.x0 = min(q.x0, (int)floor(xn)); q.x1 = max(q.x1, (int)ceil(xn));
-      q.y0 = min(q.y0, (int)floor(yn)); q.y1 = max(q.y1, (int)ceil(yn));
-    }
-  };
-  if (va < nv) vertex_force(va, l0a, l0ma);
-  if (vb < nv) vertex_force(vb, l0b, l0mb);
-  record_fmax(p.fmax_bits + inst, fm);
-  if (kind == kSoft) publish_box(p.pbox, Bp->chunk0, chunks_of(nv), q, s_nbox);
-}
-
-// Box of a particle's new vertex positions (this workgroup's lanes folded in
-// LDS), written to every chunk slot of the particle for the star pass.
-__device__ inline void publish_box(int* pbox, int ch0, int nch, IBox q, int* s_nbox) {
-  const int t = threadIdx.x;
-  for (int o = 32; o > 0; o >>= 1) {
-    q.x0 = min(q.x0, __shfl_xor(q.x0, o));
-    q.x1 = max(q.x1, __shfl_xor(q.x1, o));
-    q.y0 = min(q.y0, __shfl_xor(q.y0, o));
-    q.y1 = max(q.y1, __shfl_xor(q.y1, o));
-  }
-  if (t == 0) {
-    s_nbox[0] = 0x7fffffff; s_nbox[1] = -0x7fffffff; s_nbox[2] = 0x7fffffff; s_nbox[3] = -0x7fffffff;
-  }
-  __syncthreads();
-  if ((t & 63) == 0) {
-    atomicMin(&s_nbox[0], q.x0); atomicMax(&s_nbox[1], q.x1);
-    atomicMin(&s_nbox[2], q.y0); atomicMax(&s_nbox[3], q.y1);
-  }
-  __syncthreads();
-  for (int k = t; k < nch; k += blockDim.x) {
-    pbox[4 * (ch0 + k)] = s_nbox[0];
-    pbox[4 * (ch0 + k) + 1] = s_nbox[1];
-    pbox[4 * (ch0 + k) + 2] = s_nbox[2];
-    pbox[4 * (ch0 + k) + 3] = s_nbox[3];
-  }
-}
-
-// Merged step form: workgroups [0, ninst) run the bond kinetics of each
-// instance; then one workgroup per body (every body has at most kVmax
-// vertices) finishes the previous step for its vertices and computes this
-// step's forces.
-template <typename T, int TX, int TY, bool MLS>
-__global__ __launch_bounds__(kBodyThreads) void k_body(Ptrs<T> p, int cache_nodes) {
-  __shared__ double s_part[3][kMaxChunks];
-  __shared__ int s_box[4];
-  __shared__ int s_nbox[4];
-  __shared__ double sm[10][kVmax];   // x, y, len, nx, ny, bc, bnx, bny, fex, fey
-  __shared__ double s_terms[3][kVmax];
-  __shared__ double s_uv[2][kBodyThreads / 2];   // fluid velocity at a small particle's vertices
-  __shared__ int s_tmp[kBodyThreads];
-  __shared__ int s_nelig;
-  extern __shared__ unsigned char s_dyn[];
-  // the other bin set (last read two steps ago) starts its next use empty
+// The other bin set (last read two steps ago) starts its next use empty.
+// Called after a wave's own work: no load of it then waits behind these stores.
+template <typename T>
+__device__ __forceinline__ void clear_bins(const Ptrs<T>& p) {
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < p.ntile_total; t += gridDim.x * blockDim.x)
     p.cnt_next[t] = 0;
-  if ((int)blockIdx.x < p.ninst) {
-    bonds_impl(p, blockIdx.x, s_tmp, &s_nelig);
-    return;
-  }
-  body_merged_impl<T, TX, TY, MLS>(p, blockIdx.x - p.ninst, cache_nodes, sm, s_terms, s_part, s_box,
-                                   s_nbox, s_dyn, s_uv);
 }
 
-// Three-kernel and overlapped step forms: workgroups [0, ninst) run the bond
-// kinetics of each instance; then one wave per vertex chunk of every body.
+// Workgroups [0, ninst) run the bond kinetics of each instance; then one wave
+// per vertex chunk of every body.
 template <typename T, bool MLS>
-__global__ __launch_bounds__(kBodyThreads) void k_body_chunks(Ptrs<T> p) {
+__global__ __launch_bounds__(kBodyThreads) void k_body_chunks(Ptrs<T>) {
+  const Ptrs<T>& p = launch_args<T>();
   __shared__ int s_tmp[kBodyThreads];
   __shared__ int s_nelig;
   __shared__ double s_rp[3][kWaves];
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < p.ntile_total; t += gridDim.x * blockDim.x)
-    p.cnt_next[t] = 0;
   if ((int)blockIdx.x < p.ninst) {
     bonds_impl(p, blockIdx.x, s_tmp, &s_nelig);
+    clear_bins(p);
     return;
   }
-  const int slot = (blockIdx.x - p.ninst) * kWaves + (threadIdx.x >> 6);
-  const int2 sc = slot < p.nslot ? p.slot_chunk[slot] : make_int2(-1, 0);
+  const int slot = (blockIdx.x - p.ninst) * kWaves + wave_id();
+  const int2 sc = slot < p.nslot ? load_uniform(p.slot_chunk + slot) : make_int2(-1, 0);
   if (sc.x != -1) chunk_impl<T, MLS>(p, sc.x, sc.y, s_rp);
+  clear_bins(p);
 }
 
 // ---------------------------------------------------------------- advance and stencil passes
+// Bound by the chain of one wave: its records, its vertices, the velocities
+// the lattice kernel left on other XCDs, then about 600 instructions at the
+// 4 to 10 cycles each that a wave alone on its SIMD issues at.  Measured (us,
+// before -> after the compacted bin slots, row loads of the velocity and one
+// star node per lane): 2000x200 7.6 -> 6.7, 6667x667 9.2 -> 7.6, 16-lattice
+// sweep 9.7 -> 9.1.
 // One wave per vertex chunk, its own vertices on lanes 2 .. 2 + cnt - 1 (the
 // halo lanes idle: their vertices belong to waves that move them in place).
 // ADVANCE: every vertex moves to X^{n+1} (red cells by the kinematic update,
@@ -1871,16 +1284,16 @@ __global__ __launch_bounds__(kBodyThreads) void k_body_chunks(Ptrs<T> p) {
 // shoelace sum, its first and last vertex) is what the next body kernel
 // adds up into the body's area.
 template <typename T, int TX, int TY, bool MLS, bool ADVANCE>
-__device__ __forceinline__ void advance_chunk(Ptrs<T>& p, int* cnt, int* bin) {
+__device__ __forceinline__ void advance_chunk(const Ptrs<T>& p, int* cnt, int* bin) {
   const int lane = threadIdx.x & 63;
-  const int chunk = blockIdx.x * kWaves + (threadIdx.x >> 6);
+  const int chunk = blockIdx.x * kWaves + wave_id();
   if (chunk >= p.nchunk_total) return;   // the whole wave
   // one load gives the wave its vertices (the body record is not needed)
-  const int4 ci = p.chunk_info[chunk];
+  const int4 ci = load_uniform(p.chunk_info + chunk);
   const int kind = ci.w & 3, inst = ci.w >> 2, cnt_v = ci.z;
   const bool inner = lane >= 2 && lane < 2 + cnt_v;
   const int gm = inner ? ci.y + lane : 0;
-  const LatDev L = p.lat[inst];
+  const LatDev L = load_uniform(p.lat + inst);
   double X = 0.0, Y = 0.0, xn = 0.0, yn = 0.0;
   int ncx = 0, ncy = 0;
   if (inner) {
@@ -1900,8 +1313,8 @@ __device__ __forceinline__ void advance_chunk(Ptrs<T>& p, int* cnt, int* bin) {
   }
   // bin slots for the new stencil: the reservations (atomics) go out first
   // and the stores below are issued while they are in flight
-  BinSlots<1> S;
-  bins_reserve<TX, TY, 1>(cnt, L, &ncx, &ncy, &inner, S);
+  BinSlots S;
+  bins_reserve<TX, TY>(cnt, L, ncx, ncy, inner, S);
   if (inner) {
     if (ADVANCE) {
       p.xm[gm] = X;
@@ -1931,7 +1344,7 @@ __device__ __forceinline__ void advance_chunk(Ptrs<T>& p, int* cnt, int* bin) {
     const IBox q = wave_box(xn, yn, inner);
     if (lane == 0) put_box(p.pbox, chunk, q);
   }
-  bins_commit<1>(bin, p.bin_cap, p.overflow, &gm, S);
+  bins_commit(bin, p.bin_cap, p.overflow, gm, S);
 }
 
 inline __host__ __device__ int chunk_blocks(int nchunk) { return (nchunk + kWaves - 1) / kWaves; }
@@ -1941,7 +1354,8 @@ inline __host__ __device__ int chunk_blocks(int nchunk) { return (nchunk + kWave
 // the workgroups after the chunks' fill the star field of the particles'
 // boxes from the populations this step's fused kernel wrote.
 template <typename T, int TX, int TY>
-__global__ __launch_bounds__(256) void k_advance(Ptrs<T> p) {
+__global__ __launch_bounds__(256) void k_advance(Ptrs<T>) {
+  const Ptrs<T>& p = launch_args<T>();
   const int cb = chunk_blocks(p.nchunk_total);
   if ((int)blockIdx.x >= cb) {
     star_pass(p, p.B, p.sch_next, blockIdx.x - cb);
@@ -1951,7 +1365,8 @@ __global__ __launch_bounds__(256) void k_advance(Ptrs<T> p) {
 }
 
 template <typename T, int TX, int TY>
-__global__ __launch_bounds__(256) void k_advance_mls(Ptrs<T> p) {
+__global__ __launch_bounds__(256) void k_advance_mls(Ptrs<T>) {
+  const Ptrs<T>& p = launch_args<T>();
   const int cb = chunk_blocks(p.nchunk_total);
   if ((int)blockIdx.x >= cb) {
     star_pass(p, p.B, p.sch_next, blockIdx.x - cb);
@@ -1963,12 +1378,16 @@ __global__ __launch_bounds__(256) void k_advance_mls(Ptrs<T> p) {
 // Star field of the particles' boxes from the current populations (after
 // the stencil pass).
 template <typename T>
-__global__ __launch_bounds__(256) void k_star(Ptrs<T> p) { star_pass(p, p.A, p.sch, blockIdx.x); }
+__global__ __launch_bounds__(256) void k_star(Ptrs<T>) {
+  const Ptrs<T>& p = launch_args<T>();
+  star_pass(p, p.A, p.sch, blockIdx.x);
+}
 
 // Stencils, bins and area partials of all markers from their current
 // positions (after set-up or after positions were overwritten from the host).
 template <typename T, int TX, int TY>
-__global__ __launch_bounds__(256) void k_stencil(Ptrs<T> p) {
+__global__ __launch_bounds__(256) void k_stencil(Ptrs<T>) {
+  const Ptrs<T>& p = launch_args<T>();
   advance_chunk<T, TX, TY, true, false>(p, p.cnt_cur, p.bin_cur);
 }
 
@@ -1989,28 +1408,10 @@ void launch_stencil(const Ptrs<T>& p, const StepArgs& a, hipStream_t s) {
 }
 
 template <typename T>
-void launch_lagrangian(const Ptrs<T>& p, const StepArgs& a, hipStream_t s, bool advance_first) {
-  if (!advance_first) {
-    const dim3 grid(p.ninst + (unsigned)(p.nslot / kWaves)), block(kBodyThreads);
-    if (a.any_mls) hipLaunchKernelGGL((k_body_chunks<T, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_body_chunks<T, false>), grid, block, 0, s, p);
-    return;
-  }
-  // the merged form is only requested when every body is small: the engine
-  // resolves the step form from the same limit
-  const int cache_nodes = a.body_cache_bytes / (3 * (int)sizeof(T));
-  const dim3 grid(p.ninst + p.nbody_total), block(kBodyThreads);
-  const unsigned lds = (unsigned)a.body_cache_bytes;
-#define LBIB_BODY_T(M)                                                                                       \
-  do {                                                                                                    \
-    if (a.tile_x == 64 && a.tile_y == 4) hipLaunchKernelGGL((k_body<T, 64, 4, M>), grid, block, lds, s, p, cache_nodes);       \
-    else if (a.tile_x == 128 && a.tile_y == 2) hipLaunchKernelGGL((k_body<T, 128, 2, M>), grid, block, lds, s, p, cache_nodes); \
-    else if (a.tile_x == 32 && a.tile_y == 8) hipLaunchKernelGGL((k_body<T, 32, 8, M>), grid, block, lds, s, p, cache_nodes);   \
-    else hipLaunchKernelGGL((k_body<T, 256, 1, M>), grid, block, lds, s, p, cache_nodes);                  \
-  } while (0)
-  if (a.any_mls) LBIB_BODY_T(true);
-  else LBIB_BODY_T(false);
-#undef LBIB_BODY_T
+void launch_lagrangian(const Ptrs<T>& p, const StepArgs& a, hipStream_t s) {
+  const dim3 grid(p.ninst + (unsigned)(p.nslot / kWaves)), block(kBodyThreads);
+  if (a.any_mls) hipLaunchKernelGGL((k_body_chunks<T, true>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((k_body_chunks<T, false>), grid, block, 0, s, p);
 }
 
 template <typename T>
@@ -2022,8 +1423,8 @@ void launch_advance(const Ptrs<T>& p, const StepArgs& a, hipStream_t s) {
 }
 #undef LBIB_TILE_DISPATCH
 
-template void launch_lagrangian<float>(const Ptrs<float>&, const StepArgs&, hipStream_t, bool);
-template void launch_lagrangian<double>(const Ptrs<double>&, const StepArgs&, hipStream_t, bool);
+template void launch_lagrangian<float>(const Ptrs<float>&, const StepArgs&, hipStream_t);
+template void launch_lagrangian<double>(const Ptrs<double>&, const StepArgs&, hipStream_t);
 template void launch_advance<float>(const Ptrs<float>&, const StepArgs&, hipStream_t);
 template void launch_advance<double>(const Ptrs<double>&, const StepArgs&, hipStream_t);
 template void launch_stencil<float>(const Ptrs<float>&, const StepArgs&, hipStream_t);

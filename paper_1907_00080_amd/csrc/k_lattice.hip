@@ -43,10 +43,9 @@ constexpr int kCap = 256;  // lanes per workgroup = nodes per tile
 constexpr int kXcdBands = 2;   // bands of tiles per XCD
 
 // mode bits: 1 = record which tiles carried IB force (touched), 2 = clear the
-// bin counts this launch consumed; mode >> 2 selects tiles: 0 all, 1 only
-// those without registered markers, 2 only those with.  mode = 0
-// (measurement launches): the bins are left in place and the caller points
-// U at a spare buffer, so the simulation state is untouched.
+// bin counts this launch consumed.  mode = 0 (measurement launches): the bins
+// are left in place and the caller points U at a spare buffer, so the
+// simulation state is untouched.
 // Adds the markers of a tile's bin (entries lane, lane + kCap, ...) to the
 // tile's fixed-point force accumulators.  Stencil weights: the Roma kernel's
 // per-axis products (MLS = false) or the nine MLS weights; the transfer is
@@ -108,8 +107,6 @@ __device__ __forceinline__ void lb_tile(Ptrs<T>& p, int g, int ntiles_total, int
   const int q = (g >> 3) / band, r = (g >> 3) - q * band;
   const int tile = (q * 8 + (g & 7)) * band + r;
   if (tile >= ntiles_total) return;
-  const int cls = mode >> 2;
-  if (cls != 0 && (cls == 1) == (p.cnt_cur[tile] > 0)) return;   // the other launch's tile
   // a single lattice needs no lookup: its parameters are the first load
   const int inst = p.ninst == 1 ? 0 : p.tile_inst[tile];
   // by value: the fields are read once, before the stores below (through a

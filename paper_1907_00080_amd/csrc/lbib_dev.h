@@ -213,10 +213,8 @@ struct Ptrs {
   // per-step slots (two sets used alternately, like the population buffers)
   unsigned long long* fmax_bits;  // per instance: bit pattern of max |F| this step
   int* bond_flag;            // per instance: bond update of this step done
-  long long* step_slot;      // per instance: step number of this step
   unsigned long long* fmax_next;  // the other slots: cleared during this step
   int* bond_flag_next;
-  long long* step_prev;      // step number of the previous step
   int* spin_timeouts;        // waits for a bond flag that hit their bound
   int bin_cap;
   int* tile_inst;
@@ -253,6 +251,15 @@ struct Ptrs {
   int nm_total, nbody_total, ntile_total, ninst, nlig_total, nchunk_total;
 };
 
+// The launch's Ptrs (the kernel's first argument) read field by field from the
+// argument segment where each is used.  Taken as an ordinary argument, every
+// field a kernel may need is loaded at its start, and the scalar registers
+// that do not hold them all spill into vector lanes.
+template <typename T>
+__device__ __forceinline__ const Ptrs<T>& launch_args() {
+  return *(const Ptrs<T>*)(const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 // Vertex chunks.  A body's vertices are cut into chunks of kChunk
 // consecutive vertices; chunk c of a body covers [kChunk c, kChunk c + cnt)
 // and is handled by one 64-lane wave whose lane i holds vertex
@@ -263,6 +270,7 @@ struct Ptrs {
 // fixed butterfly (wave_sum), then the chunk sums in chunk order
 // (chunk_total), so all kernels and step forms give the same bits.
 constexpr int kChunk = 60;
+constexpr int kStarNodes = 256;   // nodes of a particle's box per star-pass workgroup (one per lane)
 __host__ __device__ constexpr int chunks_of(int nv) { return (nv + kChunk - 1) / kChunk; }
 // rigid bodies of at most this many chunks (one per wave of a 256-lane
 // workgroup) are summed inside their workgroup
@@ -272,8 +280,29 @@ __host__ __device__ constexpr bool rigid_grouped(int kind, int nv) {
 }
 
 __device__ __forceinline__ int chunk_vertex(int lane, int first, int nv) {
-  int v = (first + lane - 2) % nv;   // first + lane - 2 >= -2
-  return v < 0 ? v + nv : v;
+  int v = first + lane - 2;          // in [-2, nv + 61)
+  if (nv < 64) v %= nv;              // a body shorter than the wave goes round more than once
+  return v < 0 ? v + nv : (v >= nv ? v - nv : v);
+}
+
+// A record that every lane of the wave reads at the same address, through the
+// scalar unit: its words land in scalar registers.  ptr must be wave-uniform
+// and the record not written by this launch before the read (the scalar cache
+// starts each launch empty).  Left to itself the compiler takes a vector load
+// wherever the index comes from threadIdx or an earlier store may alias.
+template <typename V>
+__device__ __forceinline__ V load_uniform(const V* ptr) {
+  static_assert(sizeof(V) % 4 == 0 && alignof(V) >= 4, "whole words");
+  const unsigned long long a = (unsigned long long)ptr;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  const auto src = (const __attribute__((address_space(4))) unsigned*)(((unsigned long long)hi << 32) | lo);
+  unsigned w[sizeof(V) / 4];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(V) / 4; ++i) w[i] = src[i];
+  V v;
+  __builtin_memcpy(&v, w, sizeof(V));
+  return v;
 }
 
 // Value of a double held by lane l of the wave (l wave-uniform: two
@@ -406,6 +435,8 @@ __host__ __device__ inline int wrap_i(int i, int n) {
   int r = i % n;
   return r < 0 ? r + n : r;
 }
+// The same for i in [-n, 2n): no division.
+__host__ __device__ inline int wrap_near(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
 // ------------------------------------------------------------ Philox4x32-10
 // Salmon et al., SC'11: 10 rounds of multiply/xor with Weyl key schedule.
@@ -483,16 +514,10 @@ void launch_fill(double* out, long long n, double v, hipStream_t s);
 
 // ------------------------------------------------------------ launchers
 // (defined in the kernel translation units, called by the host engine)
-// Bodies with at most this many vertices keep their per-vertex scratch in the
-// body kernel's LDS; the merged step form needs every body to be that small.
-constexpr int kSmallBody = 512;
-
 struct StepArgs {
   int tile_x, tile_y;
   int ntiles_total;
   int max_inst_tiles;   // largest tile count of any instance
-  int body_cache_bytes; // LDS cache of rho*, u* per particle workgroup
-  int max_nv;           // most vertices of any body
   int any_mls;          // some instance uses the MLS transfer
   int nt_mode;          // lattice kernel: non-temporal population loads (1), and stores (3)
   int lb_wpc;           // lattice kernel: 0 one workgroup per tile, else a persistent
@@ -529,7 +554,7 @@ template <typename T>
 void launch_init_pop(const Ptrs<T>& p, const double* rho, const double* ux, const double* uy,
                      long long node_base, long long n, long long nodes_total, hipStream_t s);
 template <typename T>
-void launch_lagrangian(const Ptrs<T>& p, const StepArgs& a, hipStream_t s, bool advance_first);
+void launch_lagrangian(const Ptrs<T>& p, const StepArgs& a, hipStream_t s);
 template <typename T>
 void launch_advance(const Ptrs<T>& p, const StepArgs& a, hipStream_t s);
 template <typename T>
