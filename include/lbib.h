@@ -30,6 +30,8 @@
  *     queries the workspace size, allocates that many bytes of device
  *     memory (any allocator; 256-byte alignment required) and binds it
  *     together with a HIP stream.  The workspace must outlive the context.
+ *     It holds up to 2 MB of pinned host memory per context (from
+ *     finalize_setup to destroy) that readbacks pass through.
  *     All kernels are enqueued on the bound stream; lbib_step returns once
  *     the work is enqueued.  Readback calls synchronise that stream.
  *   - Lifecycle: create -> add_body / set_receptors / set_adhesion /

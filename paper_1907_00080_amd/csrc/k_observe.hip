@@ -86,6 +86,18 @@ void launch_observe(const Ptrs<T>& p, lbib_body_obs* obs, long long step, hipStr
   hipLaunchKernelGGL(k_observe<T>, dim3(p.nbody_total), dim3(kObsThreads), 0, s, p, obs, step);
 }
 
+// Coordinates of n vertices as pairs (x0, y0, x1, y1, ...).
+__global__ void k_pair(const double* x, const double* y, int n, double* xy) {
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= n) return;
+  xy[2 * v] = x[v];
+  xy[2 * v + 1] = y[v];
+}
+
+void launch_pair(const double* x, const double* y, int n, double* xy, hipStream_t s) {
+  hipLaunchKernelGGL(k_pair, dim3((n + 255) / 256), dim3(256), 0, s, x, y, n, xy);
+}
+
 template void launch_observe<float>(const Ptrs<float>&, lbib_body_obs*, long long, hipStream_t);
 template void launch_observe<double>(const Ptrs<double>&, lbib_body_obs*, long long, hipStream_t);
 
