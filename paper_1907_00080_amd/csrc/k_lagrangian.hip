@@ -470,6 +470,23 @@ __device__ __forceinline__ void advance_rbc(const Ptrs<T>& p, const LatDev& L, i
 }
 
 // ---------------------------------------------------------------- k_bonds
+// First of the strictly increasing xs[0, n) (in [0, nx)) not left of x.  The
+// place that even spacing gives is tried first: one trip to memory instead of
+// one per halving.
+__device__ __forceinline__ int first_not_left(const double* xs, int n, double x, int nx) {
+  const int g = min(max((int)(x * n / nx), 0), n - 1);
+  const double before = xs[max(g - 1, 0)], at = xs[g], after = xs[min(g + 1, n - 1)];
+  if (at >= x && (g == 0 || before < x)) return g;
+  if (at < x && (g + 1 == n || after >= x)) return g + 1;
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (xs[mid] < x) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
 template <typename T>
 __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L, int inst, long long n,
                                                int nx, int ny, int* s_tmp, int& s_nelig) {
@@ -568,62 +585,77 @@ __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L
     if (tid == 0) s_nelig = base + off;
     __syncthreads();
   }
-  // (b) formation, sequential over the eligible ligands in ascending order
-  if (tid == 0 && kinetics) {
+  // (b) formation, in ascending ligand order.  A ligand's choice (the nearest
+  // free receptor of its wall) and draw depend on the earlier ones only
+  // through the receptors they take, so the lanes of one wave choose and draw
+  // for 64 eligible ligands together; then the bonds form in order, and only a
+  // ligand whose receptor has just gone chooses again.  (One lane taking the
+  // ligands one after the other cost about 3 us each.)
+  if (tid < 64 && kinetics) {
     const int ne = s_nelig;
-    for (int q = 0; q < ne; ++q) {
-      const int code = p.lig_flag[L.lig_base + q];
+    for (int q0 = 0; q0 < ne; q0 += 64) {
+      const bool on = q0 + lane < ne;
+      const int code = on ? p.lig_flag[L.lig_base + q0 + lane] : 0;
       const int l = code >> 1, wall = code & 1;
       const int gl = L.lig_base + l;
       const int va = p.lig_va[gl], vb = p.lig_vb[gl];
       const double cx = 0.5 * (p.xn[va] + p.xn[vb]);
       const double cy = 0.5 * (p.yn[va] + p.yn[vb]);
       const int nr = wall == 0 ? L.n_rec0 : L.n_rec1;
-      if (nr == 0) continue;
       const int roff = wall == 0 ? 0 : L.n_rec0;
       const double* xs = p.rec_x + L.rec_base + roff;
       const int* taken = p.r2l + L.rec_base + roff;
       const double cxw = wrap_x(cx, nx);
-      // first receptor at or right of cxw (receptors strictly increasing)
-      int lo = 0, hi = nr;
-      while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (xs[mid] < cxw) lo = mid + 1; else hi = mid;
-      }
-      // merge the rightward and leftward sequences by their own distances;
-      // each receptor is met first at its minimum-image distance
-      int ir = lo % nr, il = (lo - 1 + nr) % nr;
-      int best = -1;
-      for (int it = 0; it < 2 * nr && best < 0; ++it) {
-        double dr = xs[ir] - cxw;
-        if (dr < 0) dr += nx;
-        double dl = cxw - xs[il];
-        if (dl < 0) dl += nx;
-        // oracle's minimum image: equal to the smaller of the two one-sided
-        // distances; ties between the two sides go to the lower index
-        bool take_r = dr < dl || (dr == dl && ir <= il);
-        int cand = take_r ? ir : il;
-        if (taken[cand] < 0) {
-          best = cand;
-        } else if (take_r) {
-          ir = (ir + 1) % nr;
-        } else {
-          il = (il - 1 + nr) % nr;
-        }
-      }
-      if (best < 0) continue;
-      const double yl = bond_len(cx, cy, xs[best], wall, L);
+      const bool can = on && nr > 0;
       const double sig = p.lig_sigma[gl], sts = L.sigma_ts_frac * sig;
-      const double dy = yl - L.y_eq;
-      const double kf = L.kf0_dt * exp(-sts * dy * dy / (2.0 * L.kbt));
-      const double P = 1.0 - exp(-kf);
+      const int lo = can ? first_not_left(xs, nr, cxw, nx) : 0;
       const double u = philox_uniform(L.seed, n, l, 0, L.instance);
-      ties += fabs(u - P) < 1e-12;
-      if (u < P) {
-        __hip_atomic_store(&p.l2r[gl], roff + best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        p.r2l[L.rec_base + roff + best] = gl;
-        p.lig_sp[gl] = sig * dy;
+      int best = -1;
+      double dy = 0.0;
+      bool forms = false, tie = false;
+      auto choose = [&] {
+        // merge the rightward and leftward sequences by their own distances;
+        // each receptor is met first at its minimum-image distance
+        int ir = lo % nr, il = (lo - 1 + nr) % nr;
+        best = -1;
+        for (int it = 0; it < 2 * nr && best < 0; ++it) {
+          double dr = xs[ir] - cxw;
+          if (dr < 0) dr += nx;
+          double dl = cxw - xs[il];
+          if (dl < 0) dl += nx;
+          // oracle's minimum image: equal to the smaller of the two one-sided
+          // distances; ties between the two sides go to the lower index
+          const bool take_r = dr < dl || (dr == dl && ir <= il);
+          const int cand = take_r ? ir : il;
+          if (taken[cand] < 0) best = cand;
+          else if (take_r) ir = ir + 1 == nr ? 0 : ir + 1;
+          else il = il == 0 ? nr - 1 : il - 1;
+        }
+        forms = tie = false;
+        if (best < 0) return;
+        const double yl = bond_len(cx, cy, xs[best], wall, L);
+        dy = yl - L.y_eq;
+        const double kf = L.kf0_dt * exp(-sts * dy * dy / (2.0 * L.kbt));
+        const double P = 1.0 - exp(-kf);
+        tie = fabs(u - P) < 1e-12;
+        forms = u < P;
+      };
+      if (can) choose();
+      unsigned long long todo = __ballot(forms);
+      while (todo) {
+        const int q = __ffsll((long long)todo) - 1;
+        const int rec = roff + best;
+        const int gone = __shfl(rec, q);
+        if (lane == q) {
+          __hip_atomic_store(&p.l2r[gl], rec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          p.r2l[L.rec_base + rec] = gl;
+          p.lig_sp[gl] = sig * dy;
+        }
+        __threadfence_block();   // the receptor is taken for the lanes that choose again
+        if (lane > q && best >= 0 && rec == gone) choose();
+        todo = __ballot(lane > q && forms);
       }
+      ties += tie;
     }
   }
   if (ties) atomicAdd(&p.ties[inst], ties);
