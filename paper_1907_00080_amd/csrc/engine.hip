@@ -557,6 +557,7 @@ lbib_status upload_all(lbib_ctx* c) {
     D.nx = I.lat.nx; D.ny = I.lat.ny; D.periodic_y = I.lat.periodic_y;
     D.ntx = (D.nx + c->TX - 1) / c->TX;
     D.nty = (D.ny + c->TY - 1) / c->TY;
+    D.ntx_div = fast_div((unsigned)D.ntx);
     D.tile_base = c->tile_base[i];
     D.pitch = row_pitch(D.nx);
     D.plane = (long long)D.pitch * D.ny;

@@ -46,44 +46,56 @@ constexpr int kXcdBands = 2;   // bands of tiles per XCD
 // bin counts this launch consumed.  mode = 0 (measurement launches): the bins
 // are left in place and the caller points U at a spare buffer, so the
 // simulation state is untouched.
-// Adds the markers of a tile's bin (entries lane, lane + kCap, ...) to the
-// tile's fixed-point force accumulators.  Stencil weights: the Roma kernel's
-// per-axis products (MLS = false) or the nine MLS weights; the transfer is
-// chosen per instance outside the loop, so each loop is straight-line code.
-template <bool MLS, int TX, int TY, typename T>
-__device__ __forceinline__ void spread_entries(const Ptrs<T>& p, const int* bin, int M, int lane,
-                                               double sc, int x0, int y0, int nx, int ny, bool pery,
-                                               unsigned long long* s_ax, unsigned long long* s_ay) {
+// Adds the markers of a tile's bin to the tile's fixed-point force
+// accumulators.  A lane takes one row of one marker's stencil (item idx = lane,
+// lane + kCap, ...: row idx mod 3 of entry idx / 3): most tiles hold a few
+// markers, and what they cost is the instructions of the waves that spread
+// them (18 conversions and LDS adds a lane, with a marker per lane; 6 now).
+// Measured, marker per lane -> row per lane (with the scalar divisions of
+// FastDiv), neighbour / node-local pass, us: 2000x200 9.6 / 9.0 -> 8.8 / 8.0,
+// 6667x667 55.2 / 51.0 -> 53.4 / 49.9, 256x64 float64 6.6 / 5.3 -> 5.0 / 4.9,
+// 1237x149 MLS 7.1 / 6.7 -> 6.4 / 5.9.
+// MLS: nine weights per marker, else the Roma kernel's per-axis products; the
+// transfer is chosen per instance outside the loop, so each loop is
+// straight-line code.
+template <bool MLS>
+struct MarkerRow {
+  int cx, row;
+  double w[3], wy;
+};
+
+template <bool MLS, typename T>
+__device__ __forceinline__ void load_row(const Ptrs<T>& p, int m, int b, MarkerRow<MLS>& q) {
   const int nm = p.nm_total;
-  for (int j = lane; j < M; j += kCap) {
-    const int m = bin[j];
-    const int cx = p.cx[m], cy = p.cy[m];
+  q.cx = p.cx[m];
+  q.row = p.cy[m] + b - 1;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) q.w[a] = MLS ? p.wx[(3 * b + a) * nm + m] : p.wx[a * nm + m];
+  q.wy = MLS ? 0.0 : p.wy[b * nm + m];
+}
+
+template <bool MLS, int TX, int TY, typename T>
+__device__ __forceinline__ void spread_rows(const Ptrs<T>& p, const LatDev& L, const int* bin, int M, int e0,
+                                            double sc, int x0, int y0, unsigned long long* s_ax,
+                                            unsigned long long* s_ay) {
+  const int nx = L.nx, ny = L.ny;
+  for (int idx = threadIdx.x; idx < 3 * M; idx += kCap) {
+    const int e = idx / 3, b = idx - 3 * e;
+    const int m = idx < 64 ? e0 : bin[e];
+    MarkerRow<MLS> q;
+    load_row(p, m, b, q);
     const double fx = p.fx[m] * sc, fy = p.fy[m] * sc;
-    double wxa[3], wyb[3], ph[9];
-    if constexpr (MLS) {
+    // the centre lies inside the lattice along periodic axes: one wrap
+    const int row = L.periodic_y ? wrap_near(q.row, ny) : q.row;
+    const int ly = row - y0;
+    if (ly < 0 || ly >= TY) continue;
 #pragma unroll
-      for (int k = 0; k < 9; ++k) ph[k] = p.wx[k * nm + m];
-    } else {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        wxa[k] = p.wx[k * nm + m];
-        wyb[k] = p.wy[k * nm + m];
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      int row = cy + b - 1;
-      if (pery) row = wrap_i(row, ny);
-      const int ly = row - y0;
-      if (ly < 0 || ly >= TY) continue;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const int lx = wrap_i(cx + a - 1, nx) - x0;
-        if (lx < 0 || lx >= TX) continue;
-        const double w = MLS ? ph[3 * b + a] : wxa[a] * wyb[b];
-        atomicAdd(&s_ax[ly * TX + lx], (unsigned long long)__double2ll_rn(fx * w));
-        atomicAdd(&s_ay[ly * TX + lx], (unsigned long long)__double2ll_rn(fy * w));
-      }
+    for (int a = 0; a < 3; ++a) {
+      const int lx = wrap_near(q.cx + a - 1, nx) - x0;
+      if (lx < 0 || lx >= TX) continue;
+      const double w = MLS ? q.w[a] : q.w[a] * q.wy;
+      atomicAdd(&s_ax[ly * TX + lx], (unsigned long long)__double2ll_rn(fx * w));
+      atomicAdd(&s_ay[ly * TX + lx], (unsigned long long)__double2ll_rn(fy * w));
     }
   }
 }
@@ -102,9 +114,9 @@ __device__ __forceinline__ void spread_entries(const Ptrs<T>& p, const int* bin,
 // order.  Returns early (every lane, or a lane outside the lattice after the
 // workgroup's last barrier).
 template <typename T, int TX, int TY, int NT, int SCH>
-__device__ __forceinline__ void lb_tile(Ptrs<T>& p, int g, int ntiles_total, int band, int mode) {
+__device__ __forceinline__ void lb_tile(Ptrs<T>& p, int g, int ntiles_total, int band, FastDiv band_div, int mode) {
   static_assert(TX * TY == kCap, "one lane per LDS slot");
-  const int q = (g >> 3) / band, r = (g >> 3) - q * band;
+  const int q = (int)band_div.quotient((unsigned)g >> 3), r = (g >> 3) - q * band;
   const int tile = (q * 8 + (g & 7)) * band + r;
   if (tile >= ntiles_total) return;
   // a single lattice needs no lookup: its parameters are the first load
@@ -115,7 +127,7 @@ __device__ __forceinline__ void lb_tile(Ptrs<T>& p, int g, int ntiles_total, int
   const int nx = L.nx, ny = L.ny, ntx = L.ntx, pitch = L.pitch;
   const bool pery = L.periodic_y != 0;
   const int local = tile - L.tile_base;
-  const int tx = local % ntx, ty = local / ntx;
+  const int ty = (int)L.ntx_div.quotient((unsigned)local), tx = local - ty * ntx;
   const int lane = threadIdx.x;
   const int x = tx * TX + (lane % TX);
   const int y = ty * TY + (lane / TX);
@@ -178,10 +190,13 @@ __device__ __forceinline__ void lb_tile(Ptrs<T>& p, int g, int ntiles_total, int
   // atomics).  The scale 2^S is chosen per tile from the largest force of the
   // instance and the bin size so the accumulator cannot overflow:
   // |sum| <= M * max|F| < 2^61.
+  const int* bin = p.bin_cur + (long long)tile * p.bin_cap;
   const int Mreg = p.cnt_cur[tile];
+  // the first wave's entries with the count, not after it (a bin has room for
+  // more; those past the count are not used)
+  const int e0 = lane < 64 ? bin[lane / 3] : 0;
   const bool full = Mreg > p.bin_cap;          // registrations were dropped
   const int M = full ? p.bin_cap : Mreg;
-  const int* bin = p.bin_cur + (long long)tile * p.bin_cap;
   T Fx = T(L.gx), Fy = T(L.gy);
   if (M > 0) {
     __shared__ unsigned long long s_ax[kCap], s_ay[kCap];
@@ -198,12 +213,10 @@ __device__ __forceinline__ void lb_tile(Ptrs<T>& p, int g, int ntiles_total, int
       frexp(fmax_t * (double)M, &e);
       const double sc = ldexp(1.0, 61 - e);
       const int x0 = tx * TX, y0 = ty * TY;
-      if (L.transfer == LBIB_TRANSFER_MLS)
-        spread_entries<true, TX, TY>(p, bin, M, lane, sc, x0, y0, nx, ny, pery, s_ax, s_ay);
-      else
-        spread_entries<false, TX, TY>(p, bin, M, lane, sc, x0, y0, nx, ny, pery, s_ax, s_ay);
+      if (L.transfer == LBIB_TRANSFER_MLS) spread_rows<true, TX, TY>(p, L, bin, M, e0, sc, x0, y0, s_ax, s_ay);
+      else spread_rows<false, TX, TY>(p, L, bin, M, e0, sc, x0, y0, s_ax, s_ay);
       __syncthreads();
-      const double isc = 1.0 / sc;
+      const double isc = ldexp(1.0, e - 61);   // 1 / sc, exact
       Fx = T(L.gx + (double)(long long)s_ax[lane] * isc);
       Fy = T(L.gy + (double)(long long)s_ay[lane] * isc);
     }
@@ -285,8 +298,9 @@ __device__ __forceinline__ void lb_tile(Ptrs<T>& p, int g, int ntiles_total, int
 
 // One workgroup per tile (the default launch).
 template <typename T, int TX, int TY, int NT, int SCH>
-__global__ __launch_bounds__(TX * TY) void k_lb_fused(Ptrs<T> p, int ntiles_total, int band, int mode) {
-  lb_tile<T, TX, TY, NT, SCH>(p, blockIdx.x, ntiles_total, band, mode);
+__global__ __launch_bounds__(TX * TY, sizeof(T) == 4 ? 8 : 6) void k_lb_fused(Ptrs<T> p, int ntiles_total, int band, FastDiv band_div,
+                                                           int mode) {
+  lb_tile<T, TX, TY, NT, SCH>(p, blockIdx.x, ntiles_total, band, band_div, mode);
 }
 
 // Persistent launch: a fixed grid (a multiple of 8 workgroups, sized by the
@@ -294,10 +308,11 @@ __global__ __launch_bounds__(TX * TY) void k_lb_fused(Ptrs<T> p, int ntiles_tota
 // gridDim.x, so workgroup b keeps to the tiles of XCD b mod 8.  The barrier
 // between tiles frees the LDS accumulators for the next one.
 template <typename T, int TX, int TY, int NT>
-__global__ __launch_bounds__(TX * TY) void k_lb_persistent(Ptrs<T> p, int ntiles_total, int band, int mode) {
+__global__ __launch_bounds__(TX * TY) void k_lb_persistent(Ptrs<T> p, int ntiles_total, int band, FastDiv band_div,
+                                                                int mode) {
   const int gtot = 8 * kXcdBands * band;
   for (int g = blockIdx.x; g < gtot; g += gridDim.x) {
-    lb_tile<T, TX, TY, NT, 0>(p, g, ntiles_total, band, mode);
+    lb_tile<T, TX, TY, NT, 0>(p, g, ntiles_total, band, band_div, mode);
     __syncthreads();
   }
 }
@@ -452,6 +467,7 @@ void launch_lb_fused(const Ptrs<T>& p, const StepArgs& a, hipStream_t s, int mod
                      hipEvent_t ev0, hipEvent_t ev1) {
   const int band = (a.ntiles_total + 8 * kXcdBands - 1) / (8 * kXcdBands);
   const int vgrid = 8 * kXcdBands * band;
+  const FastDiv band_div = fast_div((unsigned)band);
   // persistent: wpc workgroups per CU, a multiple of 8, at most the virtual
   // grid; two-buffer streaming only
   const bool persist = a.lb_wpc > 0 && p.sch == 0;
@@ -461,7 +477,7 @@ void launch_lb_fused(const Ptrs<T>& p, const StepArgs& a, hipStream_t s, int mod
   // time is the kernel's execution time and not that of separate markers
 #define LBIB_LB1(KERNEL, ...)                                                                    \
   hipExtLaunchKernelGGL((KERNEL<T, __VA_ARGS__>), grid, block, 0, s, ev0, ev1, 0, p,             \
-                        a.ntiles_total, band, mode)
+                        a.ntiles_total, band, band_div, mode)
 #define LBIB_LB(TXv, TYv)                                                                        \
   do {                                                                                          \
     if (p.sch == 1) LBIB_LB1(k_lb_fused, TXv, TYv, 0, 1);                                       \
