@@ -43,26 +43,31 @@ struct Stencil {
   double wx[3], dwx[3], ddwx[3], wy[3], dwy[3], ddwy[3];
 };
 
-__device__ inline void stencil_at(const LatDev& L, double X, double Y, bool second, Stencil& s) {
+// Weights of the three nodes along one axis, d = (nearest node) - (point) in
+// (-1/2, 1/2], with first and second derivatives, all from one square root
+// (roma_weights3; phi'' is -1/q^3 on the inner node and 1/(2 q^3) on the outer
+// ones).  Taken node by node the six weights cost about 1500 instructions of
+// a probe's chain; this takes about 150.
+__device__ __forceinline__ void axis_weights(double d, bool second, double w[3], double dw[3], double ddw[3]) {
+  roma_weights3<true>(d, w, dw);
+  const double q2 = 1.0 - 3.0 * d * d;
+  const double c = second ? 1.0 / (q2 * sqrt(q2)) : 0.0;
+  ddw[0] = ddw[2] = 0.5 * c;
+  ddw[1] = -c;
+}
+
+__device__ __forceinline__ void stencil_at(const LatDev& L, double X, double Y, bool second, Stencil& s) {
   const double cxr = floor(X + 0.5), cyr = floor(Y + 0.5);
   const bool pery = L.periodic_y != 0;
+  axis_weights(cxr - X, second, s.wx, s.dwx, s.ddwx);
+  axis_weights(cyr - Y, second, s.wy, s.dwy, s.ddwy);
+  const int cx = wrap_i((int)cxr, L.nx), cy = pery ? wrap_i((int)cyr, L.ny) : (int)cyr;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const double rx = cxr + (a - 1);
-    s.col[a] = wrap_i((int)rx, L.nx);
-    s.wx[a] = roma_phi(rx - X);
-    s.dwx[a] = roma_dphi(rx - X);
-    s.ddwx[a] = second ? roma_ddphi(rx - X) : 0.0;
-    const double ry = cyr + (a - 1);
-    int row = (int)ry;
-    bool ok = true;
-    if (pery) row = wrap_i(row, L.ny);
-    else ok = row >= 0 && row < L.ny;
-    s.row[a] = row;
-    s.ok[a] = ok;
-    s.wy[a] = roma_phi(ry - Y);
-    s.dwy[a] = roma_dphi(ry - Y);
-    s.ddwy[a] = second ? roma_ddphi(ry - Y) : 0.0;
+    s.col[a] = wrap_near(cx + a - 1, L.nx);
+    const int row = cy + a - 1;
+    s.row[a] = pery ? wrap_near(row, L.ny) : row;
+    s.ok[a] = pery || (row >= 0 && row < L.ny);
   }
 }
 
@@ -78,7 +83,7 @@ constexpr int kAdjThreads = 256;
 // term of magnitude 2^30 or more (or not finite) is refused and flagged, so
 // the coarse word holds sums of up to 2^9 such terms and the fine word
 // (|r 2^72| <= 2^47 per term) of up to 2^16 terms without overflow.
-__device__ inline void acc_add(const AccField& f, long long k, double v, int* bad) {
+__device__ __forceinline__ void acc_add(const AccField& f, long long k, double v, int* bad) {
   if (!(fabs(v) < 0x1p30)) {   // also NaN
     atomicOr(bad, 1);
     return;
@@ -90,11 +95,11 @@ __device__ inline void acc_add(const AccField& f, long long k, double v, int* ba
   if (lo != 0) __hip_atomic_fetch_add(&f.lo[k], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ inline double acc_get(const AccField& f, long long k) {
+__device__ __forceinline__ double acc_get(const AccField& f, long long k) {
   return double(f.hi[k]) * 0x1p-24 + double(f.lo[k]) * 0x1p-72;
 }
 
-__device__ inline void acc_clear(const AccField& f, long long k) {
+__device__ __forceinline__ void acc_clear(const AccField& f, long long k) {
   f.hi[k] = 0;
   f.lo[k] = 0;
 }
@@ -123,7 +128,7 @@ __device__ inline void block_sum(double v[K], double (*s)[kAdjThreads / 64]) {
 // element, the bond length y from the centroid (cx, cy) to its receptor and
 // (ddx, ddy) = dy/dc.  Returns false for an element without a bond.
 template <typename T>
-__device__ inline bool bond_geometry(const Ptrs<T>& p, const LatDev& L, const BodyDev* Bp, int l,
+__device__ __forceinline__ bool bond_geometry(const Ptrs<T>& p, const LatDev& L, const BodyDev* Bp, int l,
                                      double cx, double cy, double& yl, double& ddx, double& ddy) {
   if (Bp->lig_stride <= 0 || l % Bp->lig_stride != 0) return false;
   const int r = p.l2r[Bp->lig_base + l / Bp->lig_stride];
@@ -147,7 +152,7 @@ __device__ inline bool bond_geometry(const Ptrs<T>& p, const LatDev& L, const Bo
 // hydroForNu, from rho*, u* in mom).  Returns the load in (pfx, pfy); given
 // its adjoint (Fhx, Fhy), adds the adjoints of c, n and len and scatters
 // those of rho*, u* into Rh.
-__device__ inline void probe_adjoint(const LatDev& L, const AdjPtrs& a, double cx, double cy,
+__device__ __forceinline__ void probe_adjoint(const LatDev& L, const AdjPtrs& a, double cx, double cy,
                                      double nxl, double nyl, double len, double nu, double Fhx,
                                      double Fhy, double& pfx, double& pfy, double& Chx, double& Chy,
                                      double& nhx, double& nhy, double& lenh) {
@@ -228,7 +233,7 @@ __device__ inline void probe_adjoint(const LatDev& L, const AdjPtrs& a, double c
 // which writes the marker's outputs.  Every lane of the row takes part in the
 // sums, also where the marker index is past the end.
 template <typename T>
-__device__ inline void marker_adjoint(const Ptrs<T>& p, const AdjPtrs& a, int gm, int j) {
+__device__ __forceinline__ void marker_adjoint(const Ptrs<T>& p, const AdjPtrs& a, int gm, int j) {
   const bool live = gm < p.nm_total;
   const LatDev L = p.lat[0];
   const long long N = L.plane;
@@ -260,8 +265,12 @@ __device__ inline void marker_adjoint(const Ptrs<T>& p, const AdjPtrs& a, int gm
     else ok = row >= 0 && row < L.ny;
     mine = j < 9 && ok;
     if (mine) {
-      const double wx = roma_phi(rx - X), dwx = roma_dphi(rx - X);
-      const double wy = roma_phi(ry - Y), dwy = roma_dphi(ry - Y);
+      double ax[3], dax[3], ay[3], day[3];
+      roma_weights3<true>(floor(X + 0.5) - X, ax, dax);
+      roma_weights3<true>(floor(Y + 0.5) - Y, ay, day);
+      const double wx = c == 0 ? ax[0] : (c == 1 ? ax[1] : ax[2]), dwx = c == 0 ? dax[0] : (c == 1 ? dax[1] : dax[2]);
+      const double wy = bb == 0 ? ay[0] : (bb == 1 ? ay[1] : ay[2]);
+      const double dwy = bb == 0 ? day[0] : (bb == 1 ? day[1] : day[2]);
       node = (long long)row * L.pitch + wrap_i((int)rx, L.nx);
       w = wx * wy;
       if (rbc) {
@@ -369,7 +378,7 @@ __global__ void ka_collide(Ptrs<T> p, AdjPtrs a) {
 // of the state before the step (rig, out).  X^n itself was formed from the
 // state by the previous step, whose reverse maps its adjoint onto it.
 template <typename T>
-__device__ void rigid_adjoint(const Ptrs<T>& p, const AdjPtrs& a, int b,
+__device__ __forceinline__ void rigid_adjoint(const Ptrs<T>& p, const AdjPtrs& a, int b,
                               double (*s_red)[kAdjThreads / 64]) {
   const BodyDev* Bp = p.body + b;
   const BodyDev& S0 = a.body0[b];   // state before the step
@@ -532,7 +541,9 @@ __device__ void rigid_adjoint(const Ptrs<T>& p, const AdjPtrs& a, int b,
 
 // One workgroup per body.
 template <typename T>
-__global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T> p, AdjPtrs a) {
+__global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T>, AdjPtrs) {
+  const Ptrs<T>& p = launch_args<T>();
+  const AdjPtrs& a = launch_args2<T, AdjPtrs>();
   __shared__ double s_red[6][kAdjThreads / 64];
   const int b = blockIdx.x;
   const BodyDev* Bp = p.body + b;
@@ -541,9 +552,8 @@ __global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T> p, AdjPtrs a) {
     rigid_adjoint(p, a, b, s_red);
     return;
   }
-  const LatDev L = p.lat[0];
+  const LatDev L = load_uniform(p.lat);
   const long long N = L.plane;
-  const bool pery = L.periodic_y != 0;
   const double nu = (L.tau - 0.5) / 3.0;
   const double ks = Bp->ks, kb = Bp->kb, ka = Bp->ka, p_ref = Bp->p_ref, A0 = Bp->A0;
   const double mv = Bp->mv, sigma = Bp->sigma;
@@ -629,11 +639,32 @@ __global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T> p, AdjPtrs a) {
   const double area = 0.5 * shoe;
   const double kappa = ka * (1.0 - area / A0) * p_ref;
 
-  // ---- phase B (elements l: v -> v+1) and bending (vertices)
+  // ---- phase B: elements l (v -> v+1), and the bending at vertices l.  Each
+  // is a chain of several hundred instructions of a lane, so a body of at most
+  // half the workgroup's lanes takes them on different waves.
   double ksh = 0.0, kbh = 0.0, sigh = 0.0, kaph = 0.0;
-  for (int l = t; l < nv; l += nt) {
+  const bool apart = nv <= nt / 2;
+  auto bending = [&](int l) {
     const int gl = v0 + l;
     const int lp = l + 1 == nv ? 0 : l + 1, lm = l == 0 ? nv - 1 : l - 1;
+    const double dx = X[lp] - X[l], dy = Y[lp] - Y[l];
+    const double dLx = X[l] - X[lm], dLy = Y[l] - Y[lm];   // left element lm, right element l
+    const double Fhm[2] = {a.fvx[v0 + lm], a.fvy[v0 + lm]};
+    const double Fhu[2] = {a.fvx[gl], a.fvy[gl]};
+    const double Fhp[2] = {a.fvx[v0 + lp], a.fvy[v0 + lp]};
+    const double th0 = p.th0[gl];
+    double dLh[2] = {0.0, 0.0}, dRh[2] = {0.0, 0.0};
+    adj::bend_vjp(dLx, dLy, dx, dy, th0, kb, Fhm, Fhu, Fhp, dLh, dRh, kbh);
+    a.BLx[gl] = dLh[0];
+    a.BLy[gl] = dLh[1];
+    a.BRx[gl] = dRh[0];
+    a.BRy[gl] = dRh[1];
+  };
+  if (apart && t >= nt / 2 && t - nt / 2 < nv) bending(t - nt / 2);
+  for (int l = t; l < nv; l += nt) {
+    const int gl = v0 + l;
+    const int lp = l + 1 == nv ? 0 : l + 1;
+    if (!apart) bending(l);   // its loads before the probe's scatter
     const double dx = X[lp] - X[l], dy = Y[lp] - Y[l];
     const double len = sqrt(dx * dx + dy * dy);
     const double f0x = a.fvx[gl], f0y = a.fvy[gl], f1x = a.fvx[v0 + lp], f1y = a.fvy[v0 + lp];
@@ -641,11 +672,6 @@ __global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T> p, AdjPtrs a) {
     adj::strain_vjp(dx, dy, p.l0[gl], ks, f0x - f1x, f0y - f1y, Dhx, Dhy, ksh);
     const double Fex = 0.5 * (f0x + f1x), Fey = 0.5 * (f0y + f1y);   // element-load adjoint
     kaph += adj::area_vjp(dx, dy, kappa, Fex, Fey, Dhx, Dhy);
-    // bending operands (vertex l: left element lm, right element l), read
-    // before the probe's scatter
-    const double dLx = X[l] - X[lm], dLy = Y[l] - Y[lm];
-    const double Fhm[2] = {a.fvx[v0 + lm], a.fvy[v0 + lm]};
-    const double th0 = p.th0[gl];
     if (kind == kSoft) {
       lenh += 0.5 * (a.dsh[gl] + a.dsh[v0 + lp]);
       const double cx = 0.5 * (X[l] + X[lp]), cy = 0.5 * (Y[l] + Y[lp]);
@@ -664,15 +690,6 @@ __global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T> p, AdjPtrs a) {
     a.Dy[gl] = Dhy;
     a.Cx[gl] = Chx;
     a.Cy[gl] = Chy;
-    // bending at vertex l
-    const double Fhu[2] = {f0x, f0y};
-    const double Fhp[2] = {f1x, f1y};
-    double dLh[2] = {0.0, 0.0}, dRh[2] = {0.0, 0.0};
-    adj::bend_vjp(dLx, dLy, dx, dy, th0, kb, Fhm, Fhu, Fhp, dLh, dRh, kbh);
-    a.BLx[gl] = dLh[0];
-    a.BLy[gl] = dLh[1];
-    a.BRx[gl] = dRh[0];
-    a.BRy[gl] = dRh[1];
   }
   double v4[4] = {ksh, kbh, sigh, kaph};
   block_sum<4>(v4, s_red);
@@ -706,7 +723,7 @@ __global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T> p, AdjPtrs a) {
 // bounced at a wall, f^_{opp(j)}(y).  f^ includes the pre-forcing moment
 // terms of rho*, u*.
 template <typename T>
-__device__ inline void stream_adjoint(const Ptrs<T>& p, const AdjPtrs& a, long long node) {
+__device__ __forceinline__ void stream_adjoint(const Ptrs<T>& p, const AdjPtrs& a, long long node) {
   const LatDev L = p.lat[0];
   const long long N = L.plane;
   if (node >= N) return;

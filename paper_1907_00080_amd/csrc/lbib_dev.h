@@ -281,6 +281,13 @@ __device__ __forceinline__ const Ptrs<T>& launch_args() {
   return *(const Ptrs<T>*)(const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// The same for the kernel's second argument, of type A.
+template <typename T, typename A>
+__device__ __forceinline__ const A& launch_args2() {
+  constexpr size_t off = (sizeof(Ptrs<T>) + alignof(A) - 1) / alignof(A) * alignof(A);
+  return *(const A*)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + off);
+}
+
 // Vertex chunks.  A body's vertices are cut into chunks of kChunk
 // consecutive vertices; chunk c of a body covers [kChunk c, kChunk c + cnt)
 // and is handled by one 64-lane wave whose lane i holds vertex
