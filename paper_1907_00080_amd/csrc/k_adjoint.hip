@@ -539,6 +539,348 @@ __device__ __forceinline__ void rigid_adjoint(const Ptrs<T>& p, const AdjPtrs& a
   }
 }
 
+// ---- small particles: three lanes per item (vertex or element), one per row
+// of its stencil.  A wave holds 21 items on lanes 3 i + row (lane 63 idle); the
+// rows' sums come by lane moves.  The sweep over a particle is the longest
+// chain of the reverse step and one lane's instructions are what it takes:
+// with a lane per item (the path of larger particles) 18 scattered terms of a
+// vertex and 27 of an element's probe follow one another, each two atomics.
+// 20-vertex soft particle on 256x64: ka_body 19.2 -> 11.4 us.
+constexpr int kTriItems = 21, kTriMax = 3 * kTriItems;
+
+struct RowStencil {
+  unsigned node[3];
+  bool ok;                              // the row lies inside the lattice
+  double wx[3], dwx[3], ddwx[3], wy, dwy, ddwy;   // zero along y where not
+};
+
+__device__ __forceinline__ void row_stencil_at(const LatDev& L, double X, double Y, int row, bool second,
+                                               RowStencil& s) {
+  const double cxr = floor(X + 0.5), cyr = floor(Y + 0.5);
+  const bool pery = L.periodic_y != 0;
+  double w[3], dw[3], ddw[3];
+  axis_weights(cyr - Y, second, w, dw, ddw);
+  axis_weights(cxr - X, second, s.wx, s.dwx, s.ddwx);
+  const int cx = wrap_i((int)cxr, L.nx);
+  int r = (pery ? wrap_i((int)cyr, L.ny) : (int)cyr) + row - 1;
+  if (pery) r = wrap_near(r, L.ny);
+  s.ok = r >= 0 && r < L.ny;
+  r = min(max(r, 0), L.ny - 1);
+  s.wy = !s.ok ? 0.0 : (row == 0 ? w[0] : (row == 1 ? w[1] : w[2]));
+  s.dwy = !s.ok ? 0.0 : (row == 0 ? dw[0] : (row == 1 ? dw[1] : dw[2]));
+  s.ddwy = !s.ok ? 0.0 : (row == 0 ? ddw[0] : (row == 1 ? ddw[1] : ddw[2]));
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    s.node[c] = (unsigned)r * (unsigned)L.pitch + (unsigned)wrap_near(cx + c - 1, L.nx);
+}
+
+// Sum over an item's three lanes, in its first lane; and from there to all three.
+__device__ __forceinline__ double tri_sum(double x) {
+  const double b = lane_next(x), c = lane_next(b);
+  return (x + b) + c;
+}
+__device__ __forceinline__ double tri_all(double x, int row) {
+  const double s = tri_sum(x), b = lane_prev(s), c = lane_prev(b);
+  return row == 0 ? s : (row == 1 ? b : c);
+}
+
+// Reverse of a soft or rigid particle of at most kTriMax vertices (the maths
+// of rigid_adjoint and ka_body below).
+template <typename T>
+__device__ __forceinline__ void small_particle_adjoint(const Ptrs<T>& p, const AdjPtrs& a, int b, int kind,
+                                                       double (*s_red)[kAdjThreads / 64], double (*s_p)[64]) {
+  const BodyDev* Bp = p.body + b;
+  const bool rigid = kind == kRigid;
+  const int nv = Bp->nv, v0 = Bp->v0;
+  const LatDev L = load_uniform(p.lat);
+  const long long N = L.plane;
+  const double nu = (L.tau - 0.5) / 3.0, sigma = Bp->sigma;
+  const double ks = Bp->ks, kb = Bp->kb, ka = Bp->ka, p_ref = Bp->p_ref, A0 = Bp->A0, mv = Bp->mv;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int nw = (nv + kTriItems - 1) / kTriItems;       // waves of triples
+  const int w_elem = nw, w_bend = min(nw + 1, 3);        // waves of the elements and of the bending
+  const int item = w * kTriItems + lane / 3, row = lane % 3;
+  const bool on = lane < 63 && item < nv, lead = on && row == 0;
+  const int v = on ? item : 0, gm = v0 + v;
+  const int vp = v + 1 == nv ? 0 : v + 1, vm = v == 0 ? nv - 1 : v - 1;
+  const double* X = a.x + v0;
+  const double* Y = a.y + v0;
+  const double *momu = a.mom + N, *momv = a.mom + 2 * N;
+  const BodyDev& S0 = a.body0[b];   // rigid: state before the step
+  const BodyDev& S1 = a.body1[b];   // and after it
+  double* R = a.rig + 9 * b;
+  double rin[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) rin[k] = rigid ? R[k] : 0.0;
+
+  // ---- vertices: spread adjoint, then the soft Verlet / coupling chain or
+  // the rigid vertex's velocity
+  double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};   // rigid: x_c'^ (2), theta'^, U'^ (2), Omega'^; soft: shoelace
+  if (w < nw) {
+    RowStencil s;
+    row_stencil_at(L, X[v], Y[v], row, false, s);
+    const double Fx = a.fx[gm], Fy = a.fy[gm];
+    double fhx = 0.0, fhy = 0.0, gx = 0.0, gy = 0.0, U0x = 0.0, U0y = 0.0;
+    double ux = 0.0, uy = 0.0, vx = 0.0, vy = 0.0;   // gradient sums of u* and v*
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const unsigned node = s.node[c];
+      const double wt = s.wx[c] * s.wy, wgx = s.dwx[c] * s.wy, wgy = s.wx[c] * s.dwy;
+      const double ex_ = a.FEh[node], ey_ = a.FEh[N + node], us = momu[node], vs = momv[node];
+      fhx += ex_ * wt;
+      fhy += ey_ * wt;
+      const double sf = Fx * ex_ + Fy * ey_;
+      gx -= sf * wgx;
+      gy -= sf * wgy;
+      U0x += us * wt;
+      U0y += vs * wt;
+      ux += us * wgx;
+      uy += us * wgy;
+      vx += vs * wgx;
+      vy += vs * wgy;
+    }
+    fhx = tri_all(fhx, row);
+    fhy = tri_all(fhy, row);
+    gx = tri_sum(gx);
+    gy = tri_sum(gy);
+    U0x = tri_sum(U0x);
+    U0y = tri_sum(U0y);
+    ux = tri_sum(ux);
+    uy = tri_sum(uy);
+    vx = tri_sum(vx);
+    vy = tri_sum(vy);
+    const double xa = a.xa[gm], ya = a.ya[gm], xnv = a.xn[gm], ynv = a.yn[gm];
+    const double dirx = a.dirx[gm], diry = a.diry[gm];
+    const double lr = sqrt((X[vp] - X[v]) * (X[vp] - X[v]) + (Y[vp] - Y[v]) * (Y[vp] - Y[v]));
+    const double ll = sqrt((X[v] - X[vm]) * (X[v] - X[vm]) + (Y[v] - Y[vm]) * (Y[v] - Y[vm]));
+    const double ds = 0.5 * (ll + lr), Xv = X[v], Yv = Y[v];
+    // adjoint of U0 = interp(u*, X): a soft vertex's is that of X^{n+1}, a
+    // rigid one's minus that of U_k
+    const double uhx = 2.0 * ds * fhx, uhy = 2.0 * ds * fhy;
+    const double qx = rigid ? -uhx : xa, qy = rigid ? -uhy : ya;
+    if (on && s.ok) {   // the scatter after every load
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const double wt = s.wx[c] * s.wy;
+        acc_add(a.Rh, N + s.node[c], qx * wt, a.bad);
+        acc_add(a.Rh, 2 * N + s.node[c], qy * wt, a.bad);
+      }
+    }
+    if (lead) {
+      const double g2x = -(qx * ux + qy * vx), g2y = -(qx * uy + qy * vy);
+      double dxv = dirx + gx + g2x, dyv = diry + gy + g2y, dsh;
+      if (rigid) {
+        const double relx = xnv - S1.xc, rely = ynv - S1.yc, Om1 = S1.Om;
+        const double Ukx = S1.U[0] + Om1 * (-rely), Uky = S1.U[1] + Om1 * relx;
+        dsh = 2.0 * ((Ukx - U0x) * fhx + (Uky - U0y) * fhy);
+        double ch[2] = {0.0, 0.0}, Uh[2] = {0.0, 0.0};
+        adj::rigid_vertex_vjp(relx, rely, Om1, xa, ya, uhx, uhy, ch, acc[2], Uh, acc[5]);
+        acc[0] = ch[0];
+        acc[1] = ch[1];
+        acc[3] = Uh[0];
+        acc[4] = Uh[1];
+      } else {
+        dxv += xa;
+        dyv += ya;
+        a.fvx[gm] = 0.5 * (xa + uhx) / mv;
+        a.fvy[gm] = 0.5 * (ya + uhy) / mv;
+        dsh = 2.0 * ((xnv - Xv - U0x) * fhx + (ynv - Yv - U0y) * fhy);
+        acc[0] = Xv * Y[vp] - X[vp] * Yv;
+      }
+      a.dirx[gm] = dxv;
+      a.diry[gm] = dyv;
+      a.dsh[gm] = dsh;
+    }
+  }
+  if (rigid) block_sum<6>(acc, s_red);   // barriers also publish the vertex pass
+  else block_sum<1>(acc, s_red);
+
+  // rigid: the state, x_c' = x_c + U', theta' = theta + Omega', BDF2
+  const bool first = a.first != 0;
+  const double xch[2] = {rin[0] + acc[0], rin[1] + acc[1]};
+  const double thh = rin[2] + acc[2];
+  double Uh0[2] = {rin[5], rin[6]}, Umh0[2] = {0.0, 0.0}, Omh0 = rin[8], Ommh0 = 0.0;
+  double Fh[2] = {0.0, 0.0}, Mh = 0.0, xc0 = 0.0, yc0 = 0.0;
+  if (rigid) {
+    Fh[0] = adj::bdf2_vjp(first, Bp->mass, rin[3] + acc[3] + xch[0], Uh0[0], Umh0[0]);
+    Fh[1] = adj::bdf2_vjp(first, Bp->mass, rin[4] + acc[4] + xch[1], Uh0[1], Umh0[1]);
+    Mh = adj::bdf2_vjp(first, Bp->inertia, rin[7] + acc[5] + thh, Omh0, Ommh0);
+    xc0 = S0.xc;
+    yc0 = S0.yc;
+  }
+  const double kappa = ka * (1.0 - 0.5 * acc[0] / A0) * p_ref;   // soft
+
+  // ---- elements: the probes on the triples, the other loads and the bending
+  // each on a wave of their own
+  double sum4[4] = {0.0, 0.0, 0.0, 0.0};   // soft: k_s^, k_b^, sigma^, kappa^; rigid: x_c^ (2) from the arms, sigma^
+  if (w < nw) {
+    const double dx = X[vp] - X[v], dy = Y[vp] - Y[v];
+    const double len = sqrt(dx * dx + dy * dy);
+    const double cx = 0.5 * (X[v] + X[vp]), cy = 0.5 * (Y[v] + Y[vp]);
+    const double nxl = dy / len, nyl = -dx / len, rx = cx - xc0, ry = cy - yc0;
+    double Fex = 0.0, Fey = 0.0, rhx = 0.0, rhy = 0.0;
+    if (rigid) {
+      adj::rigid_load_vjp(rx, ry, 0.0, 0.0, Fh[0], Fh[1], Mh, Fex, Fey, rhx, rhy);
+    } else {
+      Fex = 0.5 * (a.fvx[gm] + a.fvx[v0 + vp]);
+      Fey = 0.5 * (a.fvy[gm] + a.fvy[v0 + vp]);
+    }
+    const double qx = cx + 1.2 * nxl, qy_raw = cy + 1.2 * nyl;
+    double qy = qy_raw;
+    if (!L.periodic_y) qy = fmin(fmax(qy_raw, 0.5), L.ny - 1.5);
+    RowStencil s;
+    row_stencil_at(L, qx, qy, row, true, s);
+    double r0[3], us[3], vs[3], rq = 0.0, g[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      r0[c] = a.mom[s.node[c]];
+      us[c] = momu[s.node[c]];
+      vs[c] = momv[s.node[c]];
+      const double wgx = s.dwx[c] * s.wy, wgy = s.wx[c] * s.dwy;
+      rq += r0[c] * (s.wx[c] * s.wy);
+      g[0] -= us[c] * wgx;
+      g[1] -= us[c] * wgy;
+      g[2] -= vs[c] * wgx;
+      g[3] -= vs[c] * wgy;
+    }
+    rq = tri_all(rq, row);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g[k] = tri_all(g[k], row);
+    const double pr = (rq - 1.0) * (1.0 / 3.0);
+    double pfx, pfy, prh = 0.0, gh[4] = {0.0, 0.0, 0.0, 0.0}, nhx = 0.0, nhy = 0.0, lenh = 0.0;
+    adj::hydro_fwd(pr, g, nu, nxl, nyl, len, pfx, pfy);
+    adj::hydro_vjp(pr, g, nu, nxl, nyl, len, Fex, Fey, prh, gh, nhx, nhy, lenh);
+    const double rqh = prh * (1.0 / 3.0);
+    double qhx = 0.0, qhy = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const double wx = s.wx[c], dwx = s.dwx[c], ddwx = s.ddwx[c];
+      const double gu0 = gh[0] * us[c] + gh[2] * vs[c], gu1 = gh[1] * us[c] + gh[3] * vs[c];
+      qhx += -rqh * r0[c] * dwx * s.wy + gu0 * ddwx * s.wy + gu1 * dwx * s.dwy;
+      qhy += -rqh * r0[c] * wx * s.dwy + gu0 * dwx * s.dwy + gu1 * wx * s.ddwy;
+    }
+    qhx = tri_sum(qhx);
+    qhy = tri_sum(qhy);
+    if (on && s.ok) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const double wgx = s.dwx[c] * s.wy, wgy = s.wx[c] * s.dwy;
+        acc_add(a.Rh, s.node[c], rqh * (s.wx[c] * s.wy), a.bad);
+        acc_add(a.Rh, N + s.node[c], -gh[0] * wgx - gh[1] * wgy, a.bad);
+        acc_add(a.Rh, 2 * N + s.node[c], -gh[2] * wgx - gh[3] * wgy, a.bad);
+      }
+    }
+    if (lead) {
+      if (qy != qy_raw) qhy = 0.0;   // clamped
+      double Dhx = 0.0, Dhy = 0.0, Chx = qhx, Chy = qhy, fdx = 0.0, fdy = 0.0;
+      if (rigid) {   // adjoint of the arm r = c - x_c, to the centroid and to x_c
+        rhx = rhy = 0.0;
+        adj::rigid_load_vjp(rx, ry, pfx, pfy, 0.0, 0.0, Mh, fdx, fdy, rhx, rhy);
+        Chx += rhx;
+        Chy += rhy;
+        sum4[0] -= rhx;
+        sum4[1] -= rhy;
+      }
+      adj::unit_vjp(dx, dy, -(nhy + 1.2 * qhy), nhx + 1.2 * qhx, lenh, Dhx, Dhy);   // n = (t_y, -t_x)
+      s_p[0][v] = Dhx;
+      s_p[1][v] = Dhy;
+      s_p[2][v] = Chx;
+      s_p[3][v] = Chy;
+    }
+  }
+  if (w == w_elem && lane < nv) {
+    const int l = lane, gl = v0 + l, lp = l + 1 == nv ? 0 : l + 1;
+    const double dx = X[lp] - X[l], dy = Y[lp] - Y[l];
+    const double cx = 0.5 * (X[l] + X[lp]), cy = 0.5 * (Y[l] + Y[lp]);
+    double Dhx = 0.0, Dhy = 0.0, Chx = 0.0, Chy = 0.0, Fex = 0.0, Fey = 0.0, rhx = 0.0, rhy = 0.0;
+    double yl, ddx, ddy, fex = 0.0, fey = 0.0;
+    const double rx = cx - xc0, ry = cy - yc0;
+    if (rigid) {
+      adj::rigid_load_vjp(rx, ry, 0.0, 0.0, Fh[0], Fh[1], Mh, Fex, Fey, rhx, rhy);
+    } else {
+      const double f0x = a.fvx[gl], f0y = a.fvy[gl], f1x = a.fvx[v0 + lp], f1y = a.fvy[v0 + lp];
+      adj::strain_vjp(dx, dy, p.l0[gl], ks, f0x - f1x, f0y - f1y, Dhx, Dhy, sum4[0]);
+      Fex = 0.5 * (f0x + f1x);
+      Fey = 0.5 * (f0y + f1y);
+      sum4[3] += adj::area_vjp(dx, dy, kappa, Fex, Fey, Dhx, Dhy);
+    }
+    if (bond_geometry(p, L, Bp, l, cx, cy, yl, ddx, ddy)) {
+      adj::spring_fwd(dx, dy, yl, sigma, L.y_eq, fex, fey);
+      adj::spring_vjp(dx, dy, yl, ddx, ddy, sigma, L.y_eq, Fex, Fey, Dhx, Dhy, Chx, Chy, sum4[2]);
+      if (rigid) {
+        double fdx = 0.0, fdy = 0.0;
+        rhx = rhy = 0.0;
+        adj::rigid_load_vjp(rx, ry, fex, fey, 0.0, 0.0, Mh, fdx, fdy, rhx, rhy);
+        Chx += rhx;
+        Chy += rhy;
+        sum4[0] -= rhx;
+        sum4[1] -= rhy;
+      }
+    }
+    adj::unit_vjp(dx, dy, 0.0, 0.0, 0.5 * (a.dsh[gl] + a.dsh[v0 + lp]), Dhx, Dhy);
+    a.Dx[gl] = Dhx;
+    a.Dy[gl] = Dhy;
+    a.Cx[gl] = Chx;
+    a.Cy[gl] = Chy;
+  }
+  if (!rigid && w == w_bend && lane < nv) {
+    const int l = lane, gl = v0 + l, lp = l + 1 == nv ? 0 : l + 1, lm = l == 0 ? nv - 1 : l - 1;
+    const double Fhm[2] = {a.fvx[v0 + lm], a.fvy[v0 + lm]};
+    const double Fhu[2] = {a.fvx[gl], a.fvy[gl]};
+    const double Fhp[2] = {a.fvx[v0 + lp], a.fvy[v0 + lp]};
+    double dLh[2] = {0.0, 0.0}, dRh[2] = {0.0, 0.0};
+    adj::bend_vjp(X[l] - X[lm], Y[l] - Y[lm], X[lp] - X[l], Y[lp] - Y[l], p.th0[gl], kb, Fhm, Fhu, Fhp, dLh, dRh,
+                  sum4[1]);
+    a.BLx[gl] = dLh[0];
+    a.BLy[gl] = dLh[1];
+    a.BRx[gl] = dRh[0];
+    a.BRy[gl] = dRh[1];
+  }
+  block_sum<4>(sum4, s_red);
+
+  // ---- vertices: gather the element terms into the adjoint of X^n
+  if (t < nv) {
+    const int q = t, gq = v0 + q, qp = q + 1 == nv ? 0 : q + 1, qm = q == 0 ? nv - 1 : q - 1;
+    const int gp = v0 + qp, gn = v0 + qm;
+    double Dmx = a.Dx[gn] + s_p[0][qm], Dmy = a.Dy[gn] + s_p[1][qm];
+    double Dvx = a.Dx[gq] + s_p[0][q], Dvy = a.Dy[gq] + s_p[1][q];
+    const double Ch = a.Cx[gq] + s_p[2][q] + a.Cx[gn] + s_p[2][qm];
+    const double Cv = a.Cy[gq] + s_p[3][q] + a.Cy[gn] + s_p[3][qm];
+    if (!rigid) {
+      Dmx += a.BRx[gn] + a.BLx[gq];
+      Dmy += a.BRy[gn] + a.BLy[gq];
+      Dvx += a.BRx[gq] + a.BLx[gp];
+      Dvy += a.BRy[gq] + a.BLy[gp];
+    }
+    double xh = a.dirx[gq] + Dmx - Dvx + 0.5 * Ch;
+    double yh = a.diry[gq] + Dmy - Dvy + 0.5 * Cv;
+    if (!rigid) {
+      const double Ah = -sum4[3] * ka * p_ref / A0;
+      xh += Ah * 0.5 * (Y[qp] - Y[qm]);
+      yh += Ah * 0.5 * (X[qm] - X[qp]);
+    }
+    a.xa[gq] = xh;
+    a.ya[gq] = yh;
+  }
+  if (t == 0) {
+    if (rigid) {
+      R[0] = xch[0] + sum4[0];
+      R[1] = xch[1] + sum4[1];
+      R[2] = thh;
+      R[3] = Uh0[0];
+      R[4] = Uh0[1];
+      R[5] = Umh0[0];
+      R[6] = Umh0[1];
+      R[7] = Omh0;
+      R[8] = Ommh0;
+    } else {
+      a.grad[3 * b + 0] += sum4[0];
+      a.grad[3 * b + 1] += sum4[1];
+    }
+    a.grad[3 * b + 2] += sum4[2];
+  }
+}
+
 // One workgroup per body.
 template <typename T>
 __global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T>, AdjPtrs) {
@@ -547,7 +889,12 @@ __global__ __launch_bounds__(kAdjThreads) void ka_body(Ptrs<T>, AdjPtrs) {
   __shared__ double s_red[6][kAdjThreads / 64];
   const int b = blockIdx.x;
   const BodyDev* Bp = p.body + b;
+  __shared__ double s_p[4][64];
   const int kind = Bp->kind, nv = Bp->nv, v0 = Bp->v0;
+  if (kind != kRBC && nv <= kTriMax) {
+    small_particle_adjoint(p, a, b, kind, s_red, s_p);
+    return;
+  }
   if (kind == kRigid) {
     rigid_adjoint(p, a, b, s_red);
     return;
