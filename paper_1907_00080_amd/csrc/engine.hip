@@ -1066,25 +1066,29 @@ AdjPtrs adj_ptrs(const lbib_ctx* c, const AdjLayout& A) {
   return a;
 }
 
-// Save (or restore) the dynamic state to (from) checkpoint j.
-void adj_checkpoint(lbib_ctx* c, const AdjLayout& A, int j, bool save) {
+// Save (or restore) the dynamic state to (from) checkpoint j.  pop: restore the
+// populations (in scheme-0 order) there instead of into the state.
+void adj_checkpoint(lbib_ctx* c, const AdjLayout& A, int j, bool save, char* pop = nullptr) {
   char* base = c->aws + A.ck + (size_t)j * A.ck_bytes;
   if (save) (void)stage_state(c);
   CopyList cl{};
   size_t off = 0;
+  bool populations = true;   // the first region
   for (auto& r : state_regions(c)) {
     if (cl.n == 24) {
       launch_copies(cl, c->stream);
       cl.n = 0;
     }
-    cl.src[cl.n] = save ? c->ws + r.first : base + off;
-    cl.dst[cl.n] = save ? base + off : c->ws + r.first;
+    char* state = populations && pop ? pop : c->ws + r.first;
+    populations = false;
+    cl.src[cl.n] = save ? state : base + off;
+    cl.dst[cl.n] = save ? base + off : state;
     cl.bytes[cl.n] = r.second;
     ++cl.n;
     off += align256(r.second);
   }
   launch_copies(cl, c->stream);
-  if (!save) (void)unstage_state(c);
+  if (!save && !pop) (void)unstage_state(c);
 }
 
 lbib_status set_freeze(lbib_ctx* c, int32_t f) {
@@ -1167,16 +1171,34 @@ lbib_status adjoint_forward_impl(lbib_ctx* c, double* J) {
   return LBIB_OK;
 }
 
-// Recompute n steps from the restored state into segment store `buf`,
-// keeping the forward data of each step (one copy launch per step, after its
-// lattice kernel: the populations h^n are still in the read buffer, positions
-// X^n, forces and particle positions X^{n+1} are set, u^n is written).
+// Where step s of a segment's recompute reads and writes: its populations h^s
+// and velocity u^s live in record s of the store and the step writes h^{s+1}
+// into the next record (two-buffer streaming, whatever the context's form; the
+// last step writes the buffer that the state does not hold).  Nothing of a
+// lattice is copied.  (Before, the step ran on the state and a conversion and
+// a copy kernel stored both: 5.8 + 2 us of 27 a step on 256x64.)
+template <typename T>
+Ptrs<T> recompute_ptrs(const lbib_ctx* c, const AdjLayout& A, int buf, long long s, long long n) {
+  char* rec = c->aws + A.seg[buf] + (size_t)s * A.rec_bytes;
+  Ptrs<T> p = make_ptrs<T>(c);
+  T* spare = c->inplace ? (T*)(c->ws + c->L.B) : p.B;
+  p.A = (T*)(rec + A.r_h);
+  p.B = s + 1 < n ? (T*)(rec + A.rec_bytes + A.r_h) : spare;
+  p.U = (T*)(rec + A.r_u);
+  p.sch = p.sch_next = 0;
+  return p;
+}
+
+// Recompute n steps into segment store `buf` (record 0 holds the populations),
+// keeping the forward data of each step: beside the lattice data, one copy
+// launch per step after its lattice kernel, while the positions X^n, forces and
+// particle positions X^{n+1} are set.
 template <typename T>
 void enqueue_recompute(lbib_ctx* c, const AdjLayout& A, int buf, long long n) {
-  const long long N = c->nodes;
-  const size_t es = elem_size(c->dtype), nmb = 8 * (size_t)c->nm;
+  const size_t nmb = 8 * (size_t)c->nm;
   const size_t bb = sizeof(BodyDev) * (size_t)c->nbody;
-  const StepArgs sa = step_args(c);
+  StepArgs sa = step_args(c);
+  sa.nt_mode = 0;   // the next step and the reverse sweep read what a step writes
   char* seg = c->aws + A.seg[buf];
   if (bb > 0) {   // the bodies before the first step (later steps: after the previous one)
     CopyList cl{};
@@ -1188,28 +1210,18 @@ void enqueue_recompute(lbib_ctx* c, const AdjLayout& A, int buf, long long n) {
   }
   for (long long s = 0; s < n; ++s) {
     char* rec = seg + (size_t)s * A.rec_bytes;
-    Ptrs<T> p = make_ptrs<T>(c);
+    const Ptrs<T> p = recompute_ptrs<T>(c, A, buf, s, n);
     launch_lagrangian<T>(p, sa, c->stream);
-    if (c->inplace) {
-      // h^n in scheme-0 order, before the lattice kernel rewrites its buffer
-      const long long nn = (long long)c->inst[0].lat.nx * c->inst[0].lat.ny;
-      launch_canon<T>(p, 1, &nn, (T*)(rec + A.r_h), 1, c->stream);
-    }
     launch_lb_fused<T>(p, sa, c->stream);
     CopyList cl{};
-    const char* src[10] = {(const char*)p.A, (const char*)p.x, (const char*)p.y, (const char*)p.fx,
-                           (const char*)p.fy, (const char*)p.xn, (const char*)p.yn, (const char*)p.U,
-                           (const char*)p.body, (const char*)p.body};
-    const size_t off[10] = {A.r_h, A.r_x, A.r_y, A.r_fx, A.r_fy, A.r_xn, A.r_yn, A.r_u, A.r_b1,
-                            A.rec_bytes + A.r_b0};
-    const size_t by[10] = {es * 9 * N, nmb, nmb, nmb, nmb, nmb, nmb, es * 2 * N, bb, bb};
-    const int k0 = c->inplace ? 1 : 0;   // in place, h^n is stored already
-    const int kn = bb == 0 ? 8 : (s + 1 < n ? 10 : 9);
-    cl.n = kn - k0;
-    for (int k = k0; k < kn; ++k) {
-      cl.src[k - k0] = src[k];
-      cl.dst[k - k0] = rec + off[k];
-      cl.bytes[k - k0] = by[k];
+    const char* src[8] = {(const char*)p.x, (const char*)p.y, (const char*)p.fx, (const char*)p.fy,
+                          (const char*)p.xn, (const char*)p.yn, (const char*)p.body, (const char*)p.body};
+    const size_t off[8] = {A.r_x, A.r_y, A.r_fx, A.r_fy, A.r_xn, A.r_yn, A.r_b1, A.rec_bytes + A.r_b0};
+    cl.n = bb == 0 ? 0 : (s + 1 < n ? 8 : 7);
+    for (int k = 0; k < cl.n; ++k) {
+      cl.src[k] = src[k];
+      cl.dst[k] = rec + off[k];
+      cl.bytes[k] = k < 6 ? nmb : bb;
     }
     launch_copies(cl, c->stream);
     launch_advance<T>(p, sa, c->stream);
@@ -1303,13 +1315,13 @@ lbib_status adjoint_backward_impl(lbib_ctx* c, double dJ, double* grad) {
   for (int j = A.nseg - 1; j >= 0; --j) {
     const int buf = j & 1;
     if (j + 2 <= A.nseg - 1) HIPCHK(c, hipStreamWaitEvent(c->stream, c->ev_rev[buf], 0));
-    adj_checkpoint(c, A, j, false);
-    c->step = c->ck_step[j];
-    // marker bins of the restored positions (eager, outside the graphs)
-    HIPCHK(c, hipMemsetAsync(c->ws + c->L.cnt[c->parity], 0, 4 * (size_t)c->ntiles, c->stream));
-    launch_stencil<T>(make_ptrs<T>(c), step_args(c), c->stream);
-    c->stencil_dirty = false;
     const long long n = std::min<long long>(c->adjk, c->adjK - (long long)j * c->adjk);
+    adj_checkpoint(c, A, j, false, c->aws + A.seg[buf] + A.r_h);
+    c->step = c->ck_step[j];
+    // marker bins and star field of the restored state (eager, outside the graphs)
+    HIPCHK(c, hipMemsetAsync(c->ws + c->L.cnt[c->parity], 0, 4 * (size_t)c->ntiles, c->stream));
+    launch_stencil<T>(recompute_ptrs<T>(c, A, buf, 0, n), step_args(c), c->stream);
+    c->stencil_dirty = false;
     const int par = c->parity, first = c->ck_step[j] == 0 ? 1 : 0;
     hipGraphExec_t gr, gv;
     st = cached_graph(c, c->adj_graphs, std::make_tuple(n, par, buf), c->stream,
