@@ -365,7 +365,7 @@ void compute_layout(lbib_ctx* c) {
   L.star = take(es * 4 * (size_t)c->nodes);
   L.pbox = take(4 * 4 * nch);
   L.star_wg = take(4 * 3 * (size_t)std::max(c->nstar_wg, 1));
-  L.slot_chunk = take(8 * (size_t)std::max(c->nslot, 1));
+  L.slot_chunk = take(sizeof(ChunkSlot) * (size_t)std::max(c->nslot, 1));
   L.total = cur;
 }
 
@@ -441,7 +441,7 @@ Ptrs<T> make_ptrs(const lbib_ctx* c) {
   p.pbox = (int*)(w + L.pbox);
   p.star_wg = (const int*)(w + L.star_wg);
   p.nstar_wg = c->nstar_wg;
-  p.slot_chunk = (const int2*)(w + L.slot_chunk);
+  p.slot_chunk = (const ChunkSlot*)(w + L.slot_chunk);
   p.nslot = c->nslot;
   p.nm_total = c->nm;
   p.nbody_total = c->nbody;
@@ -704,32 +704,27 @@ lbib_status upload_all(lbib_ctx* c) {
     if (!sw.empty()) HIPCHK(c, up(L.star_wg, sw.data(), 4 * sw.size()));
   }
   {
-    // waves of the chunked body kernel, as (chunk, body): one workgroup per
-    // grouped rigid body first (chunk c on wave c, idle waves -2), then the
-    // chunks of the other particles and of the red cells, packed (the
-    // particles' chains are the longer ones: they start first)
-    std::vector<int> sl;
+    // waves of the chunked body kernel: one workgroup per grouped rigid body
+    // first (chunk c on wave c, idle waves -2), then the chunks of the other
+    // particles and of the red cells, packed (the particles' chains are the
+    // longer ones: they start first)
+    std::vector<ChunkSlot> sl;
+    auto slot = [&](int bb, int k, bool idle) {
+      const BodyDev& B = bodies[bb];
+      sl.push_back({idle ? -2 : B.chunk0 + k, bb, B.v0, B.nv, k * kChunk, B.kind | (B.inst << 2), B.chunk0, 0});
+    };
     for (int bb = 0; bb < c->nbody; ++bb)
       if (rigid_grouped(bodies[bb].kind, bodies[bb].nv))
-        for (int k = 0; k < kGroupChunks; ++k) {
-          sl.push_back(k < chunks_of(bodies[bb].nv) ? bodies[bb].chunk0 + k : -2);
-          sl.push_back(bb);
-        }
+        for (int k = 0; k < kGroupChunks; ++k) slot(bb, k, k >= chunks_of(bodies[bb].nv));
     for (int pass = 0; pass < 2; ++pass)
       for (int bb = 0; bb < c->nbody; ++bb) {
         const bool rbc = bodies[bb].kind == LBIB_RBC_KINEMATIC;
         if (rigid_grouped(bodies[bb].kind, bodies[bb].nv) || rbc != (pass == 1)) continue;
-        for (int k = 0; k < chunks_of(bodies[bb].nv); ++k) {
-          sl.push_back(bodies[bb].chunk0 + k);
-          sl.push_back(bb);
-        }
+        for (int k = 0; k < chunks_of(bodies[bb].nv); ++k) slot(bb, k, false);
       }
-    while (sl.size() % (2 * kGroupChunks)) {
-      sl.push_back(-1);
-      sl.push_back(0);
-    }
-    if ((int)sl.size() != 2 * c->nslot) return fail(c, LBIB_EINVAL, "internal: wave slot count");
-    if (!sl.empty()) HIPCHK(c, up(L.slot_chunk, sl.data(), 4 * sl.size()));
+    while (sl.size() % kGroupChunks) sl.push_back({-1, 0, 0, 0, 0, 0, 0, 0});
+    if ((int)sl.size() != c->nslot) return fail(c, LBIB_EINVAL, "internal: wave slot count");
+    if (!sl.empty()) HIPCHK(c, up(L.slot_chunk, sl.data(), sizeof(ChunkSlot) * sl.size()));
   }
   HIPCHK(c, up(L.tile_inst, tile_inst.data(), 4 * tile_inst.size()));
   HIPCHK(c, up(L.lig_body, lig_body.data(), 4 * lig_body.size()));

@@ -487,51 +487,84 @@ __device__ __forceinline__ int first_not_left(const double* xs, int n, double x,
   return lo;
 }
 
+constexpr int kBodyThreads = 256;
+constexpr int kWaves = kBodyThreads / 64;
+// the wave's number in its workgroup, in a scalar register
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+constexpr int kLigRanks = 4;   // ligands per lane and pass of the bond kinetics
+
+// What the bond workgroup holds in LDS: the eligible ligands per wave and
+// rank (two sets, used by alternate passes), and the first 64 eligible ones.
+struct BondLds {
+  int cnt[2][kLigRanks][kWaves];
+  int code[64];                  // ligand << 1 | wall
+  double cx[64], cy[64], sig[64];
+};
+
+// The step waits for this chain (the particles near a wall need its bonds), so
+// it is kept short: all loads of a pass in flight together, one barrier per
+// pass, and the first 64 eligible ligands handed to the formation through LDS.
+// (Six boxes with a particle at the wall: the flag goes up after 4.2 us, 5.9
+// with three barriers per pass and the ligands read back from memory; the
+// kernel takes 9.3 us, 11.2 before.)
 template <typename T>
 __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L, int inst, long long n,
-                                               int nx, int ny, int* s_tmp, int& s_nelig) {
-  const int tid = threadIdx.x, nt = blockDim.x;
+                                               int nx, int ny, BondLds& S) {
+  constexpr int R = kLigRanks, nt = kBodyThreads, nw = kWaves;
+  const int tid = threadIdx.x;
   // bond kinetics (Sec. 2.2): rupture then formation (a frozen topology
   // skips both); then every bond's spring coefficient sigma (y_l - y_eq)
   // at X^n for the particles' spring forces (Eq. adhFor)
   if (L.n_lig == 0) return;
   const bool kinetics = !L.freeze;
-  __syncthreads();
-  if (tid == 0) s_nelig = 0;
-  __syncthreads();
   const double y_cr = L.y_cr;
   unsigned long long ties = 0;
   // (a) rupture (independent per bond) and formation eligibility; R
   // ligands per lane and pass (l0 + r nt + tid), their loads in flight
   // together
-  constexpr int R = 4;
-  const int lane = tid & 63, w = tid >> 6, nw = nt >> 6;
+  const int lane = tid & 63, w = wave_id();
   const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (int l0 = 0; l0 < L.n_lig; l0 += R * nt) {
+  int ne = 0;        // eligible ligands of the passes so far
+  bool odd = false;
+  for (int l0 = 0; l0 < L.n_lig; l0 += R * nt, odd = !odd) {
     int gl[R], va[R], vb[R], rr[R], flag[R];
-    bool on[R];
+    double sigma[R], x0[R], x1[R], y0[R], y1[R], xr[R];
+    // ranks that hold a ligand (the same for every lane)
+    auto held = [&](int r) { return l0 + r * nt < L.n_lig; };
+    auto on = [&](int r) { return l0 + r * nt + tid < L.n_lig; };
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int l = l0 + r * nt + tid;
-      on[r] = l < L.n_lig;
-      gl[r] = L.lig_base + (on[r] ? l : 0);
+      flag[r] = 0;
+      if (!held(r)) continue;
+      gl[r] = L.lig_base + (on(r) ? l0 + r * nt + tid : 0);
       va[r] = p.lig_va[gl[r]];
       vb[r] = p.lig_vb[gl[r]];
       rr[r] = p.l2r[gl[r]];
+      sigma[r] = p.lig_sigma[gl[r]];
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int l = l0 + r * nt + tid;
-      flag[r] = 0;
-      if (!on[r]) continue;
+      if (!held(r)) continue;
       // particle positions X^n: xn (equal to x once a step has ended)
-      const double cx = 0.5 * (p.xn[va[r]] + p.xn[vb[r]]);
-      const double cy = 0.5 * (p.yn[va[r]] + p.yn[vb[r]]);
+      x0[r] = p.xn[va[r]];
+      x1[r] = p.xn[vb[r]];
+      y0[r] = p.yn[va[r]];
+      y1[r] = p.yn[vb[r]];
+      xr[r] = p.rec_x[rr[r] >= 0 ? L.rec_base + rr[r] : 0];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (!on(r)) continue;
+      const int l = l0 + r * nt + tid;
+      x0[r] = 0.5 * (x0[r] + x1[r]);   // the element's centroid
+      y0[r] = 0.5 * (y0[r] + y1[r]);
+      const double cx = x0[r], cy = y0[r];
       const int rc = rr[r];
       if (rc >= 0) {
         const int wall = rc < L.n_rec0 ? 0 : 1;
-        const double yl = bond_len(cx, cy, p.rec_x[L.rec_base + rc], wall, L);
-        const double sig = p.lig_sigma[gl[r]], sts = L.sigma_ts_frac * sig;
+        const double yl = bond_len(cx, cy, xr[r], wall, L);
+        const double sig = sigma[r], sts = L.sigma_ts_frac * sig;
         const double dy = yl - L.y_eq;
         bool broken = false;
         if (kinetics) {
@@ -555,35 +588,43 @@ __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L
         if (d < y_cr) flag[r] = 1 + wall;
       }
     }
+    if (!kinetics) continue;
     // ordered compaction of the eligible ligands (ascending ligand id):
     // per-wave counts by ballot, then every lane's place from the counts of
-    // the earlier ligand ranges and waves
+    // the earlier ligand ranges and waves.  The next pass writes the other
+    // set of counts: a set is written again only after the barrier that
+    // follows its last reading.
+    int(*cnt)[kWaves] = S.cnt[odd];
     unsigned long long bal[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       bal[r] = __ballot(flag[r] != 0);
-      if (lane == 0) s_tmp[r * nw + w] = __popcll(bal[r]);
+      if (lane == 0) cnt[r][w] = __popcll(bal[r]);
     }
     __syncthreads();
-    const int base = s_nelig;
-    int off = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       int before = 0, tot = 0;
+#pragma unroll
       for (int k = 0; k < nw; ++k) {
-        const int c = s_tmp[r * nw + k];
+        const int c = cnt[r][k];
         before += k < w ? c : 0;
         tot += c;
       }
       if (flag[r]) {
-        const int pos = base + off + before + __popcll(bal[r] & lt);
-        p.lig_flag[L.lig_base + pos] = ((l0 + r * nt + tid) << 1) | (flag[r] - 1);
+        const int pos = ne + before + __popcll(bal[r] & lt);
+        const int code = ((l0 + r * nt + tid) << 1) | (flag[r] - 1);
+        if (pos < 64) {
+          S.code[pos] = code;
+          S.cx[pos] = x0[r];
+          S.cy[pos] = y0[r];
+          S.sig[pos] = sigma[r];
+        } else {
+          p.lig_flag[L.lig_base + pos] = code;
+        }
       }
-      off += tot;
+      ne += tot;
     }
-    __syncthreads();
-    if (tid == 0) s_nelig = base + off;
-    __syncthreads();
   }
   // (b) formation, in ascending ligand order.  A ligand's choice (the nearest
   // free receptor of its wall) and draw depend on the earlier ones only
@@ -591,23 +632,40 @@ __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L
   // for 64 eligible ligands together; then the bonds form in order, and only a
   // ligand whose receptor has just gone chooses again.  (One lane taking the
   // ligands one after the other cost about 3 us each.)
-  if (tid < 64 && kinetics) {
-    const int ne = s_nelig;
+  if (ne == 0) {
+    if (ties) atomicAdd(&p.ties[inst], ties);
+    return;
+  }
+  __syncthreads();   // the eligible ligands, and the receptors that rupture freed
+  if (tid < 64) {
     for (int q0 = 0; q0 < ne; q0 += 64) {
       const bool on = q0 + lane < ne;
-      const int code = on ? p.lig_flag[L.lig_base + q0 + lane] : 0;
+      int code = 0;
+      double cx = 0.0, cy = 0.0, sig = 0.0;
+      if (q0 == 0) {
+        if (on) {
+          code = S.code[lane];
+          cx = S.cx[lane];
+          cy = S.cy[lane];
+          sig = S.sig[lane];
+        }
+      } else {
+        code = on ? p.lig_flag[L.lig_base + q0 + lane] : 0;
+        const int g = L.lig_base + (code >> 1);
+        const int va = p.lig_va[g], vb = p.lig_vb[g];
+        cx = 0.5 * (p.xn[va] + p.xn[vb]);
+        cy = 0.5 * (p.yn[va] + p.yn[vb]);
+        sig = p.lig_sigma[g];
+      }
       const int l = code >> 1, wall = code & 1;
       const int gl = L.lig_base + l;
-      const int va = p.lig_va[gl], vb = p.lig_vb[gl];
-      const double cx = 0.5 * (p.xn[va] + p.xn[vb]);
-      const double cy = 0.5 * (p.yn[va] + p.yn[vb]);
       const int nr = wall == 0 ? L.n_rec0 : L.n_rec1;
       const int roff = wall == 0 ? 0 : L.n_rec0;
       const double* xs = p.rec_x + L.rec_base + roff;
       const int* taken = p.r2l + L.rec_base + roff;
       const double cxw = wrap_x(cx, nx);
       const bool can = on && nr > 0;
-      const double sig = p.lig_sigma[gl], sts = L.sigma_ts_frac * sig;
+      const double sts = L.sigma_ts_frac * sig;
       const int lo = can ? first_not_left(xs, nr, cxw, nx) : 0;
       const double u = philox_uniform(L.seed, n, l, 0, L.instance);
       int best = -1;
@@ -616,24 +674,27 @@ __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L
       auto choose = [&] {
         // merge the rightward and leftward sequences by their own distances;
         // each receptor is met first at its minimum-image distance
-        int ir = lo % nr, il = (lo - 1 + nr) % nr;
+        int ir = lo == nr ? 0 : lo, il = lo == 0 ? nr - 1 : lo - 1;
         best = -1;
+        double xb = 0.0;
         for (int it = 0; it < 2 * nr && best < 0; ++it) {
-          double dr = xs[ir] - cxw;
+          const double xr = xs[ir], xl = xs[il];
+          const int tr = taken[ir], tl = taken[il];
+          double dr = xr - cxw;
           if (dr < 0) dr += nx;
-          double dl = cxw - xs[il];
+          double dl = cxw - xl;
           if (dl < 0) dl += nx;
           // oracle's minimum image: equal to the smaller of the two one-sided
           // distances; ties between the two sides go to the lower index
           const bool take_r = dr < dl || (dr == dl && ir <= il);
-          const int cand = take_r ? ir : il;
-          if (taken[cand] < 0) best = cand;
+          xb = take_r ? xr : xl;
+          if ((take_r ? tr : tl) < 0) best = take_r ? ir : il;
           else if (take_r) ir = ir + 1 == nr ? 0 : ir + 1;
           else il = il == 0 ? nr - 1 : il - 1;
         }
         forms = tie = false;
         if (best < 0) return;
-        const double yl = bond_len(cx, cy, xs[best], wall, L);
+        const double yl = bond_len(cx, cy, xb, wall, L);
         dy = yl - L.y_eq;
         const double kf = L.kf0_dt * exp(-sts * dy * dy / (2.0 * L.kbt));
         const double P = 1.0 - exp(-kf);
@@ -662,36 +723,31 @@ __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L
 }
 
 // Step bookkeeping and bond kinetics of one lattice instance (the first
-// workgroups of the body kernel).  Ends by raising the instance's flag that
-// particle workgroups wait for before they read the bond table.
+// workgroups of the body kernel).  Raises the instance's flag that particle
+// workgroups wait for before they read the bond table.
 template <typename T>
-__device__ __forceinline__ void bonds_impl(const Ptrs<T>& p, int inst, int* s_tmp, int* s_nelig_p) {
-  int& s_nelig = *s_nelig_p;
-  const LatDev L = p.lat[inst];
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const long long n = p.step_next[inst];
+__device__ __forceinline__ void bonds_impl(const Ptrs<T>& p, int inst, BondLds& S) {
+  const LatDev L = load_uniform(p.lat + inst);
+  const long long n = load_uniform(p.step_next + inst);
+  const int tid = threadIdx.x;
+  bonds_kinetics(p, L, inst, n, L.nx, L.ny, S);
+  // publish: the barrier orders every lane's writes before thread 0's
+  // release store of the flag (one write-back of the cache, not one per lane)
   __syncthreads();
   if (tid == 0) {
     p.step_cur[inst] = n;
     p.step_next[inst] = n + 1;
+    __hip_atomic_store(&p.bond_flag[inst], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (inst == 0 && tid == 0) {
+  if (inst == 0) {
     // the other slot was last used by the previous step, whose kernels have
     // all finished: clear it for the next step
-    for (int i = 0; i < p.ninst; ++i) {
+    for (int i = tid; i < p.ninst; i += kBodyThreads) {
       p.fmax_next[i] = 0ull;
       p.bond_flag_next[i] = 0;
     }
   }
-  const int ny = L.ny, nx = L.nx;
-  bonds_kinetics(p, L, inst, n, nx, ny, s_tmp, s_nelig);
-  // publish: the barrier orders every lane's writes before thread 0's
-  // release store of the flag (one write-back of the cache, not one per lane)
-  __syncthreads();
-  if (tid == 0) __hip_atomic_store(&p.bond_flag[inst], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-
 
 // ---------------------------------------------------------------- star field
 // Node box of a set of positions: floor of the smallest and ceiling of the
@@ -776,10 +832,6 @@ __device__ __forceinline__ void star_pass(const Ptrs<T>& p, const T* src, int sc
 }
 
 // ---------------------------------------------------------------- k_body
-constexpr int kBodyThreads = 256;
-constexpr int kWaves = kBodyThreads / 64;
-// the wave's number in its workgroup, in a scalar register
-__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 constexpr int kSpinMax = 1 << 22;   // bounded wait for the bond flag (~0.2 s)
 
 // max that propagates NaN (fmax drops it)
@@ -1017,19 +1069,18 @@ __device__ __forceinline__ void rigid_vertex(double rx, double ry, const double 
 // and the fluid velocity at its vertices, and the chunk that arrives last
 // (a counter per body) takes the rigid step and moves every vertex.
 template <typename T, bool MLS>
-__device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, int code, int b, double (*s_rp)[kWaves]) {
+__device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl, double (*s_rp)[kWaves]) {
   const int lane = threadIdx.x & 63;
-  // code: the chunk of body b, or -2 for an idle wave in the workgroup of a
-  // rigid body whose chunks share this workgroup (it takes part in the sums)
-  const bool idle = code < 0;
-  const int chunk = idle ? -1 : code;
-  // the body record in registers, read before any store (the rigid step
-  // writes the record back through Bp)
+  // the slot alone gives the wave its vertices; the body record (in registers,
+  // read before any store: the rigid step writes it back through Bp) is in
+  // flight with them
+  const bool idle = sl.chunk < 0;   // of a rigid body's workgroup: takes part in the sums
+  const int chunk = idle ? -1 : sl.chunk, b = sl.body;
+  const int kind = sl.kind_inst & 3, inst = sl.kind_inst >> 2, nv = sl.nv, v0 = sl.v0, ch0 = sl.chunk0;
   BodyDev* Bp = p.body + b;
   const BodyDev B = *Bp;
-  const int kind = B.kind, nv = B.nv, v0 = B.v0, inst = B.inst, ch0 = B.chunk0;
   const int nch = chunks_of(nv);
-  const int first_v = idle ? 0 : (chunk - ch0) * kChunk, cnt = idle ? 0 : min(kChunk, nv - first_v);
+  const int first_v = idle ? 0 : sl.first, cnt = idle ? 0 : min(kChunk, nv - first_v);
   const int v = chunk_vertex(lane, first_v, nv), gm = v0 + v;
   const bool inner = lane >= 2 && lane < 2 + cnt;     // the chunk's own vertices
   const bool has_elem = lane >= 1 && lane < 2 + cnt;  // elements v -> v+1 they touch
@@ -1046,11 +1097,15 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, int code, int b, do
   // the ligand of element v and its bond table entry as this wave finds it:
   // the bond workgroup rewrites the table while the wave runs (see below)
   const int ls = particle ? B.lig_stride : 0;
-  const bool lig = has_elem && ls > 0 && v % ls == 0;
-  const int gl = lig ? B.lig_base + v / ls : 0;
+  int vq = 0, vr = 1;   // v / ls and its remainder (usually every or every other element)
+  if (ls > 0) {
+    vq = (ls & (ls - 1)) == 0 ? v >> __builtin_ctz(ls) : v / ls;
+    vr = v - vq * ls;
+  }
+  const bool lig = has_elem && vr == 0;
+  const int gl = lig ? B.lig_base + vq : 0;
   const int r_seen = lig ? __hip_atomic_load(&p.l2r[gl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
-  double area = 0.0;
-  if (!rigid) area = body_area2(p.area_part, p.nchunk_total, ch0, nch) * 0.5;
+  const double area_t = rigid ? 0.0 : area_term(p.area_part, p.nchunk_total, ch0, nch, lane);
 
   // element v -> v+1 and the bending at v
   const double Xp = lane_next(X), Yp = lane_next(Y);
@@ -1110,7 +1165,11 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, int code, int b, do
     }
   }
   const bool first = rigid && B.stepped == 0;
-  const double ca = rigid ? 0.0 : B.ka * (1.0 - area / B.A0) * B.p_ref * len;
+  double ca = 0.0;
+  if (!rigid) {
+    const double area = body_area2(p.area_part, p.nchunk_total, ch0, nch, area_t) * 0.5;
+    ca = B.ka * (1.0 - area / B.A0) * B.p_ref * len;
+  }
   double fex, fey;
   element_load(!rigid, ca, spring_on, sp, particle, pfx, pfy, enx, eny, fex, fey);
   const double len_m = lane_prev(len);
@@ -1124,21 +1183,23 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, int code, int b, do
       rigid_terms(fex, fey, cx - xc0, cy - yc0, rep, -sv * bnx, -sv * bny, X - xc0, Y - yc0, t3);
       if (rep) p.frep[gm] = 0.0;   // applied: the next step's repulsion kernel rewrites it
     }
-    double s3[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) s3[k] = wave_sum(t3[k]);
+    double s3[3] = {t3[0], t3[1], t3[2]};
+    wave_sum3(s3);
     double st[6], xn = 0.0, yn = 0.0, fx, fy;
     if (rigid_grouped(kind, nv)) {
       // the body's chunks are the waves of this workgroup, chunk c on wave c
-      const int w = threadIdx.x >> 6;
-      if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) s_rp[k][w] = s3[k];
-      }
+      if (lane < 3) s_rp[lane][wave_id()] = lane == 0 ? s3[0] : (lane == 1 ? s3[1] : s3[2]);
       __syncthreads();
       double r3[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) r3[k] = chunk_total(s_rp[k], nch);
+      for (int k = 0; k < 3; ++k) {   // in chunk order, as chunk_total
+        double q[kGroupChunks], s = 0.0;
+#pragma unroll
+        for (int c = 0; c < kGroupChunks; ++c) q[c] = s_rp[k][c];
+#pragma unroll
+        for (int c = 0; c < kGroupChunks; ++c) s = c < nch ? s + q[c] : s;
+        r3[k] = s;
+      }
       rigid_step(&B, first, r3, st);
       __syncthreads();   // every wave has read the rigid state
       if (threadIdx.x == 0) rigid_commit(Bp, st);
@@ -1285,17 +1346,18 @@ __device__ __forceinline__ void clear_bins(const Ptrs<T>& p) {
 template <typename T, bool MLS>
 __global__ __launch_bounds__(kBodyThreads) void k_body_chunks(Ptrs<T>) {
   const Ptrs<T>& p = launch_args<T>();
-  __shared__ int s_tmp[kBodyThreads];
-  __shared__ int s_nelig;
+  __shared__ BondLds s_bond;
   __shared__ double s_rp[3][kWaves];
   if ((int)blockIdx.x < p.ninst) {
-    bonds_impl(p, blockIdx.x, s_tmp, &s_nelig);
+    bonds_impl(p, blockIdx.x, s_bond);
     clear_bins(p);
     return;
   }
   const int slot = (blockIdx.x - p.ninst) * kWaves + wave_id();
-  const int2 sc = slot < p.nslot ? load_uniform(p.slot_chunk + slot) : make_int2(-1, 0);
-  if (sc.x != -1) chunk_impl<T, MLS>(p, sc.x, sc.y, s_rp);
+  if (slot < p.nslot) {
+    const ChunkSlot sl = load_uniform(p.slot_chunk + slot);
+    if (sl.chunk != -1) chunk_impl<T, MLS>(p, sl, s_rp);
+  }
   clear_bins(p);
 }
 

@@ -170,6 +170,18 @@ struct BodyDev {
   double Om, Omm;           // rigid: angular velocity history
 };
 
+// What a wave of the body kernel takes, in one 32-byte load: chunk -1: none;
+// -2: an idle wave in the workgroup of a rigid body whose chunks, at most four,
+// share one workgroup so that its force and torque are summed in LDS.
+struct ChunkSlot {
+  int chunk, body;
+  int v0, nv;            // the body's first vertex and vertex count
+  int first;             // the chunk's first vertex within the body
+  int kind_inst;         // kind | instance << 2
+  int chunk0;            // the body's first chunk
+  int pad_;
+};
+
 // Device pointers into the workspace.
 // Velocity walls on the node rows 0 and ny - 1 (Zou and He; the paper's wall
 // condition, Sec. 2.1): the populations of a wall node whose source lies
@@ -250,11 +262,8 @@ struct Ptrs {
   const int4* chunk_info;             // per chunk: body, global index of its first
                                       // vertex minus 2 (the marker of lane 0),
                                       // vertex count, kind | instance << 2
-  // waves of the chunked body kernel: (chunk, body) each one takes (chunk
-  // -1: none; -2: an idle wave in the workgroup of a rigid body whose
-  // chunks, at most four, share one workgroup so that its force and torque
-  // are summed in LDS)
-  const int2* slot_chunk;
+  // waves of the chunked body kernel: the chunk and body each one takes
+  const ChunkSlot* slot_chunk;
   int nslot;
   double* area_part;                  // per chunk [5][nchunk]: shoelace sum over its interior
                                       // edges, its first vertex (x, y), its last vertex (x, y)
@@ -391,6 +400,22 @@ __device__ __forceinline__ double wave_sum(double x) {
   return (readlane_d(x, 0) + readlane_d(x, 16)) + (readlane_d(x, 32) + readlane_d(x, 48));
 }
 
+// wave_sum of three values, stage by stage: the moves and adds of one value
+// fill the wait states of the others.
+__device__ __forceinline__ void wave_sum3(double x[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] += dpp_d<kDppRowRor8>(x[k]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] += dpp_d<kDppRowRor4>(x[k]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] += dpp_d<kDppRowRor2>(x[k]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] += dpp_d<kDppRowRor1>(x[k]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    x[k] = (readlane_d(x[k], 0) + readlane_d(x[k], 16)) + (readlane_d(x[k], 32) + readlane_d(x[k], 48));
+}
+
 // Reduction over the 64 lanes with an associative, commutative operation
 // that rounds nothing (min, max), every lane getting the result.
 template <typename Op>
@@ -443,19 +468,19 @@ __device__ __forceinline__ double shoelace_term(double x0, double y0, double x1,
 // from its last vertex to the first vertex of chunk k + 1 (cyclically),
 // T_k = P_k + shoelace(last_k, first_k+1), and the T_k are added in chunk
 // order.  A chunk's record never needs a vertex another wave moves.
-__device__ __forceinline__ double body_area2(const double* rec, int nct, int ch0, int nch) {
+// The terms of the first 64 chunks (lane k holds T_k) can be taken ahead of
+// their sum, so that their loads are in flight during other work.
+__device__ __forceinline__ double area_term(const double* rec, int nct, int ch0, int nch, int k) {
+  if (k >= nch) return 0.0;
+  const int kn = k + 1 == nch ? 0 : k + 1;
+  return rec[ch0 + k] + shoelace_term(rec[3 * nct + ch0 + k], rec[4 * nct + ch0 + k],
+                                      rec[nct + ch0 + kn], rec[2 * nct + ch0 + kn]);
+}
+__device__ __forceinline__ double body_area2(const double* rec, int nct, int ch0, int nch, double t0) {
   const int lane = threadIdx.x & 63;
-  double s = 0.0;
-  for (int k0 = 0; k0 < nch; k0 += 64) {
-    const int k = k0 + lane;
-    double tk = 0.0;
-    if (k < nch) {
-      const int kn = k + 1 == nch ? 0 : k + 1;
-      tk = rec[ch0 + k] + shoelace_term(rec[3 * nct + ch0 + k], rec[4 * nct + ch0 + k],
-                                        rec[nct + ch0 + kn], rec[2 * nct + ch0 + kn]);
-    }
-    s = ordered_lane_sum(s, tk, nch - k0 < 64 ? nch - k0 : 64);
-  }
+  double s = ordered_lane_sum(0.0, t0, nch < 64 ? nch : 64);
+  for (int k0 = 64; k0 < nch; k0 += 64)
+    s = ordered_lane_sum(s, area_term(rec, nct, ch0, nch, k0 + lane), nch - k0 < 64 ? nch - k0 : 64);
   return s;
 }
 
