@@ -80,7 +80,7 @@ struct lbib_ctx {
   int ninst = 0, nm = 0, nbody = 0, nlig = 0, nrec = 0, ntiles = 0;
   int nchunk = 0;              // vertex chunks of all bodies (kChunk vertices each)
   int nstar_wg = 0;            // workgroups of the star pass (particle node boxes)
-  int nslot = 0;               // waves of the chunked body kernel (a multiple of 4)
+  std::vector<ChunkSlot> slots; // waves of the chunked body kernel (whole workgroups)
   long long nodes = 0;
   std::vector<int> marker_base, body_base, lig_base, rec_base, tile_base;
   std::vector<long long> node_base;
@@ -266,12 +266,57 @@ int star_workgroups(const BodyHost& b) {
   return std::max(1, (int)std::ceil(nodes / kStarNodes));
 }
 
+// The waves of the chunked body kernel, whole workgroups.  Rigid bodies of at
+// most kGroupChunks chunks come first, each whole in one workgroup; then the
+// chunks of the other particles, then those of the red cells (the particles'
+// chains are the longer ones: they start first).  Fewer chunks per workgroup
+// gain nothing, even where the chip has room (132 chunks: 6.9 us with four or
+// with one).
+void pack_slots(lbib_ctx* c) {
+  c->slots.clear();
+  std::vector<ChunkSlot> wg;
+  const ChunkSlot none{-1, 0, 0, 0, 0, 0, 0, 0};
+  for (int pass = 0; pass < 3; ++pass) {
+    const int fill = pass == 2 ? kBodyWaves : kGroupChunks, barriers = 2 - pass;
+    auto flush = [&] {
+      const int n = (int)wg.size();
+      if (n == 0) return;
+      for (int k = 0; pass < 2 && k < n; ++k) {
+        wg.push_back(wg[k]);
+        wg.back().role = (1 + k) << 2;
+      }
+      wg.resize(kBodyWaves, none);
+      for (ChunkSlot& q : wg) q.role |= barriers;
+      c->slots.insert(c->slots.end(), wg.begin(), wg.end());
+      wg.clear();
+    };
+    int body = 0, v0 = 0, chunk0 = 0, inst = 0;
+    for (auto& I : c->inst) {
+      for (auto& b : I.bodies) {
+        const int kind = b.d.kind, nv = b.d.nv, nch = chunks_of(nv);
+        const int of = rigid_grouped(kind, nv) ? 0 : (kind == LBIB_RBC_KINEMATIC ? 2 : 1);
+        if (of == pass) {
+          if (pass == 0 && (int)wg.size() + nch > fill) flush();
+          for (int k = 0; k < nch; ++k) {
+            wg.push_back({chunk0 + k, body, v0, nv, k * kChunk, kind | (inst << 2), chunk0, 0});
+            if (pass > 0 && (int)wg.size() == fill) flush();
+          }
+        }
+        ++body;
+        v0 += nv;
+        chunk0 += nch;
+      }
+      ++inst;
+    }
+    flush();
+  }
+}
+
 void compute_sizes(lbib_ctx* c) {
   c->ninst = (int)c->inst.size();
   c->nm = c->nbody = c->nlig = c->nrec = c->ntiles = 0;
   c->nchunk = 0;
   c->nstar_wg = 0;
-  int grouped = 0, grouped_chunks = 0;
   c->nrep_chunk = 0;
   c->nodes = 0;
   c->marker_base.clear(); c->body_base.clear(); c->lig_base.clear();
@@ -289,10 +334,6 @@ void compute_sizes(lbib_ctx* c) {
       c->nrep_chunk += (b.d.nv + kRepChunk - 1) / kRepChunk;
       c->nchunk += chunks_of(b.d.nv);
       c->nstar_wg += star_workgroups(b);
-      if (rigid_grouped(b.d.kind, b.d.nv)) {
-        ++grouped;
-        grouped_chunks += chunks_of(b.d.nv);
-      }
       if (b.d.ligand_stride > 0) c->nlig += (b.d.nv + b.d.ligand_stride - 1) / b.d.ligand_stride;
     }
     c->nrec += (int)(I.rec[0].size() + I.rec[1].size());
@@ -300,8 +341,7 @@ void compute_sizes(lbib_ctx* c) {
     c->ntiles += ntx * nty;
     c->nodes += (long long)row_pitch(I.lat.nx) * I.lat.ny;   // padded rows
   }
-  const int packed = c->nchunk - grouped_chunks;
-  c->nslot = (packed + kGroupChunks - 1) / kGroupChunks * kGroupChunks + kGroupChunks * grouped;
+  pack_slots(c);
 }
 
 void compute_layout(lbib_ctx* c) {
@@ -365,7 +405,7 @@ void compute_layout(lbib_ctx* c) {
   L.star = take(es * 4 * (size_t)c->nodes);
   L.pbox = take(4 * 4 * nch);
   L.star_wg = take(4 * 3 * (size_t)std::max(c->nstar_wg, 1));
-  L.slot_chunk = take(sizeof(ChunkSlot) * (size_t)std::max(c->nslot, 1));
+  L.slot_chunk = take(sizeof(ChunkSlot) * std::max<size_t>(c->slots.size(), 1));
   L.total = cur;
 }
 
@@ -442,7 +482,7 @@ Ptrs<T> make_ptrs(const lbib_ctx* c) {
   p.star_wg = (const int*)(w + L.star_wg);
   p.nstar_wg = c->nstar_wg;
   p.slot_chunk = (const ChunkSlot*)(w + L.slot_chunk);
-  p.nslot = c->nslot;
+  p.nslot = (int)c->slots.size();
   p.nm_total = c->nm;
   p.nbody_total = c->nbody;
   p.ntile_total = c->ntiles;
@@ -703,29 +743,8 @@ lbib_status upload_all(lbib_ctx* c) {
       }
     if (!sw.empty()) HIPCHK(c, up(L.star_wg, sw.data(), 4 * sw.size()));
   }
-  {
-    // waves of the chunked body kernel: one workgroup per grouped rigid body
-    // first (chunk c on wave c, idle waves -2), then the chunks of the other
-    // particles and of the red cells, packed (the particles' chains are the
-    // longer ones: they start first)
-    std::vector<ChunkSlot> sl;
-    auto slot = [&](int bb, int k, bool idle) {
-      const BodyDev& B = bodies[bb];
-      sl.push_back({idle ? -2 : B.chunk0 + k, bb, B.v0, B.nv, k * kChunk, B.kind | (B.inst << 2), B.chunk0, 0});
-    };
-    for (int bb = 0; bb < c->nbody; ++bb)
-      if (rigid_grouped(bodies[bb].kind, bodies[bb].nv))
-        for (int k = 0; k < kGroupChunks; ++k) slot(bb, k, k >= chunks_of(bodies[bb].nv));
-    for (int pass = 0; pass < 2; ++pass)
-      for (int bb = 0; bb < c->nbody; ++bb) {
-        const bool rbc = bodies[bb].kind == LBIB_RBC_KINEMATIC;
-        if (rigid_grouped(bodies[bb].kind, bodies[bb].nv) || rbc != (pass == 1)) continue;
-        for (int k = 0; k < chunks_of(bodies[bb].nv); ++k) slot(bb, k, false);
-      }
-    while (sl.size() % kGroupChunks) sl.push_back({-1, 0, 0, 0, 0, 0, 0, 0});
-    if ((int)sl.size() != c->nslot) return fail(c, LBIB_EINVAL, "internal: wave slot count");
-    if (!sl.empty()) HIPCHK(c, up(L.slot_chunk, sl.data(), sizeof(ChunkSlot) * sl.size()));
-  }
+  if (!c->slots.empty())
+    HIPCHK(c, up(L.slot_chunk, c->slots.data(), sizeof(ChunkSlot) * c->slots.size()));
   HIPCHK(c, up(L.tile_inst, tile_inst.data(), 4 * tile_inst.size()));
   HIPCHK(c, up(L.lig_body, lig_body.data(), 4 * lig_body.size()));
   HIPCHK(c, up(L.lig_elem, lig_elem.data(), 4 * lig_elem.size()));

@@ -487,17 +487,16 @@ __device__ __forceinline__ int first_not_left(const double* xs, int n, double x,
   return lo;
 }
 
-constexpr int kBodyThreads = 256;
-constexpr int kWaves = kBodyThreads / 64;
+constexpr int kBodyThreads = 64 * kBodyWaves;
 // the wave's number in its workgroup, in a scalar register
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
-constexpr int kLigRanks = 4;   // ligands per lane and pass of the bond kinetics
+constexpr int kLigRanks = 2;   // ligands per lane and pass of the bond kinetics
 
 // What the bond workgroup holds in LDS: the eligible ligands per wave and
 // rank (two sets, used by alternate passes), and the first 64 eligible ones.
 struct BondLds {
-  int cnt[2][kLigRanks][kWaves];
+  int cnt[2][kLigRanks][kBodyWaves];
   int code[64];                  // ligand << 1 | wall
   double cx[64], cy[64], sig[64];
 };
@@ -511,7 +510,7 @@ struct BondLds {
 template <typename T>
 __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L, int inst, long long n,
                                                int nx, int ny, BondLds& S) {
-  constexpr int R = kLigRanks, nt = kBodyThreads, nw = kWaves;
+  constexpr int R = kLigRanks, nt = kBodyThreads, nw = kBodyWaves;
   const int tid = threadIdx.x;
   // bond kinetics (Sec. 2.2): rupture then formation (a frozen topology
   // skips both); then every bond's spring coefficient sigma (y_l - y_eq)
@@ -594,7 +593,7 @@ __device__ __forceinline__ void bonds_kinetics(const Ptrs<T>& p, const LatDev& L
     // the earlier ligand ranges and waves.  The next pass writes the other
     // set of counts: a set is written again only after the barrier that
     // follows its last reading.
-    int(*cnt)[kWaves] = S.cnt[odd];
+    int(*cnt)[kBodyWaves] = S.cnt[odd];
     unsigned long long bal[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -1068,19 +1067,46 @@ __device__ __forceinline__ void rigid_vertex(double rx, double ry, const double 
 // force and torque need all its chunks: each chunk stores its partial sums
 // and the fluid velocity at its vertices, and the chunk that arrives last
 // (a counter per body) takes the rigid step and moves every vertex.
+//
+// Bound by the chain of instructions of one wave (a lone wave issues one every
+// 4 to 10 cycles).  A particle's chunk needs the fluid at two points per vertex,
+// the probe of its element and the vertex itself: a second wave takes the
+// vertices and hands u* over in LDS, while the first takes the probes.  (Body
+// kernel of a 1237x149 run with moving least squares 8.7 us, 11.5 with one wave
+// for both; of a 2000x200 capillary 6.9, 7.2; of 96 lattices with 1150 particle
+// chunks 14.4, 16.3.)
+struct BodyLds {
+  double rp[3][kGroupChunks];       // a rigid body's sums, per chunk
+  double uv[2][kGroupChunks][64];   // u* at the vertices of each chunk's lanes
+};
+
+// u* at the vertices of a chunk, for wave w of the workgroup.
 template <typename T, bool MLS>
-__device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl, double (*s_rp)[kWaves]) {
+__device__ __forceinline__ void sample_vertices(const Ptrs<T>& p, const ChunkSlot& sl, int w, BodyLds& S) {
+  const int lane = threadIdx.x & 63;
+  const int gm = sl.v0 + chunk_vertex(lane, sl.first, sl.nv);
+  const double X = p.x[gm], Y = p.y[gm];
+  const LatDev L = load_uniform(p.lat + (sl.kind_inst >> 2));
+  Star9<T> n;
+  star_load(p.star + 4 * L.node_base, L, X, Y, n);
+  double rho, ux, uy, g[4];
+  star_sum<MLS, false>(L, X, Y, n, rho, ux, uy, g);
+  S.uv[0][w][lane] = ux;
+  S.uv[1][w][lane] = uy;
+}
+
+template <typename T, bool MLS>
+__device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl, BodyLds& lds) {
   const int lane = threadIdx.x & 63;
   // the slot alone gives the wave its vertices; the body record (in registers,
   // read before any store: the rigid step writes it back through Bp) is in
   // flight with them
-  const bool idle = sl.chunk < 0;   // of a rigid body's workgroup: takes part in the sums
-  const int chunk = idle ? -1 : sl.chunk, b = sl.body;
+  const int chunk = sl.chunk, b = sl.body;
   const int kind = sl.kind_inst & 3, inst = sl.kind_inst >> 2, nv = sl.nv, v0 = sl.v0, ch0 = sl.chunk0;
   BodyDev* Bp = p.body + b;
   const BodyDev B = *Bp;
   const int nch = chunks_of(nv);
-  const int first_v = idle ? 0 : sl.first, cnt = idle ? 0 : min(kChunk, nv - first_v);
+  const int first_v = sl.first, cnt = min(kChunk, nv - first_v);
   const int v = chunk_vertex(lane, first_v, nv), gm = v0 + v;
   const bool inner = lane >= 2 && lane < 2 + cnt;     // the chunk's own vertices
   const bool has_elem = lane >= 1 && lane < 2 + cnt;  // elements v -> v+1 they touch
@@ -1118,30 +1144,33 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl
   if (bend || rep) vertex_normal(txl, tyl, tx, ty, bnx, bny);
   if (bend) bc = bend_coeff(txl, tyl, tx, ty, B.kb, th0v);
 
-  // particles: probe load of the element and fluid velocity u* at the vertex,
-  // from the star field of the particle's box
+  // particles: probe load of the element, from the star field of the
+  // particle's box
   const double cx = 0.5 * (X + Xp), cy = 0.5 * (Y + Yp);
   double pfx = 0.0, pfy = 0.0, uvx = 0.0, uvy = 0.0;
+  const bool grouped = rigid_grouped(kind, nv);
   if (particle) {
     const double nu = (L.tau - 0.5) / 3.0;
-    // the probe of element v (lanes without an element probe at the vertex:
-    // always a point of the box) and the vertex itself: both points' loads
-    // are issued before either sum
+    // lanes without an element probe at the vertex: always a point of the box
     double qx = X, qy = Y;
     if (has_elem) probe_point(L, cx, cy, enx, eny, qx, qy);
-    Star9<T> nq, nv;
+    Star9<T> nq;
     star_load(S, L, qx, qy, nq);
-    star_load(S, L, X, Y, nv);
-    // the vertex first: its sum needs fewer registers beside the other
-    // point's nodes
     double rho, ux, uy, g[4];
-    star_sum<MLS, false>(L, X, Y, nv, rho, ux, uy, g);
-    if (inner) {
-      uvx = ux;
-      uvy = uy;
-    }
     star_sum<MLS, true>(L, qx, qy, nq, rho, ux, uy, g);
     if (has_elem) probe_load(rho, g, nu, enx, eny, len, pfx, pfy);
+  }
+  // u* at the vertices, from the sampling wave; a grouped rigid body takes it
+  // over at the barrier of its sums
+  auto take_samples = [&] {
+    if (inner) {
+      uvx = lds.uv[0][wave_id()][lane];
+      uvy = lds.uv[1][wave_id()][lane];
+    }
+  };
+  if (particle && !grouped) {
+    __syncthreads();
+    take_samples();
   }
   // adhesion springs on bonded ligand elements (after this step's bond
   // update).  A ligand element whose centroid lies farther than y_cr from
@@ -1186,23 +1215,26 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl
     double s3[3] = {t3[0], t3[1], t3[2]};
     wave_sum3(s3);
     double st[6], xn = 0.0, yn = 0.0, fx, fy;
-    if (rigid_grouped(kind, nv)) {
-      // the body's chunks are the waves of this workgroup, chunk c on wave c
-      if (lane < 3) s_rp[lane][wave_id()] = lane == 0 ? s3[0] : (lane == 1 ? s3[1] : s3[2]);
+    if (grouped) {
+      // the body's chunks are on neighbouring waves of this workgroup, the
+      // first on wave w0
+      const int w0 = wave_id() - (chunk - ch0);
+      if (lane < 3) lds.rp[lane][wave_id()] = lane == 0 ? s3[0] : (lane == 1 ? s3[1] : s3[2]);
       __syncthreads();
       double r3[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {   // in chunk order, as chunk_total
         double q[kGroupChunks], s = 0.0;
 #pragma unroll
-        for (int c = 0; c < kGroupChunks; ++c) q[c] = s_rp[k][c];
+        for (int c = 0; c < kGroupChunks; ++c) q[c] = lds.rp[k][min(w0 + c, kGroupChunks - 1)];
 #pragma unroll
         for (int c = 0; c < kGroupChunks; ++c) s = c < nch ? s + q[c] : s;
         r3[k] = s;
       }
+      take_samples();
       rigid_step(&B, first, r3, st);
       __syncthreads();   // every wave has read the rigid state
-      if (threadIdx.x == 0) rigid_commit(Bp, st);
+      if (lane == 0 && chunk == ch0) rigid_commit(Bp, st);
       double sn, cs;
       sincos(st[5], &sn, &cs);
       if (inner) {
@@ -1214,7 +1246,7 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl
         fm = fmax_nan(fabs(fx), fabs(fy));
       }
       const IBox q = wave_box(xn, yn, inner);
-      if (lane == 0 && !idle) put_box(p.pbox, chunk, q);
+      if (lane == 0) put_box(p.pbox, chunk, q);
     } else {
       // a larger rigid body: its chunks' partial sums meet in memory, and
       // the chunk that arrives last takes the rigid step for all vertices
@@ -1341,27 +1373,37 @@ __device__ __forceinline__ void clear_bins(const Ptrs<T>& p) {
     p.cnt_next[t] = 0;
 }
 
-// Workgroups [0, ninst) run the bond kinetics of each instance; then one wave
-// per vertex chunk of every body.
+// Workgroups [0, ninst) run the bond kinetics of each instance; then the waves
+// of the slot list.
 template <typename T, bool MLS>
 __global__ __launch_bounds__(kBodyThreads) void k_body_chunks(Ptrs<T>) {
   const Ptrs<T>& p = launch_args<T>();
-  __shared__ BondLds s_bond;
-  __shared__ double s_rp[3][kWaves];
+  __shared__ union {
+    BondLds bond;
+    BodyLds body;
+  } lds;
   if ((int)blockIdx.x < p.ninst) {
-    bonds_impl(p, blockIdx.x, s_bond);
+    bonds_impl(p, blockIdx.x, lds.bond);
     clear_bins(p);
     return;
   }
-  const int slot = (blockIdx.x - p.ninst) * kWaves + wave_id();
-  if (slot < p.nslot) {
+  const int slot = (blockIdx.x - p.ninst) * kBodyWaves + wave_id();
+  if (slot < p.nslot) {   // nslot holds whole workgroups
     const ChunkSlot sl = load_uniform(p.slot_chunk + slot);
-    if (sl.chunk != -1) chunk_impl<T, MLS>(p, sl, s_rp);
+    const int w = (sl.role >> 2) - 1;
+    if (sl.chunk == -1 || w >= 0) {
+      // no chunk of its own: the barriers of the waves that have one
+      if (w >= 0) sample_vertices<T, MLS>(p, sl, w, lds.body);
+      for (int k = sl.role & 3; k > 0; --k) __syncthreads();
+    } else {
+      chunk_impl<T, MLS>(p, sl, lds.body);
+    }
   }
   clear_bins(p);
 }
 
 // ---------------------------------------------------------------- advance and stencil passes
+constexpr int kAdvWaves = 4;   // chunks per workgroup
 // Bound by the chain of one wave: its records, its vertices, the velocities
 // the lattice kernel left on other XCDs, then about 600 instructions at the
 // 4 to 10 cycles each that a wave alone on its SIMD issues at.  Measured (us,
@@ -1380,7 +1422,7 @@ __global__ __launch_bounds__(kBodyThreads) void k_body_chunks(Ptrs<T>) {
 template <typename T, int TX, int TY, bool MLS, bool ADVANCE>
 __device__ __forceinline__ void advance_chunk(const Ptrs<T>& p, int* cnt, int* bin) {
   const int lane = threadIdx.x & 63;
-  const int chunk = blockIdx.x * kWaves + wave_id();
+  const int chunk = blockIdx.x * kAdvWaves + wave_id();
   if (chunk >= p.nchunk_total) return;   // the whole wave
   // one load gives the wave its vertices (the body record is not needed)
   const int4 ci = load_uniform(p.chunk_info + chunk);
@@ -1441,7 +1483,7 @@ __device__ __forceinline__ void advance_chunk(const Ptrs<T>& p, int* cnt, int* b
   bins_commit(bin, p.bin_cap, p.overflow, gm, S);
 }
 
-inline __host__ __device__ int chunk_blocks(int nchunk) { return (nchunk + kWaves - 1) / kWaves; }
+inline __host__ __device__ int chunk_blocks(int nchunk) { return (nchunk + kAdvWaves - 1) / kAdvWaves; }
 
 // Marker advance, new stencils, bins and area records (kernel weights only,
 // or with the MLS transfer compiled in, launched when an instance uses it);
@@ -1503,7 +1545,7 @@ void launch_stencil(const Ptrs<T>& p, const StepArgs& a, hipStream_t s) {
 
 template <typename T>
 void launch_lagrangian(const Ptrs<T>& p, const StepArgs& a, hipStream_t s) {
-  const dim3 grid(p.ninst + (unsigned)(p.nslot / kWaves)), block(kBodyThreads);
+  const dim3 grid(p.ninst + (unsigned)(p.nslot / kBodyWaves)), block(kBodyThreads);
   if (a.any_mls) hipLaunchKernelGGL((k_body_chunks<T, true>), grid, block, 0, s, p);
   else hipLaunchKernelGGL((k_body_chunks<T, false>), grid, block, 0, s, p);
 }

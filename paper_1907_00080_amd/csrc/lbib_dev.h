@@ -170,16 +170,16 @@ struct BodyDev {
   double Om, Omm;           // rigid: angular velocity history
 };
 
-// What a wave of the body kernel takes, in one 32-byte load: chunk -1: none;
-// -2: an idle wave in the workgroup of a rigid body whose chunks, at most four,
-// share one workgroup so that its force and torque are summed in LDS.
+// What a wave of the body kernel takes, in one 32-byte load.  The waves come in
+// workgroups of kBodyWaves: chunks of red cells, or chunks of particles on the
+// first waves and then, for each, a wave that samples the fluid at its vertices.
 struct ChunkSlot {
-  int chunk, body;
+  int chunk, body;       // chunk -1: none
   int v0, nv;            // the body's first vertex and vertex count
   int first;             // the chunk's first vertex within the body
   int kind_inst;         // kind | instance << 2
   int chunk0;            // the body's first chunk
-  int pad_;
+  int role;              // barriers of the workgroup | (1 + the wave sampled for) << 2
 };
 
 // Device pointers into the workspace.
@@ -309,8 +309,9 @@ __device__ __forceinline__ const A& launch_args2() {
 constexpr int kChunk = 60;
 constexpr int kStarNodes = 256;   // nodes of a particle's box per star-pass workgroup (one per lane)
 __host__ __device__ constexpr int chunks_of(int nv) { return (nv + kChunk - 1) / kChunk; }
-// rigid bodies of at most this many chunks (one per wave of a 256-lane
-// workgroup) are summed inside their workgroup
+// Waves per workgroup of the body kernel, and the particle chunks among them;
+// rigid bodies of at most kGroupChunks chunks are summed inside a workgroup.
+constexpr int kBodyWaves = 8;
 constexpr int kGroupChunks = 4;
 __host__ __device__ constexpr bool rigid_grouped(int kind, int nv) {
   return kind == kRigid && chunks_of(nv) <= kGroupChunks;
