@@ -285,8 +285,9 @@ void pack_slots(lbib_ctx* c) {
         wg.push_back(wg[k]);
         wg.back().role = (1 + k) << 2;
       }
+      const bool shared = pass == 2 && wg[0].kind_inst == wg[n - 1].kind_inst;   // in order of instances
       wg.resize(kBodyWaves, none);
-      for (ChunkSlot& q : wg) q.role |= barriers;
+      for (ChunkSlot& q : wg) q.role |= barriers | (shared ? n << 8 : 0);
       c->slots.insert(c->slots.end(), wg.begin(), wg.end());
       wg.clear();
     };

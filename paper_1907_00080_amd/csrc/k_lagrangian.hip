@@ -836,15 +836,6 @@ constexpr int kSpinMax = 1 << 22;   // bounded wait for the bond flag (~0.2 s)
 // max that propagates NaN (fmax drops it)
 __device__ __forceinline__ double fmax_nan(double a, double b) { return (a > b || a != a) ? a : b; }
 
-// Largest |F| the lanes of a wave hand to the fluid, folded into the
-// instance maximum (non-negative doubles order like their bit patterns; NaN
-// and Inf sort above every finite value, so a broken force shows up as a
-// non-finite maximum).
-__device__ __forceinline__ void record_fmax(unsigned long long* slot, double m) {
-  m = wave_reduce_d(m, [](double a, double b) { return fmax_nan(a, b); });
-  if ((threadIdx.x & 63) == 0 && m != 0.0) atomicMax(slot, (unsigned long long)__double_as_longlong(m));
-}
-
 // Particles read the bond table (and rigid ones the step counter) that this
 // instance's bond workgroup writes during the same launch: each wave waits
 // for its flag (bounded spin; the bond workgroups have the lowest ids, so
@@ -1074,11 +1065,34 @@ __device__ __forceinline__ void rigid_vertex(double rx, double ry, const double 
 // vertices and hands u* over in LDS, while the first takes the probes.  (Body
 // kernel of a 1237x149 run with moving least squares 8.7 us, 11.5 with one wave
 // for both; of a 2000x200 capillary 6.9, 7.2; of 96 lattices with 1150 particle
-// chunks 14.4, 16.3.)
+// chunks 14.2, 16.3.)
 struct BodyLds {
   double rp[3][kGroupChunks];       // a rigid body's sums, per chunk
   double uv[2][kGroupChunks][64];   // u* at the vertices of each chunk's lanes
+  unsigned long long fmax;          // largest |F| of the waves that have ended, as bits
+  int ended;
 };
+
+// Largest |F| a wave hands to the fluid (m: each lane's), folded into its
+// instance's maximum (non-negative doubles order like their bit patterns; NaN
+// and Inf sort above every finite value, so a broken force shows up as a
+// non-finite maximum).  Atomics on one instance's maximum are taken one after
+// the other, so where a workgroup holds n > 0 red-cell chunks of one instance its
+// last wave sends one for all (body kernel of 16 lattices with 990 chunks 8.5 us,
+// 10.5 with one per chunk; 6667x667 with 372 chunks 8.3, 9.5).  No wave waits for
+// another, as it would at a barrier: ended waves make room (96 lattices with 12
+// particles and 16 red-cell chunks each: 14.2 us, 17.5 with a barrier).
+__device__ __forceinline__ void record_fmax(unsigned long long* slot, double m, int n, BodyLds& S) {
+  m = wave_reduce_d(m, [](double a, double b) { return fmax_nan(a, b); });
+  if ((threadIdx.x & 63) != 0) return;
+  unsigned long long f = (unsigned long long)__double_as_longlong(m);
+  if (n > 0) {
+    __hip_atomic_fetch_max(&S.fmax, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__hip_atomic_fetch_add(&S.ended, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) != n - 1) return;
+    f = __hip_atomic_load(&S.fmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  if (f != 0) atomicMax(slot, f);
+}
 
 // u* at the vertices of a chunk, for wave w of the workgroup.
 template <typename T, bool MLS>
@@ -1096,7 +1110,7 @@ __device__ __forceinline__ void sample_vertices(const Ptrs<T>& p, const ChunkSlo
 }
 
 template <typename T, bool MLS>
-__device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl, BodyLds& lds) {
+__device__ __forceinline__ double chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl, BodyLds& lds) {
   const int lane = threadIdx.x & 63;
   // the slot alone gives the wave its vertices; the body record (in registers,
   // read before any store: the rigid step writes it back through Bp) is in
@@ -1265,7 +1279,7 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl
       if (lane == 0)
         done = __hip_atomic_fetch_add(&p.body_cnt[b], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
       done = __builtin_amdgcn_readfirstlane(done);   // lane 0's count
-      if (done != nch - 1) return;   // a later chunk finishes the body
+      if (done != nch - 1) return 0.0;   // a later chunk finishes the body
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       if (lane == 0) p.body_cnt[b] = 0;
       double r3[3];
@@ -1311,8 +1325,7 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl
                wave_reduce_i(q.y1, mx)};
       for (int k = lane; k < nch; k += 64) put_box(p.pbox, ch0 + k, q);
     }
-    record_fmax(p.fmax_bits + inst, fm);
-    return;
+    return fm;
   }
 
   // red cells and soft particles: vertex forces
@@ -1362,7 +1375,7 @@ __device__ __forceinline__ void chunk_impl(const Ptrs<T>& p, const ChunkSlot& sl
     const IBox q = wave_box(sxn, syn, inner);
     if (lane == 0) put_box(p.pbox, chunk, q);
   }
-  record_fmax(p.fmax_bits + inst, fm);
+  return fm;
 }
 
 // The other bin set (last read two steps ago) starts its next use empty.
@@ -1390,13 +1403,21 @@ __global__ __launch_bounds__(kBodyThreads) void k_body_chunks(Ptrs<T>) {
   const int slot = (blockIdx.x - p.ninst) * kBodyWaves + wave_id();
   if (slot < p.nslot) {   // nslot holds whole workgroups
     const ChunkSlot sl = load_uniform(p.slot_chunk + slot);
-    const int w = (sl.role >> 2) - 1;
+    const int barriers = sl.role & 3, w = ((sl.role >> 2) & 15) - 1, n = sl.role >> 8;
+    if (n > 0) {
+      if (threadIdx.x == 0) {
+        lds.body.fmax = 0ull;
+        lds.body.ended = 0;
+      }
+      __syncthreads();
+    }
     if (sl.chunk == -1 || w >= 0) {
       // no chunk of its own: the barriers of the waves that have one
       if (w >= 0) sample_vertices<T, MLS>(p, sl, w, lds.body);
-      for (int k = sl.role & 3; k > 0; --k) __syncthreads();
+      for (int k = 0; k < barriers; ++k) __syncthreads();
     } else {
-      chunk_impl<T, MLS>(p, sl, lds.body);
+      const double fm = chunk_impl<T, MLS>(p, sl, lds.body);
+      record_fmax(p.fmax_bits + (sl.kind_inst >> 2), fm, n, lds.body);
     }
   }
   clear_bins(p);

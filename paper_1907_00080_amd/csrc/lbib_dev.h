@@ -180,6 +180,7 @@ struct ChunkSlot {
   int kind_inst;         // kind | instance << 2
   int chunk0;            // the body's first chunk
   int role;              // barriers of the workgroup | (1 + the wave sampled for) << 2
+                         // | the workgroup's chunks, all of one instance's red cells << 8
 };
 
 // Device pointers into the workspace.
