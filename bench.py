@@ -222,7 +222,7 @@ def main():
     ap.add_argument("--tile", default="auto",
                     help="TXxTY, or auto: tile, step form and cache hints from the autotuner")
     ap.add_argument("--step-mode", type=int, default=None,
-                    help="with a fixed --tile: step form (1 three kernels, 2 merged, 3 overlapped)")
+                    help="with a fixed --tile: step mode (1, 2 or 3: names of one form)")
     ap.add_argument("--launch", type=int, default=0,
                     help="lattice-kernel launch with a fixed --tile: 0 one workgroup per tile, "
                          "1/2/4/8 persistent workgroups per CU")
@@ -440,9 +440,9 @@ def run_workload(pkg, torch, wl, tile, steps, warmup, graph_steps, kernel_steps,
 
 def repulsion_cost(pkg, torch, name, tile, steps, graph_steps):
     """The same workload with the vertex repulsion (Eq. repFor, the paper's
-    coefficient, cutoff 2) switched on, which runs the three-kernel step form
-    plus the repulsion kernel; against the same form without it and against
-    the default (merged) form without it."""
+    coefficient, cutoff 2) switched on, which adds the
+    repulsion kernel to the step; against the step without it, in step mode 1
+    and in the default mode."""
     from workloads import configs
     res = {}
     for key, coeff, mode in (("on", configs.REPULSION_COEFF, 0), ("off_three_kernel", 0.0, 1),

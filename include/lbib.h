@@ -225,10 +225,10 @@ lbib_status lbib_set_transfer(lbib_ctx* ctx, int32_t mode, int32_t weight, doubl
  * cutoff 2 is this library's reading (the expression has none).  Evaluated
  * at X^n with the membrane forces: red cells spread it, soft particles add
  * it to their vertex forces, rigid particles to their force and torque.
- * coeff = 0 switches it off.  With it on, the merged step form is not
- * reported and the adjoint calls return LBIB_EINVAL.  Errors: LBIB_EINVAL for coeff < 0, a non-finite value or a
- * cutoff outside (0, 16]; LBIB_ESTATE outside set-up or on a batch (a batch
- * takes each instance's setting). */
+ * coeff = 0 switches it off.  With it on, step mode 2 is not
+ * reported and the adjoint calls return LBIB_EINVAL.  Errors: LBIB_EINVAL for
+ * coeff < 0, a non-finite value or a cutoff outside (0, 16]; LBIB_ESTATE
+ * outside set-up or on a batch (a batch takes each instance's setting). */
 lbib_status lbib_set_repulsion(lbib_ctx* ctx, double coeff, double cutoff);
 
 /* Initial fluid state (setup phase): populations at the equilibrium of

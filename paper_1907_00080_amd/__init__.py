@@ -235,7 +235,7 @@ class _Ctx:
         self.check(self.lib.lbib_set_graph_steps(self.h, int(n)))
 
     def set_step_mode(self, mode: int):
-        """0 automatic, 1 three kernels, 2 merged advance, 3 overlapped tiles."""
+        """0 automatic, 1, 2 or 3: names of one form, three kernels per step."""
         self.check(self.lib.lbib_set_step_mode(self.h, int(mode)))
 
     @property

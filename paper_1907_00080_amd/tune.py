@@ -3,8 +3,7 @@ lattice-kernel launch form and population streaming (host logic).
 
 A batch advances many uneven capillary instances together (one launch per
 kernel per step for all of them).  Which tile shape of the fused lattice
-kernel, which step form (three kernels, merged marker advance, overlapped
-lattice tiles) and which number of steps per captured HIP graph run fastest
+kernel and which number of steps per captured HIP graph run fastest
 depends on the instance mix and the device, and so do the cache hints of the
 lattice kernel's population accesses (plain, non-temporal loads, non-temporal
 loads and stores), so `autotune` times whole steps of the actual batch for
@@ -25,7 +24,7 @@ from typing import Callable, Iterable, Optional, Sequence, Tuple
 
 TILES: Tuple[Tuple[int, int], ...] = ((64, 4), (128, 2), (32, 8), (256, 1))
 GRAPH_STEPS: Tuple[int, ...] = (10, 100)
-STEP_MODES: Tuple[int, ...] = (1, 2, 3)   # three kernels, merged advance, overlapped tiles
+STEP_MODES: Tuple[int, ...] = (1, 2, 3)   # names of one step form, three kernels
 CACHE_HINTS: Tuple[int, ...] = (0, 1, 3)   # plain, non-temporal loads, non-temporal loads + stores
 # lattice-kernel launch: one workgroup per tile (0) or a persistent grid of
 # that many workgroups per CU; timed for the best of the other choices
