@@ -1424,15 +1424,22 @@ __global__ __launch_bounds__(kBodyThreads) void k_body_chunks(Ptrs<T>) {
 }
 
 // ---------------------------------------------------------------- advance and stencil passes
-constexpr int kAdvWaves = 4;   // chunks per workgroup
+constexpr int kAdvWaves = 4;   // waves per workgroup
+// chunks per workgroup: an advancing chunk has two waves
+template <bool ADVANCE>
+__host__ __device__ constexpr int adv_chunks() { return ADVANCE ? kAdvWaves / 2 : kAdvWaves; }
 // Bound by the chain of one wave: its records, its vertices, the velocities
 // the lattice kernel left on other XCDs, then about 600 instructions at the
 // 4 to 10 cycles each that a wave alone on its SIMD issues at.  Measured (us,
 // before -> after the compacted bin slots, row loads of the velocity and one
 // star node per lane): 2000x200 7.6 -> 6.7, 6667x667 9.2 -> 7.6, 16-lattice
-// sweep 9.7 -> 9.1.
-// One wave per vertex chunk, its own vertices on lanes 2 .. 2 + cnt - 1 (the
-// halo lanes idle: their vertices belong to waves that move them in place).
+// sweep 9.7 -> 9.1.  When advancing, a chunk has two waves: the first moves the
+// vertices and registers them in the bins, the second takes the new positions
+// from LDS and does the stencils and the area record meanwhile: 2000x200 7.3 ->
+// 6.3, 6667x667 7.7 -> 7.0, sweep 9.2 -> 8.9, 1237x149 with moving least squares
+// 8.1 -> 6.1, 48 lattices of 14 cells 26.9 -> 26.3.
+// A chunk's own vertices are on lanes 2 .. 2 + cnt - 1 (the halo lanes idle:
+// their vertices belong to waves that move them in place).
 // ADVANCE: every vertex moves to X^{n+1} (red cells by the kinematic update,
 // particles adopt the positions of their dynamics); otherwise X stays (the
 // stencil pass after set-up or after the positions were set).  Each vertex
@@ -1442,18 +1449,22 @@ constexpr int kAdvWaves = 4;   // chunks per workgroup
 // adds up into the body's area.
 template <typename T, int TX, int TY, bool MLS, bool ADVANCE>
 __device__ __forceinline__ void advance_chunk(const Ptrs<T>& p, int* cnt, int* bin) {
+  constexpr int kChunks = adv_chunks<ADVANCE>();
+  __shared__ double s_xy[kChunks][2][64];   // new positions, from a chunk's first wave to its second
   const int lane = threadIdx.x & 63;
-  const int chunk = blockIdx.x * kAdvWaves + wave_id();
-  if (chunk >= p.nchunk_total) return;   // the whole wave
+  const int w = wave_id() % kChunks;
+  const bool second = wave_id() >= kChunks;
+  const int chunk = blockIdx.x * kChunks + w;
+  const bool held = chunk < p.nchunk_total;   // the same for the whole wave
   // one load gives the wave its vertices (the body record is not needed)
-  const int4 ci = load_uniform(p.chunk_info + chunk);
+  const int4 ci = load_uniform(p.chunk_info + (held ? chunk : 0));
   const int kind = ci.w & 3, inst = ci.w >> 2, cnt_v = ci.z;
-  const bool inner = lane >= 2 && lane < 2 + cnt_v;
+  const bool inner = held && lane >= 2 && lane < 2 + cnt_v;
   const int gm = inner ? ci.y + lane : 0;
   const LatDev L = load_uniform(p.lat + inst);
   double X = 0.0, Y = 0.0, xn = 0.0, yn = 0.0;
   int ncx = 0, ncy = 0;
-  if (inner) {
+  if (inner && !second) {
     X = p.x[gm];
     Y = p.y[gm];
     xn = X;
@@ -1468,43 +1479,61 @@ __device__ __forceinline__ void advance_chunk(const Ptrs<T>& p, int* cnt, int* b
     }
     stencil_centre(L, xn, yn, ncx, ncy);
   }
+  if constexpr (ADVANCE) {
+    if (!second) {
+      s_xy[w][0][lane] = xn;
+      s_xy[w][1][lane] = yn;
+    }
+    __syncthreads();
+    if (second) {
+      xn = s_xy[w][0][lane];
+      yn = s_xy[w][1][lane];
+    }
+  }
+  if (!held) return;
   // bin slots for the new stencil: the reservations (atomics) go out first
   // and the stores below are issued while they are in flight
   BinSlots S;
-  bins_reserve<TX, TY>(cnt, L, ncx, ncy, inner, S);
-  if (inner) {
-    if (ADVANCE) {
+  if (!second) {
+    bins_reserve<TX, TY>(cnt, L, ncx, ncy, inner, S);
+    if (ADVANCE && inner) {
       p.xm[gm] = X;
       p.ym[gm] = Y;
       p.x[gm] = xn;
       p.y[gm] = yn;
     }
+  }
+  if (!ADVANCE || second) {
     // stencil of the new position, used by the next step's spreading and
-    // interpolation (this lane has finished reading the old one)
-    marker_stencil<MLS>(p, L, gm, xn, yn, ncx, ncy);
+    // interpolation (the first wave has finished reading the old one: the
+    // position it handed over depends on all of it)
+    if (inner) marker_stencil<MLS>(p, L, gm, xn, yn, ncx, ncy);
+    const double xr = lane_next(xn), yr = lane_next(yn);
+    const double part = wave_sum(lane >= 2 && lane < 1 + cnt_v ? shoelace_term(xn, yn, xr, yr) : 0.0);
+    const int nct = p.nchunk_total;
+    if (lane == 0) p.area_part[chunk] = part;
+    if (lane == 2) {
+      p.area_part[nct + chunk] = xn;
+      p.area_part[2 * nct + chunk] = yn;
+    }
+    if (lane == 1 + cnt_v) {
+      p.area_part[3 * nct + chunk] = xn;
+      p.area_part[4 * nct + chunk] = yn;
+    }
+    if (!ADVANCE && kind != kRBC) {
+      // the stencil pass boxes the particles for the star pass that follows
+      // it (when advancing, the body kernel has boxed their new positions)
+      const IBox q = wave_box(xn, yn, inner);
+      if (lane == 0) put_box(p.pbox, chunk, q);
+    }
   }
-  const double xr = lane_next(xn), yr = lane_next(yn);
-  const double part = wave_sum(lane >= 2 && lane < 1 + cnt_v ? shoelace_term(xn, yn, xr, yr) : 0.0);
-  const int nct = p.nchunk_total;
-  if (lane == 0) p.area_part[chunk] = part;
-  if (lane == 2) {
-    p.area_part[nct + chunk] = xn;
-    p.area_part[2 * nct + chunk] = yn;
-  }
-  if (lane == 1 + cnt_v) {
-    p.area_part[3 * nct + chunk] = xn;
-    p.area_part[4 * nct + chunk] = yn;
-  }
-  if (!ADVANCE && kind != kRBC) {
-    // the stencil pass boxes the particles for the star pass that follows
-    // it (when advancing, the body kernel has boxed their new positions)
-    const IBox q = wave_box(xn, yn, inner);
-    if (lane == 0) put_box(p.pbox, chunk, q);
-  }
-  bins_commit(bin, p.bin_cap, p.overflow, gm, S);
+  if (!second) bins_commit(bin, p.bin_cap, p.overflow, gm, S);
 }
 
-inline __host__ __device__ int chunk_blocks(int nchunk) { return (nchunk + kAdvWaves - 1) / kAdvWaves; }
+template <bool ADVANCE>
+inline __host__ __device__ int chunk_blocks(int nchunk) {
+  return (nchunk + adv_chunks<ADVANCE>() - 1) / adv_chunks<ADVANCE>();
+}
 
 // Marker advance, new stencils, bins and area records (kernel weights only,
 // or with the MLS transfer compiled in, launched when an instance uses it);
@@ -1513,7 +1542,7 @@ inline __host__ __device__ int chunk_blocks(int nchunk) { return (nchunk + kAdvW
 template <typename T, int TX, int TY>
 __global__ __launch_bounds__(256) void k_advance(Ptrs<T>) {
   const Ptrs<T>& p = launch_args<T>();
-  const int cb = chunk_blocks(p.nchunk_total);
+  const int cb = chunk_blocks<true>(p.nchunk_total);
   if ((int)blockIdx.x >= cb) {
     star_pass(p, p.B, p.sch_next, blockIdx.x - cb);
     return;
@@ -1524,7 +1553,7 @@ __global__ __launch_bounds__(256) void k_advance(Ptrs<T>) {
 template <typename T, int TX, int TY>
 __global__ __launch_bounds__(256) void k_advance_mls(Ptrs<T>) {
   const Ptrs<T>& p = launch_args<T>();
-  const int cb = chunk_blocks(p.nchunk_total);
+  const int cb = chunk_blocks<true>(p.nchunk_total);
   if ((int)blockIdx.x >= cb) {
     star_pass(p, p.B, p.sch_next, blockIdx.x - cb);
     return;
@@ -1560,7 +1589,7 @@ __global__ __launch_bounds__(256) void k_stencil(Ptrs<T>) {
 template <typename T>
 void launch_stencil(const Ptrs<T>& p, const StepArgs& a, hipStream_t s) {
   if (p.nchunk_total == 0) return;
-  LBIB_TILE_DISPATCH(a, k_stencil, dim3(chunk_blocks(p.nchunk_total)), dim3(256), 0, s, p);
+  LBIB_TILE_DISPATCH(a, k_stencil, dim3(chunk_blocks<false>(p.nchunk_total)), dim3(256), 0, s, p);
   if (p.nstar_wg > 0) hipLaunchKernelGGL((k_star<T>), dim3(p.nstar_wg), dim3(256), 0, s, p);
 }
 
@@ -1574,7 +1603,7 @@ void launch_lagrangian(const Ptrs<T>& p, const StepArgs& a, hipStream_t s) {
 template <typename T>
 void launch_advance(const Ptrs<T>& p, const StepArgs& a, hipStream_t s) {
   if (p.nchunk_total == 0) return;
-  const dim3 grid((unsigned)(chunk_blocks(p.nchunk_total) + p.nstar_wg)), block(256);
+  const dim3 grid((unsigned)(chunk_blocks<true>(p.nchunk_total) + p.nstar_wg)), block(64 * kAdvWaves);
   if (a.any_mls) LBIB_TILE_DISPATCH(a, k_advance_mls, grid, block, 0, s, p);
   else LBIB_TILE_DISPATCH(a, k_advance, grid, block, 0, s, p);
 }
