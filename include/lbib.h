@@ -459,15 +459,15 @@ lbib_status lbib_adjoint_backward(lbib_ctx* ctx, double dJ, double* grad);
  * the last adjoint forward window. */
 lbib_status lbib_set_body_params(lbib_ctx* ctx, int32_t body, double ks, double kb, double sigma);
 
-/* Step form.  All forms run the same kernels and give the same bits: body
- * forces and particle motion, fused lattice step, marker advance.
- *   1  three kernels per step;
- *   2  merged advance (reported only when every body has <= 512 vertices and
- *      the repulsion is off, else as 1);
- *   3  overlapped lattice tiles;
+/* Step form.  All forms run the same three kernels per step and give the same
+ * bits: body forces and particle motion, fused lattice step, marker advance.
+ *   1  reported as 1;
+ *   2  reported as 2 when every body has <= 512 vertices and the repulsion is
+ *      off, else as 1;
+ *   3  reported as 3;
  *   0  automatic (default): 1.
- * Forms 2 and 3 name launch forms that measured slower everywhere and are
- * kept as names.  Allowed in any phase; LBIB_EINVAL for other values.
+ * 2 and 3 named launch forms that measured slower everywhere; the names are
+ * kept.  Allowed in any phase; LBIB_EINVAL for other values.
  * lbib_get_step_mode returns the form (after finalize_setup) or the
  * requested mode. */
 lbib_status lbib_set_step_mode(lbib_ctx* ctx, int32_t mode);

@@ -807,8 +807,8 @@ lbib_status upload_all(lbib_ctx* c) {
   return LBIB_OK;
 }
 
-// Whether the merged form, where it was asked for, can be the form in use
-// (lbib_get_step_mode): it needs small bodies and no vertex repulsion.
+// Whether mode 2, where it was asked for, is reported (lbib_get_step_mode): with
+// small bodies and without the vertex repulsion.
 constexpr int kSmallBody = 512;
 void resolve_step_mode(lbib_ctx* c) {
   bool small_bodies = true;

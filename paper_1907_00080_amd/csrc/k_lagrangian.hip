@@ -1,11 +1,12 @@
 // k_lagrangian.hip - Lagrangian side of the LB-IB step (gfx950), float64.
 //
 // Per time step n (the order is the one used throughout the library):
-//   k_body        first one workgroup per lattice instance:
+//   k_body_chunks first one workgroup per lattice instance:
 //                   - bond kinetics: rupture pass, then formation pass in
 //                     ascending ligand order (Sec. 2.2 Wall-Particle Interaction),
 //                     with Philox4x32-10 uniforms keyed by (step, ligand).
-//                 then one workgroup per body:
+//                 then one wave per vertex chunk of every body (a particle's
+//                 chunk has a second one for the fluid at its vertices):
 //                   - membrane strain, bending and area forces (Eqs. strainFor,
 //                     bendFor, areaFor), adhesion springs (Eq. adhFor);
 //                   - particles: probe pressure/viscous loads (Eqs. hydroForP,
@@ -13,7 +14,7 @@
 //                     position update (Eqs. newtonSoft, verletPos) or rigid BDF2
 //                     (Eqs. linearVelRig, angularVelRig), weak-coupling force.
 //   (the fused lattice kernel runs here)
-//   k_advance     one lane per marker: red cells by the kinematic IB
+//   k_advance     two waves per chunk: red cells by the kinematic IB
 //                 (Eq. kinematicPos), particles adopt their new positions;
 //                 the stencil of the new position (centre node floor(X + 1/2)
 //                 and the 3+3 weights of the Roma 3-point kernel) is stored
@@ -830,7 +831,7 @@ __device__ __forceinline__ void star_pass(const Ptrs<T>& p, const T* src, int sc
   }
 }
 
-// ---------------------------------------------------------------- k_body
+// ---------------------------------------------------------------- body kernel
 constexpr int kSpinMax = 1 << 22;   // bounded wait for the bond flag (~0.2 s)
 
 // max that propagates NaN (fmax drops it)
@@ -1055,7 +1056,8 @@ __device__ __forceinline__ void rigid_vertex(double rx, double ry, const double 
 // from the neighbouring lanes, the body's area from the chunk records of
 // X^n that the advance (or stencil) pass left, so a red cell's or a soft
 // particle's chunk needs nothing from any other wave.  A rigid particle's
-// force and torque need all its chunks: each chunk stores its partial sums
+// force and torque need all its chunks: up to kGroupChunks of them meet in the
+// LDS of their workgroup; in a larger body each chunk stores its partial sums
 // and the fluid velocity at its vertices, and the chunk that arrives last
 // (a counter per body) takes the rigid step and moves every vertex.
 //

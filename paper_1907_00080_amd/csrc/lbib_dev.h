@@ -306,7 +306,7 @@ __device__ __forceinline__ const A& launch_args2() {
 // sum over a body's vertices (its area, the rigid loads) is taken the same
 // way on every path: each chunk's inner terms summed over the 64 lanes by a
 // fixed butterfly (wave_sum), then the chunk sums in chunk order
-// (chunk_total), so all kernels and step forms give the same bits.
+// (chunk_total), so all kernels give the same bits.
 constexpr int kChunk = 60;
 constexpr int kStarNodes = 256;   // nodes of a particle's box per star-pass workgroup (one per lane)
 __host__ __device__ constexpr int chunks_of(int nv) { return (nv + kChunk - 1) / kChunk; }
