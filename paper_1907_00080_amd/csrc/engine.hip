@@ -179,9 +179,26 @@ struct Piece {
   size_t n;
 };
 
+// Makes the device of a stream current while it lives: an event can be recorded
+// only on streams of the device that was current when it was created, and the
+// stream a context is bound to may be another device's (the null stream is the
+// current device's).
+struct OnDeviceOf {
+  int was = -1;
+  explicit OnDeviceOf(hipStream_t s) {
+    hipDevice_t d = 0;
+    if (hipGetDevice(&was) == hipSuccess && hipStreamGetDevice(s, &d) == hipSuccess && d != was) (void)hipSetDevice(d);
+    else was = -1;
+  }
+  ~OnDeviceOf() {
+    if (was >= 0) (void)hipSetDevice(was);
+  }
+};
+
 // Pinned ring for readbacks of up to `most` bytes at a time.
 void make_ring(lbib_ctx* c, size_t most) {
   if (c->pin) return;
+  const OnDeviceOf on(c->stream);
   c->pin_slot = std::min(kPinSlotMax, std::max<size_t>(64u << 10, ((most + kPinSlots - 1) / kPinSlots + 255) & ~size_t(255)));
   void* q = nullptr;
   bool ok = hipHostMalloc(&q, c->pin_slot * kPinSlots, hipHostMallocDefault) == hipSuccess;

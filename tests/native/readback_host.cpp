@@ -1,0 +1,94 @@
+// Host side of the readbacks, on the HIP runtime of fake_hip.h.
+// readback_host CASE runs one case and says "ok".
+#include "fake_hip.h"
+
+#include <string>
+
+#include "lbib.h"
+
+#define CHECK(cond)                                                               \
+  do {                                                                            \
+    if (!(cond)) {                                                                \
+      std::fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #cond);      \
+      std::exit(1);                                                               \
+    }                                                                             \
+  } while (0)
+
+// A running context of one body on the given device's stream, the workspace in
+// host memory.
+struct Ctx {
+  lbib_ctx* h = nullptr;
+  char* ws = nullptr;
+  int nx, ny, nv;
+
+  Ctx(int nx_, int ny_, int nv_, int device) : nx(nx_), ny(ny_), nv(nv_) {
+    lbib_lattice_desc d;
+    std::memset(&d, 0, sizeof(d));
+    d.nx = nx;
+    d.ny = ny;
+    d.tau = 1.0;
+    CHECK(lbib_create(&d, &h) == LBIB_OK);
+    lbib_body_desc b;
+    std::memset(&b, 0, sizeof(b));
+    b.kind = LBIB_PARTICLE_RIGID;
+    b.nv = nv;
+    b.density_ratio = 1.1;
+    std::vector<double> xy(2 * nv);
+    for (int k = 0; k < nv; ++k) {
+      xy[2 * k] = 0.5 * nx + 6.0 * __builtin_cos(2 * 3.14159265358979 * k / nv);
+      xy[2 * k + 1] = 0.5 * ny + 6.0 * __builtin_sin(2 * 3.14159265358979 * k / nv);
+    }
+    CHECK(lbib_add_body(h, &b, xy.data(), nullptr) == LBIB_OK);
+    size_t n = 0;
+    CHECK(lbib_workspace_query(h, &n) == LBIB_OK);
+    CHECK(posix_memalign((void**)&ws, 256, n) == 0);
+    std::memset(ws, 0x5a, n);
+    CHECK(lbib_bind(h, ws, n, fake::stream_of(device)) == LBIB_OK);
+    CHECK(lbib_finalize_setup(h) == LBIB_OK);
+  }
+  void close() {
+    CHECK(lbib_destroy(h) == LBIB_OK);
+    std::free(ws);
+  }
+  void read_all() {
+    const size_t N = (size_t)nx * ny;
+    std::vector<double> r(N), u(N), v(N), xy(2 * nv);
+    CHECK(lbib_get_fields(h, r.data(), u.data(), v.data()) == LBIB_OK);
+    CHECK(lbib_get_markers(h, 0, xy.data()) == LBIB_OK);
+    CHECK(lbib_get_marker_forces(h, 0, xy.data()) == LBIB_OK);
+    lbib_diag d;
+    CHECK(lbib_diagnostics(h, &d) == LBIB_OK);
+    CHECK(state().size() > 0);
+  }
+  std::vector<char> state() {
+    size_t n = 0;
+    CHECK(lbib_get_state(h, nullptr, &n) == LBIB_OK);
+    std::vector<char> s(n, 0x11);
+    CHECK(lbib_get_state(h, s.data(), &n) == LBIB_OK);
+    return s;
+  }
+};
+
+// A context on a stream of device 1 while device 0 is current.
+static void device() {
+  fake::current = 0;
+  Ctx c(200, 90, 40, 1);
+  c.read_all();
+  CHECK(fake::current == 0);
+  fake::current = 1;
+  Ctx d(64, 32, 20, 0);
+  d.read_all();
+  c.read_all();
+  CHECK(fake::current == 1);
+  c.close();
+  d.close();
+  CHECK(fake::events.empty());
+}
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "device") device();
+  else return 2;
+  std::puts("ok");
+  return 0;
+}
