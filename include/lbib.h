@@ -30,8 +30,10 @@
  *     queries the workspace size, allocates that many bytes of device
  *     memory (any allocator; 256-byte alignment required) and binds it
  *     together with a HIP stream.  The workspace must outlive the context.
- *     It holds up to 2 MB of pinned host memory per context (from
- *     finalize_setup to destroy) that readbacks pass through.
+ *     Readbacks pass through pinned host memory that all contexts share:
+ *     2 MB for each readback under way at once, at most 8 MB per device.
+ *     When the last bound context is destroyed all but 2 MB per device are
+ *     freed, which waits for the device; no other destroy waits for it.
  *     All kernels are enqueued on the bound stream; lbib_step returns once
  *     the work is enqueued.  Readback calls synchronise that stream.
  *   - Lifecycle: create -> add_body / set_receptors / set_adhesion /

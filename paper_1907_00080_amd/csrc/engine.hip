@@ -89,11 +89,6 @@ struct lbib_ctx {
   size_t ws_bytes = 0;
   hipStream_t stream = nullptr;
   int device = -1;            // device current at lbib_bind (the workspace's)
-  // pinned ring that readbacks pass through (download): kPinSlots
-  // slots of pin_slot bytes, an event per slot; null where it was refused
-  char* pin = nullptr;
-  size_t pin_slot = 0;
-  hipEvent_t pin_ev[4] = {nullptr, nullptr, nullptr, nullptr};
   long long step = 0;
   int parity = 0;  // 0: A holds the state; 1: B holds it
   bool watchdog = false;
@@ -163,15 +158,15 @@ lbib_status fail(lbib_ctx* c, lbib_status s, const std::string& msg) {
   } while (0)
 
 // ---------------------------------------------------------------- host transfers
-// A readback to pageable host memory is cut into the slots of a pinned ring: the
-// copy engine fills one slot while the host empties another.  The runtime's own path for pageable memory pins or stages it
-// page by page, and the callers' arrays are usually new, so page faults are
-// much of the time: 3 x 35.6 MB of fields to new arrays 33 ms through a vector
-// (as it was), 10 ms straight, 7 ms through slots of 512 KB (256 KB 8.8; 4 MB
-// 7.8, with four copying threads 5, for a ring that takes 6 ms to set up);
-// 3 x 128 KB 0.24, 0.25 and 0.08 ms.
+// A readback to pageable host memory passes through the slots of a pinned ring:
+// the copy engine fills one slot while the host empties another.  The runtime's
+// own path for pageable memory pins or stages it page by page, and the callers'
+// arrays are usually new, so page faults are much of the time: 3 x 35.6 MB of
+// fields to new arrays 33 ms through a vector (as it was), 10 ms straight, 7 ms
+// through slots of 512 KB (256 KB 8.8; 4 MB 7.8, with four copying threads 5,
+// for a ring that takes 6 ms to set up); 3 x 128 KB 0.24, 0.25 and 0.08 ms.
 constexpr int kPinSlots = 4;
-constexpr size_t kPinSlotMax = 512u << 10;
+constexpr size_t kPinSlot = 512u << 10;
 
 struct Piece {
   char* host;
@@ -185,63 +180,150 @@ struct Piece {
 // current device's).
 struct OnDeviceOf {
   int was = -1;
+  hipDevice_t device = 0;
   explicit OnDeviceOf(hipStream_t s) {
-    hipDevice_t d = 0;
-    if (hipGetDevice(&was) == hipSuccess && hipStreamGetDevice(s, &d) == hipSuccess && d != was) (void)hipSetDevice(d);
-    else was = -1;
+    if (hipGetDevice(&was) == hipSuccess && hipStreamGetDevice(s, &device) == hipSuccess && device != was)
+      (void)hipSetDevice(device);
+    else
+      was = -1;
   }
   ~OnDeviceOf() {
     if (was >= 0) (void)hipSetDevice(was);
   }
 };
 
-// Pinned ring for readbacks of up to `most` bytes at a time.
-void make_ring(lbib_ctx* c, size_t most) {
-  if (c->pin) return;
-  const OnDeviceOf on(c->stream);
-  c->pin_slot = std::min(kPinSlotMax, std::max<size_t>(64u << 10, ((most + kPinSlots - 1) / kPinSlots + 255) & ~size_t(255)));
-  void* q = nullptr;
-  bool ok = hipHostMalloc(&q, c->pin_slot * kPinSlots, hipHostMallocDefault) == hipSuccess;
-  for (auto& e : c->pin_ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-  if (ok) {
-    c->pin = (char*)q;
-  } else {
-    if (q) (void)hipHostFree(q);
-    (void)hipGetLastError();
+struct Ring {
+  char* mem = nullptr;
+  hipEvent_t ev[kPinSlots] = {};
+
+  bool make() {
+    void* q = nullptr;
+    bool ok = hipHostMalloc(&q, kPinSlot * kPinSlots, hipHostMallocDefault) == hipSuccess;
+    mem = (char*)q;
+    for (auto& e : ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
+      drop();
+      (void)hipGetLastError();
+    }
+    return ok;
   }
+  void drop() {
+    if (mem) (void)hipHostFree(mem);
+    for (auto& e : ev)
+      if (e) (void)hipEventDestroy(e);
+    *this = Ring{};
+  }
+};
+
+// The rings of a process.  A readback takes one and gives it back at its end,
+// so as many exist as readbacks have run at once on a device, at most kMaxRings
+// (further ones go without).  They outlive the contexts that use them: freeing
+// pinned memory waits for every stream of the device (closing a context beside
+// another one's run took as long as that run, 0.1 ms without the free).  Only
+// when the last bound context closes are all freed but one per device.
+constexpr int kMaxRings = 4;
+struct RingPool {
+  std::mutex mu;
+  struct OfDevice {
+    std::vector<Ring> idle;
+    int made = 0;
+  };
+  std::map<int, OfDevice> dev;
+  int contexts = 0;   // bound
+};
+RingPool& ring_pool() {
+  static RingPool* p = new RingPool;   // not destroyed: contexts may close while the process exits
+  return *p;
 }
 
-void free_ring(lbib_ctx* c) {
-  if (c->pin) (void)hipHostFree(c->pin);
-  for (auto& e : c->pin_ev)
-    if (e) (void)hipEventDestroy(e);
-  c->pin = nullptr;
+void ring_context_bound() {
+  RingPool& P = ring_pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  ++P.contexts;
 }
+
+void ring_context_closed() {
+  std::vector<Ring> out;
+  {
+    RingPool& P = ring_pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    if (--P.contexts > 0) return;
+    for (auto& d : P.dev)
+      while (d.second.idle.size() > 1) {
+        out.push_back(d.second.idle.back());
+        d.second.idle.pop_back();
+        --d.second.made;
+      }
+  }
+  for (Ring& r : out) r.drop();
+}
+
+// A ring for one readback on stream s (ring.mem null: none to be had).
+struct RingUse {
+  Ring ring;
+  bool busy = false;   // copies into the ring may be under way
+  hipStream_t s;
+  int device;
+  explicit RingUse(hipStream_t stream) : s(stream) {
+    const OnDeviceOf on(stream);
+    device = on.device;
+    RingPool& P = ring_pool();
+    {
+      std::lock_guard<std::mutex> lock(P.mu);
+      RingPool::OfDevice& d = P.dev[device];
+      if (!d.idle.empty()) {
+        ring = d.idle.back();
+        d.idle.pop_back();
+        return;
+      }
+      if (d.made == kMaxRings) return;
+      ++d.made;
+    }
+    if (ring.make()) return;
+    std::lock_guard<std::mutex> lock(P.mu);
+    --P.dev[device].made;
+  }
+  ~RingUse() {
+    if (!ring.mem) return;
+    // (after an error: a ring that may still be written is not used again)
+    const bool lost = busy && hipStreamSynchronize(s) != hipSuccess;
+    RingPool& P = ring_pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    if (lost) --P.dev[device].made;
+    else P.dev[device].idle.push_back(ring);
+  }
+};
 
 // Copies every piece from the device on the context's stream; returns when the
 // host arrays hold them.
 lbib_status download(lbib_ctx* c, const std::vector<Piece>& ps) {
   hipStream_t s = c->stream;
-  if (!c->pin) {
+  size_t total = 0;
+  for (auto& p : ps) total += p.n;
+  RingUse use(s);
+  if (!use.ring.mem || total == 0) {
     for (auto& p : ps) HIPCHK(c, hipMemcpyAsync(p.host, p.dev, p.n, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     return LBIB_OK;
   }
+  // a load fills a slot, or a quarter of a smaller readback, so that its loads
+  // overlap too
+  const size_t load = std::min(kPinSlot, std::max<size_t>(64u << 10, (total / kPinSlots + 255) & ~size_t(255)));
   struct Seg {
     char* host;
     const char* dev;
     size_t n, off;
   };
   std::vector<Seg> segs;
-  std::vector<size_t> first;   // first segment of every slot's load
-  size_t off = c->pin_slot;    // full: the first segment opens a load
+  std::vector<size_t> first;   // first segment of every load
+  size_t off = load;           // full: the first segment opens a load
   for (auto& p : ps)
     for (size_t o = 0; o < p.n;) {
-      if (off >= c->pin_slot) {
+      if (off >= load) {
         first.push_back(segs.size());
         off = 0;
       }
-      const size_t n = std::min(p.n - o, c->pin_slot - off);
+      const size_t n = std::min(p.n - o, load - off);
       segs.push_back({p.host + o, p.dev + o, n, off});
       o += n;
       off = (off + n + 255) & ~size_t(255);
@@ -249,20 +331,22 @@ lbib_status download(lbib_ctx* c, const std::vector<Piece>& ps) {
   const size_t nl = first.size(), ahead = kPinSlots - 1;
   first.push_back(segs.size());
   auto enqueue = [&](size_t l) -> hipError_t {
-    char* slot = c->pin + (l % kPinSlots) * c->pin_slot;
+    char* slot = use.ring.mem + (l % kPinSlots) * kPinSlot;
     for (size_t k = first[l]; k < first[l + 1]; ++k) {
       const hipError_t e = hipMemcpyAsync(slot + segs[k].off, segs[k].dev, segs[k].n, hipMemcpyDeviceToHost, s);
       if (e != hipSuccess) return e;
     }
-    return hipEventRecord(c->pin_ev[l % kPinSlots], s);
+    return hipEventRecord(use.ring.ev[l % kPinSlots], s);
   };
+  use.busy = true;
   for (size_t l = 0; l < std::min(ahead, nl); ++l) HIPCHK(c, enqueue(l));
   for (size_t l = 0; l < nl; ++l) {
     if (l + ahead < nl) HIPCHK(c, enqueue(l + ahead));   // its slot was emptied in the last round
-    HIPCHK(c, hipEventSynchronize(c->pin_ev[l % kPinSlots]));
-    const char* slot = c->pin + (l % kPinSlots) * c->pin_slot;
+    HIPCHK(c, hipEventSynchronize(use.ring.ev[l % kPinSlots]));
+    const char* slot = use.ring.mem + (l % kPinSlots) * kPinSlot;
     for (size_t k = first[l]; k < first[l + 1]; ++k) std::memcpy(segs[k].host, slot + segs[k].off, segs[k].n);
   }
+  use.busy = false;
   return LBIB_OK;
 }
 
@@ -1653,6 +1737,7 @@ lbib_status lbib_bind(lbib_ctx* c, void* ws, size_t bytes, void* stream) {
   c->ws_bytes = bytes;
   c->stream = (hipStream_t)stream;
   c->phase = 1;
+  ring_context_bound();
   return LBIB_OK;
 }
 
@@ -1661,7 +1746,6 @@ lbib_status lbib_finalize_setup(lbib_ctx* c) {
   if (c->phase != 1) return fail(c, LBIB_ESTATE, "bind a workspace before finalize_setup");
   resolve_step_mode(c);
   c->inplace = resolve_inplace(c);
-  make_ring(c, std::max<size_t>(24 * (size_t)c->nodes, 9 * (size_t)elem_size(c->dtype) * c->nodes));
   lbib_status s = c->dtype == LBIB_F64 ? upload_all<double>(c) : upload_all<float>(c);
   if (s != LBIB_OK) return s;
   s = record_mass(c);
@@ -1816,13 +1900,18 @@ static lbib_status copy_marker_pair(lbib_ctx* c, int inst, int body, size_t ox, 
   if (s != LBIB_OK) return s;
   const int v0 = body_v0(c, inst, body), nv = c->inst[inst].bodies[body].d.nv;
   const double *x = (const double*)(c->ws + ox) + v0, *y = (const double*)(c->ws + oy) + v0;
-  if (c->pin && 16 * (size_t)nv <= c->pin_slot) {
-    // interleaved by a kernel straight into the pinned ring: one launch
-    launch_pair(x, y, nv, (double*)c->pin, c->stream);
-    HIPCHK(c, hipGetLastError());
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    std::memcpy(xy, c->pin, 16 * (size_t)nv);
-    return LBIB_OK;
+  if (16 * (size_t)nv <= kPinSlot) {
+    RingUse use(c->stream);
+    if (use.ring.mem) {
+      // interleaved by a kernel straight into the pinned ring: one launch
+      use.busy = true;
+      launch_pair(x, y, nv, (double*)use.ring.mem, c->stream);
+      HIPCHK(c, hipGetLastError());
+      HIPCHK(c, hipStreamSynchronize(c->stream));
+      use.busy = false;
+      std::memcpy(xy, use.ring.mem, 16 * (size_t)nv);
+      return LBIB_OK;
+    }
   }
   std::vector<double> a(nv), b(nv);
   s = download(c, {{(char*)a.data(), (char*)x, 8 * (size_t)nv}, {(char*)b.data(), (char*)y, 8 * (size_t)nv}});
@@ -2122,7 +2211,7 @@ lbib_status lbib_destroy(lbib_ctx* c) {
     if (st) (void)hipStreamDestroy(st);
   if (c->ev_adj_start) (void)hipEventDestroy(c->ev_adj_start);
   drop_kevents(c);
-  free_ring(c);
+  if (c->phase >= 1) ring_context_closed();
   delete c;
   return LBIB_OK;
 }

@@ -2,11 +2,12 @@
 // the test's executable, these functions are found before libamdhip64's.
 // Kernels do nothing.  Copies and fills run when something waits for them (an
 // event or a stream), in order, so that data taken too early is seen to be old.
-// Two devices; streams 0x1000 + d and what is created under device d belong to
+// Two devices; streams 0x1000 + 256 k + d and what is created under device d belong to
 // device d.
 #pragma once
 #include <hip/hip_runtime_api.h>
 
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -15,6 +16,7 @@
 #include <map>
 #include <mutex>
 #include <set>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -31,9 +33,11 @@ struct Stream {
 };
 
 inline std::mutex mu;
-inline int current = 0;                        // the current device
-inline hipError_t last = hipSuccess;           // what hipGetLastError gives
+inline thread_local int current = 0;           // the current device
+inline thread_local hipError_t last = hipSuccess;   // what hipGetLastError gives
 inline int refuse_malloc = 0;                  // refuse this many pinned allocations
+inline int fail_copy = 0;                      // this many copies to the host from now, one fails
+inline int wait_us = 0;                        // what waiting for an event takes
 inline std::map<hipStream_t, Stream> streams;
 inline std::set<Event*> events;
 inline std::map<char*, size_t> pinned;         // live pinned allocations
@@ -41,7 +45,7 @@ inline std::set<const void*> user_pinned;      // test buffers to be taken as pi
 inline long long mallocs = 0, frees = 0;
 inline std::vector<std::pair<char*, size_t>> d2h;   // targets of copies to the host
 
-inline hipStream_t stream_of(int device) { return (hipStream_t)(uintptr_t)(0x1000 + device); }
+inline hipStream_t stream_of(int device, int k = 0) { return (hipStream_t)(uintptr_t)(0x1000 + 256 * k + device); }
 inline int device_of(hipStream_t s) { return s ? (int)((uintptr_t)s & 0xff) : current; }
 inline hipError_t err(hipError_t e) {
   if (e != hipSuccess) last = e;
@@ -138,6 +142,7 @@ FAKE hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   return hipSuccess;
 }
 FAKE hipError_t hipEventSynchronize(hipEvent_t e) {
+  if (fake::wait_us) std::this_thread::sleep_for(std::chrono::microseconds(fake::wait_us));
   std::lock_guard<std::mutex> l(fake::mu);
   auto* v = (fake::Event*)e;
   fake::run(fake::streams[v->stream], v->at);
@@ -157,6 +162,7 @@ FAKE hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKi
     if (k == hipMemcpyDeviceToHost) {
       std::lock_guard<std::mutex> l(fake::mu);
       fake::d2h.push_back({(char*)dst, n});
+      if (fake::fail_copy > 0 && --fake::fail_copy == 0) return fake::err(hipErrorUnknown);
     }
     fake::issue(s, [=] { std::memcpy(dst, src, n); });
   }

@@ -3,6 +3,7 @@
 #include "fake_hip.h"
 
 #include <string>
+#include <thread>
 
 #include "lbib.h"
 
@@ -14,14 +15,14 @@
     }                                                                             \
   } while (0)
 
-// A running context of one body on the given device's stream, the workspace in
+// A running context of one body on a stream of the given device, the workspace in
 // host memory.
 struct Ctx {
   lbib_ctx* h = nullptr;
   char* ws = nullptr;
   int nx, ny, nv;
 
-  Ctx(int nx_, int ny_, int nv_, int device) : nx(nx_), ny(ny_), nv(nv_) {
+  Ctx(int nx_, int ny_, int nv_, int device, int k = 0) : nx(nx_), ny(ny_), nv(nv_) {
     lbib_lattice_desc d;
     std::memset(&d, 0, sizeof(d));
     d.nx = nx;
@@ -43,7 +44,7 @@ struct Ctx {
     CHECK(lbib_workspace_query(h, &n) == LBIB_OK);
     CHECK(posix_memalign((void**)&ws, 256, n) == 0);
     std::memset(ws, 0x5a, n);
-    CHECK(lbib_bind(h, ws, n, fake::stream_of(device)) == LBIB_OK);
+    CHECK(lbib_bind(h, ws, n, fake::stream_of(device, k)) == LBIB_OK);
     CHECK(lbib_finalize_setup(h) == LBIB_OK);
   }
   void close() {
@@ -82,12 +83,101 @@ static void device() {
   CHECK(fake::current == 1);
   c.close();
   d.close();
-  CHECK(fake::events.empty());
+}
+
+// Closing a context frees no pinned memory (that waits for all streams of the
+// device) while another is open; of what the readbacks of the last one used,
+// 2 MB stay for the next.
+static void close_one() {
+  fake::current = 0;
+  for (int round = 0; round < 3; ++round) {
+    Ctx a(200, 90, 40, 0, 0), b(64, 32, 20, 0, 1), c(300, 100, 30, 0, 2);
+    a.read_all();
+    b.read_all();
+    c.read_all();
+    a.close();
+    b.close();
+    CHECK(fake::frees == 0);
+    c.close();
+    size_t held = 0;
+    for (auto& m : fake::pinned) held += m.second;
+    CHECK(held <= (2u << 20));
+  }
+}
+
+// Contexts on threads of their own, more than there are rings: right data, at
+// most 8 MB pinned at a time.
+static void threads() {
+  fake::current = 0;
+  fake::wait_us = 300;
+  constexpr int n = 12;
+  std::vector<Ctx> cs;
+  std::vector<std::vector<char>> want;
+  for (int k = 0; k < n; ++k) {
+    cs.emplace_back(180 + 7 * k, 80, 24 + k, 0, k);
+    want.push_back(cs[k].state());
+  }
+  CHECK(want[0] != want[1]);
+  std::vector<std::thread> ts;
+  for (int k = 0; k < n; ++k)
+    ts.emplace_back([&, k] {
+      for (int i = 0; i < 15; ++i) {
+        CHECK(cs[k].state() == want[k]);
+        cs[k].read_all();
+      }
+    });
+  for (auto& t : ts) t.join();
+  size_t held = 0;
+  for (auto& m : fake::pinned) held += m.second;
+  CHECK(held <= (8u << 20));
+  for (auto& c : cs) c.close();
+  held = 0;
+  for (auto& m : fake::pinned) held += m.second;
+  CHECK(held <= (2u << 20));
+}
+
+// Pinned memory refused, then granted.
+static void refused() {
+  fake::current = 0;
+  fake::refuse_malloc = 1000;
+  Ctx a(200, 90, 40, 0);
+  const std::vector<char> direct = a.state();
+  a.read_all();
+  CHECK(fake::pinned.empty());
+  CHECK(hipGetLastError() == hipSuccess);
+  fake::refuse_malloc = 0;
+  Ctx b(200, 90, 40, 0, 1);
+  CHECK(b.state() == direct);
+  a.close();
+  b.close();
+}
+
+// A copy that fails leaves nothing under way that would still write to the ring.
+static void failed() {
+  fake::current = 0;
+  Ctx a(700, 300, 40, 0);
+  const std::vector<char> want = a.state();
+  for (int k : {1, 2, 5, 9}) {
+    std::vector<char> s(want.size());
+    size_t n = 0;
+    CHECK(lbib_get_state(a.h, nullptr, &n) == LBIB_OK);
+    fake::fail_copy = k;
+    CHECK(lbib_get_state(a.h, s.data(), &n) == LBIB_EHIP);
+    CHECK(hipGetLastError() != hipSuccess);
+    const fake::Stream& q = fake::streams[fake::stream_of(0)];
+    CHECK(q.done == q.issued);
+    CHECK(a.state() == want);
+  }
+  a.close();
 }
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "device") device();
+  else if (what == "close") close_one();
+  else if (what == "threads") threads();
+  else if (what == "refused") refused();
+  else if (what == "failed") failed();
   else return 2;
   std::puts("ok");
   return 0;
