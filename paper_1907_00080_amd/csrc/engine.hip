@@ -1905,8 +1905,7 @@ static lbib_status copy_marker_pair(lbib_ctx* c, int inst, int body, size_t ox, 
     if (use.ring.mem) {
       // interleaved by a kernel straight into the pinned ring: one launch
       use.busy = true;
-      launch_pair(x, y, nv, (double*)use.ring.mem, c->stream);
-      HIPCHK(c, hipGetLastError());
+      HIPCHK(c, launch_pair(x, y, nv, (double*)use.ring.mem, c->stream));
       HIPCHK(c, hipStreamSynchronize(c->stream));
       use.busy = false;
       std::memcpy(xy, use.ring.mem, 16 * (size_t)nv);

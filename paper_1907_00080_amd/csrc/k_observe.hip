@@ -94,8 +94,11 @@ __global__ void k_pair(const double* x, const double* y, int n, double* xy) {
   xy[2 * v + 1] = y[v];
 }
 
-void launch_pair(const double* x, const double* y, int n, double* xy, hipStream_t s) {
-  hipLaunchKernelGGL(k_pair, dim3((n + 255) / 256), dim3(256), 0, s, x, y, n, xy);
+// Returns the launch's own error: hipGetLastError would also give one that a
+// call of the program's before it left behind.
+hipError_t launch_pair(const double* x, const double* y, int n, double* xy, hipStream_t s) {
+  void* args[] = {&x, &y, &n, &xy};
+  return hipLaunchKernel((const void*)k_pair, dim3((n + 255) / 256), dim3(256), args, 0, s);
 }
 
 template void launch_observe<float>(const Ptrs<float>&, lbib_body_obs*, long long, hipStream_t);

@@ -580,7 +580,7 @@ struct StepArgs {
   int n_cu;             // compute units of the device
 };
 
-void launch_pair(const double* x, const double* y, int n, double* xy, hipStream_t s);
+hipError_t launch_pair(const double* x, const double* y, int n, double* xy, hipStream_t s);
 template <typename T>
 void launch_observe(const Ptrs<T>& p, lbib_body_obs* obs, long long step, hipStream_t s);
 

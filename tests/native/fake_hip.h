@@ -37,6 +37,7 @@ inline thread_local int current = 0;           // the current device
 inline thread_local hipError_t last = hipSuccess;   // what hipGetLastError gives
 inline int refuse_malloc = 0;                  // refuse this many pinned allocations
 inline int fail_copy = 0;                      // this many copies to the host from now, one fails
+inline int refuse_launch = 0;                  // refuse this many launches
 inline int wait_us = 0;                        // what waiting for an event takes
 inline std::map<hipStream_t, Stream> streams;
 inline std::set<Event*> events;
@@ -172,7 +173,11 @@ FAKE hipError_t hipMemsetAsync(void* p, int v, size_t n, hipStream_t s) {
   fake::issue(s, [=] { std::memset(p, v, n); });
   return hipSuccess;
 }
-FAKE hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+FAKE hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+  if (fake::refuse_launch == 0) return hipSuccess;
+  --fake::refuse_launch;
+  return fake::err(hipErrorLaunchFailure);
+}
 FAKE hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t, hipEvent_t, hipEvent_t, int) {
   return hipSuccess;
 }

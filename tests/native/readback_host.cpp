@@ -171,6 +171,23 @@ static void failed() {
   a.close();
 }
 
+// An error that a call of the program's own left behind is not the marker
+// read's, and stays for the program to see.
+static void stale_error() {
+  fake::current = 0;
+  Ctx a(64, 32, 20, 0);
+  std::vector<double> xy(40);
+  CHECK(hipSetDevice(7) != hipSuccess);
+  CHECK(lbib_get_markers(a.h, 0, xy.data()) == LBIB_OK);
+  CHECK(lbib_get_marker_forces(a.h, 0, xy.data()) == LBIB_OK);
+  CHECK(hipGetLastError() == hipErrorInvalidDevice);
+  fake::refuse_launch = 1;
+  CHECK(lbib_get_markers(a.h, 0, xy.data()) == LBIB_EHIP);
+  (void)hipGetLastError();
+  CHECK(lbib_get_markers(a.h, 0, xy.data()) == LBIB_OK);
+  a.close();
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "device") device();
@@ -178,6 +195,7 @@ int main(int argc, char** argv) {
   else if (what == "threads") threads();
   else if (what == "refused") refused();
   else if (what == "failed") failed();
+  else if (what == "error") stale_error();
   else return 2;
   std::puts("ok");
   return 0;

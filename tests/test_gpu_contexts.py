@@ -1,5 +1,6 @@
 """Contexts beside each other: what one does must not wait for, or be changed
 by, another one's run."""
+import ctypes
 import threading
 
 import numpy as np
@@ -65,3 +66,18 @@ def test_readbacks_on_threads_of_their_own():
         assert got[k] is not None
         for a, b in zip(want[k], got[k]):
             assert np.array_equal(a, b)
+
+
+def test_marker_reads_after_a_refused_call_of_the_program():
+    """A HIP call of the program's own that the runtime refused (and whose error
+    it still holds for this thread) is not an error of the next marker read."""
+    print("[gpu-contexts] refused call", flush=True)
+    s = pkg.Sim(_small(0))
+    s.step(2)
+    want = [s.markers(1), s.marker_forces(1)]
+    hip_set_device = s.lib.hipSetDevice   # the runtime the library is linked to
+    hip_set_device.argtypes, hip_set_device.restype = [ctypes.c_int], ctypes.c_int
+    for k, read in enumerate((s.markers, s.marker_forces)):
+        assert hip_set_device(999) != 0
+        assert np.array_equal(read(1), want[k])
+    s.close()
