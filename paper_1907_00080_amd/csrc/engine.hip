@@ -294,18 +294,32 @@ struct RingUse {
   }
 };
 
+// Whether host memory is pinned (or managed): the copy engine writes it itself,
+// without a ring's second copy.
+bool is_pinned(const void* host) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, host) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged;
+}
+
 // Copies every piece from the device on the context's stream; returns when the
 // host arrays hold them.
+lbib_status download_direct(lbib_ctx* c, const std::vector<Piece>& ps) {
+  for (auto& p : ps) HIPCHK(c, hipMemcpyAsync(p.host, p.dev, p.n, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  return LBIB_OK;
+}
+
+// The same through a ring.
 lbib_status download(lbib_ctx* c, const std::vector<Piece>& ps) {
   hipStream_t s = c->stream;
   size_t total = 0;
   for (auto& p : ps) total += p.n;
   RingUse use(s);
-  if (!use.ring.mem || total == 0) {
-    for (auto& p : ps) HIPCHK(c, hipMemcpyAsync(p.host, p.dev, p.n, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
-    return LBIB_OK;
-  }
+  if (!use.ring.mem || total == 0) return download_direct(c, ps);
   // a load fills a slot, or a quarter of a smaller readback, so that its loads
   // overlap too
   const size_t load = std::min(kPinSlot, std::max<size_t>(64u << 10, (total / kPinSlots + 255) & ~size_t(255)));
@@ -2036,7 +2050,8 @@ lbib_status lbib_get_state(lbib_ctx* c, void* blob, size_t* bytes) {
     ps.push_back({o, c->ws + r.first, r.second});
     o += r.second;
   }
-  st = download(c, ps);
+  // (200 MB to a pinned blob 3.8 ms, 9.3 through the ring)
+  st = is_pinned(blob) ? download_direct(c, ps) : download(c, ps);
   if (st != LBIB_OK) return st;
   *bytes = total;
   return LBIB_OK;

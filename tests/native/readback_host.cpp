@@ -188,6 +188,29 @@ static void stale_error() {
   a.close();
 }
 
+// A state blob in pinned memory is written by the copy engine itself.
+static void pinned_blob() {
+  fake::current = 0;
+  Ctx a(700, 300, 40, 0);
+  const std::vector<char> want = a.state();
+  std::vector<char> s(want.size());
+  size_t n = 0;
+  CHECK(lbib_get_state(a.h, nullptr, &n) == LBIB_OK);
+  for (bool pinned : {true, false}) {
+    if (pinned) fake::user_pinned.insert(s.data());
+    else fake::user_pinned.clear();
+    std::fill(s.begin(), s.end(), 0);
+    fake::d2h.clear();
+    CHECK(lbib_get_state(a.h, s.data(), &n) == LBIB_OK);
+    CHECK(s == want);
+    size_t direct = 0;
+    for (auto& d : fake::d2h)
+      if (d.first >= s.data() && d.first < s.data() + s.size()) direct += d.second;
+    CHECK(pinned ? direct > 0.99 * n : direct == 0);
+  }
+  a.close();
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "device") device();
@@ -196,6 +219,7 @@ int main(int argc, char** argv) {
   else if (what == "refused") refused();
   else if (what == "failed") failed();
   else if (what == "error") stale_error();
+  else if (what == "pinned") pinned_blob();
   else return 2;
   std::puts("ok");
   return 0;

@@ -29,8 +29,9 @@ def driver(tmp_path_factory):
 
 # device: a stream of another device than the current one; close: contexts
 # closed beside others; threads: more of them than rings; refused, failed: no
-# pinned memory, a copy that fails; error: one left behind by the program
-@pytest.mark.parametrize("case", ["device", "close", "threads", "refused", "failed", "error"])
+# pinned memory, a copy that fails; error: one left behind by the program;
+# pinned: a state blob in pinned memory
+@pytest.mark.parametrize("case", ["device", "close", "threads", "refused", "failed", "error", "pinned"])
 def test_readbacks(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
