@@ -227,8 +227,8 @@ lbib_status lbib_set_transfer(lbib_ctx* ctx, int32_t mode, int32_t weight, doubl
  * cutoff 2 is this library's reading (the expression has none).  Evaluated
  * at X^n with the membrane forces: red cells spread it, soft particles add
  * it to their vertex forces, rigid particles to their force and torque.
- * coeff = 0 switches it off.  With it on, step mode 2 is not
- * reported and the adjoint calls return LBIB_EINVAL.  Errors: LBIB_EINVAL for
+ * coeff = 0 switches it off.  With it on, step mode 2 is
+ * answered as 1 and the adjoint calls return LBIB_EINVAL.  Errors: LBIB_EINVAL for
  * coeff < 0, a non-finite value or a cutoff outside (0, 16]; LBIB_ESTATE
  * outside set-up or on a batch (a batch takes each instance's setting). */
 lbib_status lbib_set_repulsion(lbib_ctx* ctx, double coeff, double cutoff);
@@ -461,17 +461,17 @@ lbib_status lbib_adjoint_backward(lbib_ctx* ctx, double dJ, double* grad);
  * the last adjoint forward window. */
 lbib_status lbib_set_body_params(lbib_ctx* ctx, int32_t body, double ks, double kb, double sigma);
 
-/* Step form.  All forms run the same three kernels per step and give the same
- * bits: body forces and particle motion, fused lattice step, marker advance.
- *   1  reported as 1;
- *   2  reported as 2 when every body has <= 512 vertices and the repulsion is
+/* Step mode.  Every mode runs the same three kernels per step, body forces and
+ * particle motion, fused lattice step, marker advance (and the repulsion first
+ * where it is on).  2 and 3 named launch forms that measured slower everywhere
+ * and are gone; their names, and which contexts answer with them, are kept:
+ *   1  answered as 1;
+ *   2  answered as 2 when every body has <= 512 vertices and the repulsion is
  *      off, else as 1;
- *   3  reported as 3;
- *   0  automatic (default): 1.
- * 2 and 3 named launch forms that measured slower everywhere; the names are
- * kept.  Allowed in any phase; LBIB_EINVAL for other values.
- * lbib_get_step_mode returns the form (after finalize_setup) or the
- * requested mode. */
+ *   3  answered as 3;
+ *   0  automatic (default): as 2.
+ * Allowed in any phase; LBIB_EINVAL for other values.  lbib_get_step_mode
+ * gives that answer after finalize_setup, the requested mode before. */
 lbib_status lbib_set_step_mode(lbib_ctx* ctx, int32_t mode);
 lbib_status lbib_get_step_mode(const lbib_ctx* ctx, int32_t* mode);
 

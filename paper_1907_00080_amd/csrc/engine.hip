@@ -104,9 +104,9 @@ struct lbib_ctx {
   bool ktiming = false;       // bracket fused-kernel launches with events
   std::vector<std::pair<hipEvent_t, hipEvent_t>> kevents;
   int bin_cap = 1024;         // marker registrations per tile and bin set
-  // the step form asked for (lbib_set_step_mode) and, below, reported; every
-  // form launches the same kernels
-  int step_mode = 0;
+  // the step mode asked for (lbib_set_step_mode) and the one reported once
+  // running; every mode launches the same kernels
+  int step_mode = 0, step_mode_name = 1;
   // cache hints of the fused lattice kernel's population accesses
   // (lbib_set_cache_hints): -1 automatic, else the NT bits
   int cache_hints = -1;
@@ -118,10 +118,8 @@ struct lbib_ctx {
   // inplace is the resolved form (see streamed_slot in lbib_dev.h)
   int streaming = -1;
   bool inplace = false;
-  bool merge_advance = false; // form 2 asked for and possible
   bool repulsion = false;     // some instance has the vertex repulsion on
   int nrep_chunk = 0;         // repulsion work units (kRepChunk vertices of a body)
-  bool overlap = false;       // form 3 asked for
   // streams of the adjoint's backward pass (segment recompute, reverse
   // sweep), created together so that they sit on different hardware queues
   hipStream_t adj_s[2] = {nullptr, nullptr};
@@ -922,19 +920,22 @@ lbib_status upload_all(lbib_ctx* c) {
   return LBIB_OK;
 }
 
-// Whether mode 2, where it was asked for, is reported (lbib_get_step_mode): with
-// small bodies and without the vertex repulsion.
+// Which step mode is reported (lbib_get_step_mode).  1 is what runs; 2 and 3
+// were launch forms that are gone, and each context still answers with the name
+// it would have answered with then: 2 (also the automatic choice) needed every
+// body within kSmallBody vertices and the vertex repulsion off.
 constexpr int kSmallBody = 512;
 void resolve_step_mode(lbib_ctx* c) {
-  bool small_bodies = true;
+  bool two = true;
   c->repulsion = false;
   for (auto& I : c->inst) {
     for (auto& b : I.bodies)
-      if (b.d.nv > kSmallBody) small_bodies = false;
+      if (b.d.nv > kSmallBody) two = false;
     if (I.rep_coeff > 0.0 && !I.bodies.empty()) c->repulsion = true;
   }
-  c->merge_advance = c->step_mode == 2 && small_bodies && !c->repulsion;
-  c->overlap = c->step_mode == 3;
+  two = two && !c->repulsion;
+  const int m = c->step_mode == 0 ? 2 : c->step_mode;
+  c->step_mode_name = m == 2 && !two ? 1 : m;
 }
 
 // n steps of three kernels each (four with the repulsion): bodies, lattice,
@@ -1853,7 +1854,7 @@ lbib_status lbib_get_cache_hints(const lbib_ctx* cc, int32_t* hints) {
 lbib_status lbib_get_step_mode(const lbib_ctx* cc, int32_t* mode) {
   lbib_ctx* c = const_cast<lbib_ctx*>(cc);
   if (!c || !mode) return fail(c, LBIB_EINVAL, "NULL argument");
-  *mode = c->phase == 2 ? (c->overlap ? 3 : (c->merge_advance ? 2 : 1)) : c->step_mode;
+  *mode = c->phase == 2 ? c->step_mode_name : c->step_mode;
   return LBIB_OK;
 }
 

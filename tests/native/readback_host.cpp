@@ -1,4 +1,5 @@
-// Host side of the readbacks, on the HIP runtime of fake_hip.h.
+// Host side of the readbacks and of the step modes, on the HIP runtime of
+// fake_hip.h.
 // readback_host CASE runs one case and says "ok".
 #include "fake_hip.h"
 
@@ -22,7 +23,7 @@ struct Ctx {
   char* ws = nullptr;
   int nx, ny, nv;
 
-  Ctx(int nx_, int ny_, int nv_, int device, int k = 0) : nx(nx_), ny(ny_), nv(nv_) {
+  Ctx(int nx_, int ny_, int nv_, int device, int k = 0, double repulsion = 0.0) : nx(nx_), ny(ny_), nv(nv_) {
     lbib_lattice_desc d;
     std::memset(&d, 0, sizeof(d));
     d.nx = nx;
@@ -40,6 +41,7 @@ struct Ctx {
       xy[2 * k + 1] = 0.5 * ny + 6.0 * __builtin_sin(2 * 3.14159265358979 * k / nv);
     }
     CHECK(lbib_add_body(h, &b, xy.data(), nullptr) == LBIB_OK);
+    CHECK(lbib_set_repulsion(h, repulsion, 2.0) == LBIB_OK);
     size_t n = 0;
     CHECK(lbib_workspace_query(h, &n) == LBIB_OK);
     CHECK(posix_memalign((void**)&ws, 256, n) == 0);
@@ -211,6 +213,26 @@ static void pinned_blob() {
   a.close();
 }
 
+// What lbib_get_step_mode answers for each mode asked for: the name that the
+// form of that mode has had throughout (automatic: 2 where 2 is possible).
+static void modes() {
+  fake::current = 0;
+  Ctx small(64, 32, 512, 0), large(64, 32, 513, 0), crowd(64, 32, 40, 0, 0, 1e-5);
+  const struct {
+    Ctx* c;
+    int want[4];
+  } rows[] = {{&small, {2, 1, 2, 3}}, {&large, {1, 1, 1, 3}}, {&crowd, {1, 1, 1, 3}}};
+  for (auto& r : rows) {
+    int32_t got = -1;
+    CHECK(lbib_get_step_mode(r.c->h, &got) == LBIB_OK && got == r.want[0]);
+    for (int m : {3, 1, 2, 0}) {
+      CHECK(lbib_set_step_mode(r.c->h, m) == LBIB_OK);
+      CHECK(lbib_get_step_mode(r.c->h, &got) == LBIB_OK && got == r.want[m]);
+    }
+    r.c->close();
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "device") device();
@@ -220,6 +242,7 @@ int main(int argc, char** argv) {
   else if (what == "failed") failed();
   else if (what == "error") stale_error();
   else if (what == "pinned") pinned_blob();
+  else if (what == "modes") modes();
   else return 2;
   std::puts("ok");
   return 0;

@@ -1,4 +1,4 @@
-"""Host side of the readbacks (no GPU): the built library on a HIP runtime that
+"""Host side of the readbacks and the step modes (no GPU): the built library on a HIP runtime that
 works on host memory and runs copies only when something waits for them
 (tests/native/fake_hip.h)."""
 import os
@@ -30,8 +30,8 @@ def driver(tmp_path_factory):
 # device: a stream of another device than the current one; close: contexts
 # closed beside others; threads: more of them than rings; refused, failed: no
 # pinned memory, a copy that fails; error: one left behind by the program;
-# pinned: a state blob in pinned memory
-@pytest.mark.parametrize("case", ["device", "close", "threads", "refused", "failed", "error", "pinned"])
-def test_readbacks(driver, case):
+# pinned: a state blob in pinned memory; modes: the step modes' names
+@pytest.mark.parametrize("case", ["device", "close", "threads", "refused", "failed", "error", "pinned", "modes"])
+def test_host_side(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
