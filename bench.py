@@ -184,9 +184,9 @@ def traffic_from_profile(workload_name: str, tile=None, hints=None, launch=0, st
 
 
 def tuned_config(pkg, wl, args):
-    """Tile shape and step form for one workload: the autotuner's pick (whole
-    steps of this workload timed for every tile and step form), or the tile
-    given on the command line with the default step form."""
+    """Tile shape and launch settings for one workload: the autotuner's pick
+    (whole steps of this workload timed for every tile and cache-hint form), or
+    the ones given on the command line."""
     if args.tile != "auto":
         return (tuple(int(v) for v in args.tile.split("x")), args.step_mode, args.hints, args.launch,
                 args.streaming, None)
@@ -440,17 +440,14 @@ def run_workload(pkg, torch, wl, tile, steps, warmup, graph_steps, kernel_steps,
 
 def repulsion_cost(pkg, torch, name, tile, steps, graph_steps):
     """The same workload with the vertex repulsion (Eq. repFor, the paper's
-    coefficient, cutoff 2) switched on, which adds the
-    repulsion kernel to the step; against the step without it, in step mode 1
-    and in the default mode."""
+    coefficient, cutoff 2) switched on, which adds the repulsion kernel to the
+    step; against the step without it."""
     from workloads import configs
     res = {}
-    for key, coeff, mode in (("on", configs.REPULSION_COEFF, 0), ("off_three_kernel", 0.0, 1),
-                             ("off_default", 0.0, 0)):
+    for key, coeff in (("on", configs.REPULSION_COEFF), ("off", 0.0)):
         wl = make_workload(name)
         wl.repulsion = coeff
         sim = pkg.Sim(wl, dtype="f32", tile=tile, device="cuda:0", graph_steps=graph_steps)
-        sim.set_step_mode(mode)
         sim.step(200)
         ms = _timed(torch, sim, steps) / steps
         d = sim.diagnostics()
@@ -461,10 +458,9 @@ def repulsion_cost(pkg, torch, name, tile, steps, graph_steps):
         sim.close()
     res["workload"] = name + " with vertex repulsion"
     res["repulsion_us_per_step"] = round(1e3 * (res["on"]["ms_per_step"]
-                                               - res["off_three_kernel"]["ms_per_step"]), 2)
-    print(f"bench: repulsion on {res['on']['ms_per_step'] * 1e3:.2f} us/step, three kernels "
-          f"without {res['off_three_kernel']['ms_per_step'] * 1e3:.2f}, default form "
-          f"{res['off_default']['ms_per_step'] * 1e3:.2f}", file=sys.stderr, flush=True)
+                                               - res["off"]["ms_per_step"]), 2)
+    print(f"bench: repulsion on {res['on']['ms_per_step'] * 1e3:.2f} us/step, "
+          f"without {res['off']['ms_per_step'] * 1e3:.2f}", file=sys.stderr, flush=True)
     return res
 
 
