@@ -43,19 +43,6 @@ struct Stencil {
   double wx[3], dwx[3], ddwx[3], wy[3], dwy[3], ddwy[3];
 };
 
-// Weights of the three nodes along one axis, d = (nearest node) - (point) in
-// (-1/2, 1/2], with first and second derivatives, all from one square root
-// (roma_weights3; phi'' is -1/q^3 on the inner node and 1/(2 q^3) on the outer
-// ones).  Taken node by node the six weights cost about 1500 instructions of
-// a probe's chain; this takes about 150.
-__device__ __forceinline__ void axis_weights(double d, bool second, double w[3], double dw[3], double ddw[3]) {
-  roma_weights3<true>(d, w, dw);
-  const double q2 = 1.0 - 3.0 * d * d;
-  const double c = second ? 1.0 / (q2 * sqrt(q2)) : 0.0;
-  ddw[0] = ddw[2] = 0.5 * c;
-  ddw[1] = -c;
-}
-
 __device__ __forceinline__ void stencil_at(const LatDev& L, double X, double Y, bool second, Stencil& s) {
   const double cxr = floor(X + 0.5), cyr = floor(Y + 0.5);
   const bool pery = L.periodic_y != 0;

@@ -46,6 +46,20 @@ LBIB_HD void roma_weights3(double d, double w[3], double dw[3]) {
   }
 }
 
+// The same with second derivatives (zero unless asked for), phi'' being -1/q^3
+// on the inner node and 1/(2 q^3) on the outer ones, at both ends of d too:
+// each node keeps the piece that its weight is taken from.  Taken node by node
+// the six weights of a probe cost about 1500 instructions of its chain; this
+// takes about 150.
+LBIB_HD void axis_weights(double d, bool second, double w[3], double dw[3], double ddw[3]) {
+  roma_weights3<true>(d, w, dw);
+  const double q2 = 1.0 - 3.0 * d * d;
+  const double c = second ? 1.0 / (q2 * sqrt(q2)) : 0.0;
+  ddw[0] = ddw[2] = 0.5 * c;
+  ddw[1] = -c;
+}
+
+// Derivative at any r.
 LBIB_HD double roma_dphi(double r) {
   double a = fabs(r);
   if (a <= 0.5) return -r / sqrt(1.0 - 3.0 * r * r);
@@ -59,7 +73,8 @@ LBIB_HD double roma_dphi(double r) {
 
 // Second derivative: -(1 - 3 r^2)^(-3/2) on the inner piece and
 // (1 - 3 (1 - |r|)^2)^(-3/2) / 2 on the outer one; phi is C1, so this jumps
-// at |r| = 1/2 and 3/2.
+// at |r| = 1/2 and 3/2.  (No kernel takes it node by node: it is what the host
+// checks hold axis_weights against.)
 LBIB_HD double roma_ddphi(double r) {
   double a = fabs(r);
   if (a <= 0.5) {
