@@ -61,9 +61,9 @@ struct Layout {
   size_t lat, body, A, B, U;
   size_t x, y, xm, ym, xn, yn, fx, fy, l0, th0, r0x, r0y;
   size_t mbody, minfo, cx, cy, wx, wy, frep, rep_chunk, obs;
-  size_t s[9];
+  size_t s[3];
   size_t cnt[2], bins[2], touched, overflow, fmax, bond_flag, spin, Uspare, tile_inst;
-  size_t lig_body, lig_elem, l2r, r2l, lig_flag, rec_x, lig_va, lig_vb, lig_sigma, lig_sp;
+  size_t l2r, r2l, lig_flag, rec_x, lig_va, lig_vb, lig_sigma, lig_sp;
   size_t step_next, step_cur, ties, red;
   size_t chunk_info, area_part, rig_part, body_cnt, star, pbox, star_wg, slot_chunk;
   size_t total;
@@ -497,8 +497,6 @@ void compute_layout(lbib_ctx* c) {
   L.spin = take(8);
   L.Uspare = take(es * 2 * c->nodes);   // velocity output of measurement launches
   L.tile_inst = take(4 * c->ntiles);
-  L.lig_body = take(4 * nl);
-  L.lig_elem = take(4 * nl);
   L.l2r = take(4 * nl);
   L.lig_flag = take(4 * nl);
   L.lig_va = take(4 * nl);
@@ -554,8 +552,8 @@ Ptrs<T> make_ptrs(const lbib_ctx* c) {
   p.cx = (int*)(w + L.cx); p.cy = (int*)(w + L.cy);
   p.wx = (double*)(w + L.wx); p.wy = (double*)(w + L.wy);
   p.frep = (double*)(w + L.frep);
-  double** sp[] = {&p.s_len, &p.s_nx, &p.s_ny, &p.s_bc, &p.s_bnx, &p.s_bny, &p.s_bfl, &p.s_fex, &p.s_fey};
-  for (int k = 0; k < 9; ++k) *sp[k] = (double*)(w + L.s[k]);
+  double** sp[] = {&p.s_len, &p.s_fex, &p.s_fey};
+  for (int k = 0; k < 3; ++k) *sp[k] = (double*)(w + L.s[k]);
   p.cnt_cur = (int*)(w + L.cnt[c->parity]);
   p.cnt_next = (int*)(w + L.cnt[c->parity ^ 1]);
   p.bin_cur = (int*)(w + L.bins[c->parity]);
@@ -573,8 +571,6 @@ Ptrs<T> make_ptrs(const lbib_ctx* c) {
   p.spin_timeouts = (int*)(w + L.spin);
   p.bin_cap = c->bin_cap;
   p.tile_inst = (int*)(w + L.tile_inst);
-  p.lig_body = (int*)(w + L.lig_body);
-  p.lig_elem = (int*)(w + L.lig_elem);
   p.l2r = (int*)(w + L.l2r);
   p.lig_flag = (int*)(w + L.lig_flag);
   p.lig_va = (int*)(w + L.lig_va);
@@ -698,7 +694,6 @@ lbib_status upload_all(lbib_ctx* c) {
   std::vector<double> x(nm), y(nm), l0(nm), th0(nm), r0x(nm, 0.0), r0y(nm, 0.0);
   std::vector<int> mbody(nm, 0), minfo(nm, 0);
   std::vector<int> tile_inst(std::max(c->ntiles, 1));
-  std::vector<int> lig_body(std::max(c->nlig, 1)), lig_elem(std::max(c->nlig, 1));
   std::vector<int> lig_va(std::max(c->nlig, 1)), lig_vb(std::max(c->nlig, 1));
   std::vector<double> lig_sigma(std::max(c->nlig, 1), 0.0);
   std::vector<double> rec_x(std::max(c->nrec, 1));
@@ -783,8 +778,6 @@ lbib_status upload_all(lbib_ctx* c) {
       if (b.d.ligand_stride > 0) {
         int k = 0;
         for (int e = 0; e < b.d.nv; e += b.d.ligand_stride, ++k) {
-          lig_body[li] = bi;
-          lig_elem[li] = e;
           lig_va[li] = m + e;
           lig_vb[li] = m + (e + 1) % b.d.nv;
           lig_sigma[li] = b.d.sigma;
@@ -860,8 +853,6 @@ lbib_status upload_all(lbib_ctx* c) {
   if (!c->slots.empty())
     HIPCHK(c, up(L.slot_chunk, c->slots.data(), sizeof(ChunkSlot) * c->slots.size()));
   HIPCHK(c, up(L.tile_inst, tile_inst.data(), 4 * tile_inst.size()));
-  HIPCHK(c, up(L.lig_body, lig_body.data(), 4 * lig_body.size()));
-  HIPCHK(c, up(L.lig_elem, lig_elem.data(), 4 * lig_elem.size()));
   HIPCHK(c, up(L.lig_va, lig_va.data(), 4 * lig_va.size()));
   HIPCHK(c, up(L.lig_vb, lig_vb.data(), 4 * lig_vb.size()));
   HIPCHK(c, up(L.lig_sigma, lig_sigma.data(), 8 * lig_sigma.size()));

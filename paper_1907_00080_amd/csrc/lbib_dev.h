@@ -236,7 +236,7 @@ struct Ptrs {
   double* frep;          // per marker: summed repulsion magnitude of this step
                          // (written by the repulsion kernel, cleared by the
                          // body kernel once applied)
-  double *s_len, *s_nx, *s_ny, *s_bc, *s_bnx, *s_bny, *s_bfl, *s_fex, *s_fey;  // per-vertex scratch
+  double *s_len, *s_fex, *s_fey;  // per-vertex scratch of rigid bodies that several workgroups share
   // marker bins of fixed capacity per tile, double buffered: the fused
   // kernel consumes (and clears) the current set while the marker advance
   // fills the other one for the next step
@@ -252,7 +252,7 @@ struct Ptrs {
   int* spin_timeouts;        // waits for a bond flag that hit their bound
   int bin_cap;
   int* tile_inst;
-  int *lig_body, *lig_elem, *l2r, *r2l, *lig_flag;
+  int *l2r, *r2l, *lig_flag;
   int *lig_va, *lig_vb;  // global vertex ids of a ligand element's two ends
   double* lig_sigma;     // bond spring constant of each ligand's body
   double* lig_sp;        // per ligand holding a bond: sigma (y_l - y_eq) at X^n (Eq. adhFor),
