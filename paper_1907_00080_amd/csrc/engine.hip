@@ -223,8 +223,8 @@ constexpr int kMaxRings = 4;
 struct RingPool {
   std::mutex mu;
   struct OfDevice {
-    std::vector<Ring> idle;
-    int made = 0;
+    Ring idle[kMaxRings];
+    int nidle = 0, made = 0;
   };
   std::map<int, OfDevice> dev;
   int contexts = 0;   // bound
@@ -241,19 +241,24 @@ void ring_context_bound() {
 }
 
 void ring_context_closed() {
-  std::vector<Ring> out;
+  RingPool& P = ring_pool();
   {
-    RingPool& P = ring_pool();
     std::lock_guard<std::mutex> lock(P.mu);
-    if (--P.contexts > 0) return;
-    for (auto& d : P.dev)
-      while (d.second.idle.size() > 1) {
-        out.push_back(d.second.idle.back());
-        d.second.idle.pop_back();
-        --d.second.made;
-      }
+    --P.contexts;
   }
-  for (Ring& r : out) r.drop();
+  for (bool more = true; more;) {
+    Ring r;
+    {
+      std::lock_guard<std::mutex> lock(P.mu);
+      for (auto& d : P.dev)
+        if (P.contexts == 0 && !r.mem && d.second.nidle > 1) {
+          r = d.second.idle[--d.second.nidle];
+          --d.second.made;
+        }
+    }
+    more = r.mem != nullptr;
+    r.drop();
+  }
 }
 
 // A ring for one readback on stream s (ring.mem null: none to be had).
@@ -261,34 +266,31 @@ struct RingUse {
   Ring ring;
   bool busy = false;   // copies into the ring may be under way
   hipStream_t s;
-  int device;
+  RingPool::OfDevice* of = nullptr;
   explicit RingUse(hipStream_t stream) : s(stream) {
     const OnDeviceOf on(stream);
-    device = on.device;
     RingPool& P = ring_pool();
     {
       std::lock_guard<std::mutex> lock(P.mu);
-      RingPool::OfDevice& d = P.dev[device];
-      if (!d.idle.empty()) {
-        ring = d.idle.back();
-        d.idle.pop_back();
+      of = &P.dev[on.device];
+      if (of->nidle > 0) {
+        ring = of->idle[--of->nidle];
         return;
       }
-      if (d.made == kMaxRings) return;
-      ++d.made;
+      if (of->made == kMaxRings) return;
+      ++of->made;
     }
     if (ring.make()) return;
     std::lock_guard<std::mutex> lock(P.mu);
-    --P.dev[device].made;
+    --of->made;
   }
   ~RingUse() {
     if (!ring.mem) return;
     // (after an error: a ring that may still be written is not used again)
     const bool lost = busy && hipStreamSynchronize(s) != hipSuccess;
-    RingPool& P = ring_pool();
-    std::lock_guard<std::mutex> lock(P.mu);
-    if (lost) --P.dev[device].made;
-    else P.dev[device].idle.push_back(ring);
+    std::lock_guard<std::mutex> lock(ring_pool().mu);
+    if (lost) --of->made;
+    else of->idle[of->nidle++] = ring;
   }
 };
 
