@@ -174,16 +174,21 @@ struct Piece {
 
 // Makes the device of a stream current while it lives: an event can be recorded
 // only on streams of the device that was current when it was created, and the
-// stream a context is bound to may be another device's (the null stream is the
-// current device's).
+// stream a context is bound to may be another device's.
 struct OnDeviceOf {
   int was = -1;
-  hipDevice_t device = 0;
+  int device = 0;
   explicit OnDeviceOf(hipStream_t s) {
-    if (hipGetDevice(&was) == hipSuccess && hipStreamGetDevice(s, &device) == hipSuccess && device != was)
-      (void)hipSetDevice(device);
-    else
-      was = -1;
+    if (hipGetDevice(&device) != hipSuccess) return;
+    // the current device's own streams (hipStreamGetDevice faults on the legacy one)
+    if (s == nullptr || s == hipStreamLegacy || s == hipStreamPerThread) return;
+    hipDevice_t d = 0;
+    if (hipStreamGetDevice(s, &d) != hipSuccess) {
+      (void)hipGetLastError();   // a handle that it does not know: the current device
+    } else if (d != device && hipSetDevice(d) == hipSuccess) {
+      was = device;
+      device = d;
+    }
   }
   ~OnDeviceOf() {
     if (was >= 0) (void)hipSetDevice(was);

@@ -38,6 +38,7 @@ inline thread_local hipError_t last = hipSuccess;   // what hipGetLastError give
 inline int refuse_malloc = 0;                  // refuse this many pinned allocations
 inline int fail_copy = 0;                      // this many copies to the host from now, one fails
 inline int refuse_launch = 0;                  // refuse this many launches
+inline bool unknown_stream = false;            // hipStreamGetDevice refuses
 inline int wait_us = 0;                        // what waiting for an event takes
 inline std::map<hipStream_t, Stream> streams;
 inline std::set<Event*> events;
@@ -47,7 +48,7 @@ inline long long mallocs = 0, frees = 0;
 inline std::vector<std::pair<char*, size_t>> d2h;   // targets of copies to the host
 
 inline hipStream_t stream_of(int device, int k = 0) { return (hipStream_t)(uintptr_t)(0x1000 + 256 * k + device); }
-inline int device_of(hipStream_t s) { return s ? (int)((uintptr_t)s & 0xff) : current; }
+inline int device_of(hipStream_t s) { return (uintptr_t)s > 2 ? (int)((uintptr_t)s & 0xff) : current; }
 inline hipError_t err(hipError_t e) {
   if (e != hipSuccess) last = e;
   return e;
@@ -81,7 +82,12 @@ FAKE hipError_t hipSetDevice(int d) {
   fake::current = d;
   return hipSuccess;
 }
-FAKE hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = fake::device_of(s); return hipSuccess; }
+FAKE hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) {
+  if ((uintptr_t)s < 2) std::abort();   // as the real one does on hipStreamLegacy
+  if (fake::unknown_stream) return fake::err(hipErrorInvalidHandle);
+  *d = fake::device_of(s);
+  return hipSuccess;
+}
 FAKE hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 FAKE hipError_t hipGetLastError() {
   const hipError_t e = fake::last;

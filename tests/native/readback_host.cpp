@@ -23,7 +23,10 @@ struct Ctx {
   char* ws = nullptr;
   int nx, ny, nv;
 
-  Ctx(int nx_, int ny_, int nv_, int device, int k = 0, double repulsion = 0.0) : nx(nx_), ny(ny_), nv(nv_) {
+  explicit Ctx(hipStream_t s) : Ctx(64, 32, 20, s, 0.0) {}
+  Ctx(int nx_, int ny_, int nv_, int device, int k = 0, double repulsion = 0.0)
+      : Ctx(nx_, ny_, nv_, fake::stream_of(device, k), repulsion) {}
+  Ctx(int nx_, int ny_, int nv_, hipStream_t stream, double repulsion) : nx(nx_), ny(ny_), nv(nv_) {
     lbib_lattice_desc d;
     std::memset(&d, 0, sizeof(d));
     d.nx = nx;
@@ -46,7 +49,7 @@ struct Ctx {
     CHECK(lbib_workspace_query(h, &n) == LBIB_OK);
     CHECK(posix_memalign((void**)&ws, 256, n) == 0);
     std::memset(ws, 0x5a, n);
-    CHECK(lbib_bind(h, ws, n, fake::stream_of(device, k)) == LBIB_OK);
+    CHECK(lbib_bind(h, ws, n, stream) == LBIB_OK);
     CHECK(lbib_finalize_setup(h) == LBIB_OK);
   }
   void close() {
@@ -83,6 +86,18 @@ static void device() {
   d.read_all();
   c.read_all();
   CHECK(fake::current == 1);
+  // a stream whose device the runtime does not tell: the current device's
+  fake::unknown_stream = true;
+  fake::current = 0;
+  d.read_all();
+  CHECK(hipGetLastError() == hipSuccess);
+  fake::unknown_stream = false;
+  // the null stream, the legacy and the per-thread one
+  for (uintptr_t h = 0; h < 3; ++h) {
+    Ctx e((hipStream_t)h);
+    e.read_all();
+    e.close();
+  }
   c.close();
   d.close();
 }

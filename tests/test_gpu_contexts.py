@@ -84,3 +84,23 @@ def test_marker_reads_after_a_refused_call_of_the_program():
     finally:
         s.lib.hipGetLastError()   # taken back: other calls of this process look at it
     s.close()
+
+
+@pytest.mark.parametrize("handle", [0, 1, 2])
+def test_default_legacy_and_per_thread_streams(handle):
+    """A context on the null stream, the legacy or the per-thread one."""
+    import torch
+    print(f"[gpu-contexts] stream handle {handle}", flush=True)
+
+    class Stream:
+        cuda_stream = handle
+
+    ref = pkg.Sim(_small(0))
+    torch.cuda.synchronize()
+    s = pkg.Sim(_small(0), stream=Stream())
+    for a in (ref, s):
+        a.step(3)
+    for a, b in zip([*ref.fields(), ref.markers(1)], [*s.fields(), s.markers(1)]):
+        assert np.array_equal(a, b)
+    ref.close()
+    s.close()
