@@ -220,7 +220,7 @@ def main():
                     help="timed windows of K steps; the first is the reported region, the "
                          "median of all is reported beside it")
     ap.add_argument("--tile", default="auto",
-                    help="TXxTY, or auto: tile, step form and cache hints from the autotuner")
+                    help="TXxTY, or auto: tile and launch settings from the autotuner")
     ap.add_argument("--step-mode", type=int, default=None,
                     help="with a fixed --tile: step mode (1, 2 or 3: names of one form)")
     ap.add_argument("--launch", type=int, default=0,
@@ -569,7 +569,7 @@ def _timed(torch, ctx, steps):
 
 def batched_vs_plain(pkg, torch, args, n_inst, steps):
     """Sweep of uneven capillary instances (20-100 um long, 200 rows): one
-    batch with autotuned tile, step form, cache hints and graph chunk, against
+    batch with autotuned tile, cache hints and graph chunk, against
     the same instances run one after another (a) through plain launches (no
     graphs, default tile) and (b) graph-captured with the configuration the
     autotuner picks for a single instance of median length."""

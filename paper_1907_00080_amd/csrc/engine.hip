@@ -622,11 +622,13 @@ StepArgs step_args(const lbib_ctx* c) {
   a.lb_wpc = c->lb_wpc;
   a.n_cu = c->n_cu;
   a.any_mls = 0;
-  // automatic cache hints: non-temporal loads and stores on a single lattice
-  // whose two population buffers stay well inside the 256 MB last-level cache
-  // (28.8 MB measured), plain accesses otherwise (with 256-byte aligned rows
-  // they measured as fast or faster on 320 MB, and on batches); the
-  // autotuner times all three forms
+  // automatic cache hints (two buffers only): non-temporal loads and stores on
+  // a single lattice whose two population buffers stay well inside the 256 MB
+  // last-level cache (28.8 MB measured), plain accesses otherwise: as fast or
+  // faster on one lattice of 320 MB (256-byte aligned rows) and on a batch
+  // inside the cache (6 lattices, 109 MB: 36.7 us a step, 41.6 with both hints).
+  // On batches beyond it they are not: 16 lattices, 312 MB, 93.8 and 87.4; 64,
+  // 1126 MB, 308 and 268.  The autotuner times all three forms.
   const double pop_bytes = 2.0 * 9.0 * (double)c->nodes * (double)elem_size(c->dtype);
   a.nt_mode = c->cache_hints >= 0 ? c->cache_hints
                                   : (c->ninst == 1 && pop_bytes <= 128.0 * 1024 * 1024 ? 3 : 0);
@@ -937,7 +939,7 @@ void resolve_step_mode(lbib_ctx* c) {
 }
 
 // n steps of three kernels each (four with the repulsion): bodies, lattice,
-// advance.  Every step form runs these.  Two others were measured and gone:
+// advance.  Every step mode runs these.  Two other forms were measured and are gone:
 // a body kernel per body that also finished the previous step's advance
 // (us per step, against these three: 256x64 22.0 and 18.4, 2000x200 27.5 and
 // 23.4, six Couette boxes 43.7 and 31.9), and the lattice tiles without

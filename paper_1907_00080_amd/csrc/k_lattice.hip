@@ -104,10 +104,11 @@ __device__ __forceinline__ void spread_rows(const Ptrs<T>& p, const LatDev& L, c
 // streaming is a permutation of the nodes, so every population is read
 // exactly once per step and its cache line is worth nothing to this kernel
 // afterwards; measured on one lattice the hint gains a few per cent, on
-// batches of many small lattices it loses.  NT bit 1: the population stores
-// carry it too, which measured faster on a lattice whose populations stay in
-// the last-level cache and much slower on one larger than it.  The host
-// chooses per context.
+// batches it gains 5 % (16 lattices, 312 MB in two buffers) or loses 7 to 12
+// (64, 1126 MB; 6, 109 MB).  NT bit 1: the population stores carry it too,
+// which measured faster on a lattice whose populations stay in the last-level
+// cache, much slower on one larger than it, and 7 to 13 % faster than plain on
+// batches larger than it.  The host chooses per context.
 // One tile, the g-th of the launch's virtual grid of 8 * kXcdBands * band
 // workgroups (band = tiles per band): g mod 8 is the XCD the hardware gives
 // workgroup g, whose (g / 8)-th workgroup takes the tiles of its bands in

@@ -1,4 +1,4 @@
-"""Autotuner for batched sweeps: tile shape, step form, cache hints, graph chunk,
+"""Autotuner for batched sweeps: tile shape, cache hints, graph chunk,
 lattice-kernel launch form and population streaming (host logic).
 
 A batch advances many uneven capillary instances together (one launch per
@@ -24,7 +24,7 @@ from typing import Callable, Iterable, Optional, Sequence, Tuple
 
 TILES: Tuple[Tuple[int, int], ...] = ((64, 4), (128, 2), (32, 8), (256, 1))
 GRAPH_STEPS: Tuple[int, ...] = (10, 100)
-STEP_MODES: Tuple[int, ...] = (1, 2, 3)   # names of one step form, three kernels
+STEP_MODES: Tuple[int, ...] = (1, 2, 3)   # names of one launch form, three kernels
 CACHE_HINTS: Tuple[int, ...] = (0, 1, 3)   # plain, non-temporal loads, non-temporal loads + stores
 # lattice-kernel launch: one workgroup per tile (0) or a persistent grid of
 # that many workgroups per CU; timed for the best of the other choices
@@ -38,7 +38,7 @@ def signature(workloads: Sequence, dtype: str) -> str:
     """Stable key of a batch: dtype plus, per instance, lattice shape, wall
     mode, lattice <-> marker transfer (and MLS weight), whether the vertex
     repulsion is on, body count and marker count: everything that changes
-    which kernel variants and step forms run."""
+    which kernel variants run."""
     h = hashlib.sha256()
     h.update(str(dtype).encode())
     for w in workloads:
@@ -103,8 +103,9 @@ def autotune(workloads: Sequence, dtype: str = "f32", cache: Optional[str] = Non
              lattice_launches: Sequence[int] = LATTICE_LAUNCHES,
              streamings: Sequence[int] = STREAMINGS,
              measure: Optional[Callable] = None) -> dict:
-    """Pick the tile shape, step form, cache hints and graph chunk for a batch
-    of `workloads`, then the lattice kernel's launch form for that pick.
+    """Pick the tile shape, cache hints and graph chunk for a batch of
+    `workloads`, then the lattice kernel's launch form for that pick.  (The
+    step modes are names of one form; the record names the first.)
 
     Returns {"tile": [tx, ty], "graph_steps": g, "step_mode": m, "cache_hints": c,
     "lattice_launch": w, "streaming": s, "ms_per_step": t, "mlups": ...,
